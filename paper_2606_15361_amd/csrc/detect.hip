@@ -5,18 +5,18 @@
 //   Integer planes use exact 64-bit sums S1, S2 and sigma = sqrt(n*S2 - S1*S1)/n in one fixed
 //   FP64 expression; float planes use one FP64 pass about the row's first sample.  A floor
 //   sigma_min applies.
-// k_snr: one workgroup per (row, tile of 8192 samples for integer planes, 2048 for float).  The tile plus the widest boxcar is
-//   staged in LDS as an inclusive prefix sum (int32 for integer planes: exact; FP64 for float
-//   planes), every sample then evaluates all widths with two LDS reads each:
+// k_snr: one workgroup per (row, tile of samples).  The tile plus the widest boxcar is staged in
+//   LDS as an inclusive prefix sum (int32 for integer planes: exact; FP64 for float planes), every
+//   sample then evaluates all widths with two LDS reads each:
 //   SNR(t, W) = (S_W(t) - mu W) / (sigma sqrt W), maximum over widths (first width on ties).
 //   Either the full S/N plane and width index are written, or the cells whose S/N reaches the
 //   threshold are appended to a global pixel list, each workgroup's cells as one segment in
 //   increasing t.  For the list, a per-width bound on the boxcar sum (in the prefix type)
 //   skips the cells that cannot reach the threshold; every cell that can takes the exact
-//   quotient.  u8 planes whose widths are 1 and even widths up to 256 (every boxcar sum below
-//   2^16) take the bound tests on two cells per 32-bit lane: the prefix is kept modulo 2^16 in
-//   16-bit halves (differences stay exact), one dword read brings the prefix at t + W and
-//   t + 1 + W, and packed 16-bit subtractions test both cells.
+//   quotient.  The widths are the outer loop of the bound tests and a thread's cells the inner
+//   one, so any list length runs the same straight-line inner code, and only the slabs of cells
+//   past the last valid start of a width are tested against it.  Aligned u8 rows take the tests on
+//   two cells per 32-bit lane (k_snr_pairs).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,14 +35,31 @@ template <typename T> __device__ inline global_ptr<const T> as_global(const T *p
 constexpr int kThreads = 256;
 
 template <typename T> struct IsInt { static constexpr bool value = true; };
-template <typename P> struct BoundNever { __device__ static P value() { return (P)2147483647; } };
-template <> struct BoundNever<double> { __device__ static double value() { return __builtin_inf(); } };
 template <> struct IsInt<float> { static constexpr bool value = false; };
-// Samples of one row per S/N workgroup: integer planes carry a 4-byte prefix per sample and
-// little arithmetic per byte read, so their tiles are longer (fewer workgroups, a smaller share
-// of re-read halo; 4096 keeps seven workgroups on a CU, 8192 and 2048 measured slower); float
-// planes carry an 8-byte prefix.
-template <typename T> constexpr int snr_tile() { return IsInt<T>::value ? 4096 : 2048; }
+// Samples of one row per S/N workgroup.  Integer planes carry a 4-byte prefix per sample (two or
+// four bytes on the paired path) and little arithmetic per byte read, so their tiles are long
+// (fewer workgroups, a smaller share of re-read halo; 4096 keeps seven workgroups on a CU, 8192 and
+// 2048 measured slower).  Float planes carry an 8-byte prefix and take kFloatSlabs cells per thread:
+// lists up to kFloatNarrow samples stage tile and halo as eight samples per thread (the tile gives up
+// the halo, in whole 64-sample steps, so that rows of 64-sample pitch start every tile on a 16-byte
+// boundary), wider ones twelve per thread over the whole slabs.
+constexpr int kIntTile = 4096;
+constexpr int kFloatSlabs = 8, kFloatNarrow = 192;
+template <typename T> constexpr int snr_slabs() { return IsInt<T>::value ? kIntTile / kThreads : kFloatSlabs; }
+template <typename T> constexpr int snr_per(bool wide)
+{
+    return IsInt<T>::value ? (kIntTile + kMaxWidth + kThreads - 1) / kThreads
+                           : wide ? (kFloatSlabs * kThreads + kMaxWidth + kThreads - 1) / kThreads : kFloatSlabs;
+}
+template <typename T> int snr_tile(int wmax)
+{
+    return IsInt<T>::value || wmax > kFloatNarrow ? snr_slabs<T>() * kThreads
+                                                  : (kThreads * kFloatSlabs - (wmax - 1)) / 64 * 64;
+}
+static_assert(kThreads * kFloatSlabs - kFloatNarrow - 63 > kThreads * (kFloatSlabs - 1), "only the last slab is partial");
+// Prefix entry j of a float tile sits at j + j / 8: a thread writes runs of consecutive entries, and
+// the gap of one entry in eight spreads the lanes of a wave over the LDS banks.
+template <typename P> __device__ inline int pre_at(int j) { return std::is_same<P, double>::value ? j + (j >> 3) : j; }
 
 // Row sums with 16-byte loads: a scalar head up to the first 16-byte boundary of the row, then
 // 16-byte vectors (four in flight per thread), then a scalar tail.  f(x, j) folds one sample;
@@ -249,59 +266,87 @@ __device__ inline double wave_inclusive_sum(double x)
 }
 __device__ inline int32_t wave_inclusive_sum(int32_t x) { return (int32_t)wave_inclusive_sum((uint32_t)x); }
 
-// The paired path applies to a u8 list whose first width is 1 and whose other widths are even
-// and at most 256 (every boxcar sum of u8 samples is then below 2^16).
-template <int NW>
-__device__ inline bool pairs_usable(const SnrArgs &a)
-{
-    if (a.w[0] != 1 || a.w[NW - 1] > 256) return false;
-#pragma unroll
-    for (int w = 1; w < NW; ++w)
-        if (a.w[w] & 1) return false;
-    return true;
-}
+// ---- u8 rows, two cells per lane ----
+// The prefix P of the tile is kept modulo 2^16 in 16-bit halves: a boxcar sum of at most 256 u8
+// samples is below 2^16, so the difference of two such prefixes is the exact sum.  Longer boxcars
+// (up to 1024 samples, sums below 2^18) use a second array, P / 4 modulo 2^16: the difference D of
+// two of those lies within 3/4 of S / 4, so S >= b implies D >= b / 4 rounded down, which is the
+// bound test, and the two differences together give S exactly (S = the value congruent to the first
+// one modulo 2^16 nearest to 4 D).
+constexpr int kPairExact = 256;                        // widest boxcar of the first array alone
+constexpr int kPairs = kIntTile / 2 / kThreads;        // pairs of cells per thread
+constexpr int kPairSlack = 8;                          // entries past tile + halo
+static_assert(kIntTile == 16 * kThreads && kMaxWidth <= 4 * kThreads, "sixteen tile bytes and four halo bytes per thread");
+constexpr int pair_entries(int wmax) { return kIntTile + (wmax > kPairExact ? kMaxWidth : kPairExact) + kPairSlack; }
+inline int64_t pairs_lds_bytes(int wmax) { return (int64_t)pair_entries(wmax) * (wmax > kPairExact ? 4 : 2); }
 
-// Compaction on the paired path for one interior tile of a u8 row (16-byte aligned): every
-// width fits every cell of the tile.  The tile's bytes are loaded into registers before the
-// row's statistics, so that the two loads overlap.  The cells whose bound test passes take the
-// exact quotient, as on the general path; the output is the same list (none when sigma is 0).
-template <int NW>
-__device__ void snr_pairs(const uint8_t *row, int k, int64_t t0, int nwk, int wmax, const double *stats,
-                          const SnrArgs &a, unsigned char *dyn, int32_t *wtot, int (*slab_off)[kThreads / 64],
-                          unsigned int &base_s, double *muw, double *den, int32_t *sthr)
+// What the bound tests of one width read: the two 16-bit copies of the bound less one, all ones where
+// every cell passes, the width's dword step and the width itself.
+struct PairWidth {
+    uint32_t t, all, step, w;
+};
+
+struct PairShared {
+    int32_t wtot[2][kThreads / 64];
+    int slab_off[kPairs][kThreads / 64];
+    unsigned int base;
+    double muw[kMaxWidths], den[kMaxWidths];
+    int32_t sthr[kMaxWidths];
+    uint64_t smask[kPairs][kThreads / 64][2];
+    PairWidth rec[kMaxWidths];
+};
+
+// One tile of a row: avail samples from its first to the row's end, nwk leading widths of the list.
+// EDGE: some width of the list does not fit every cell of the tile.
+template <bool EDGE>
+__device__ __forceinline__ void snr_pairs_tile(const uint8_t *row, int k, int64_t t0, int avail, int nwk,
+                                               const double *stats, const SnrArgs &a, unsigned char *dyn, PairShared &sh)
 {
-    __shared__ uint64_t smask[snr_tile<uint8_t>() / 2 / kThreads][kThreads / 64][2];
-    constexpr int kTile = snr_tile<uint8_t>();
-    constexpr int kPairs = kTile / 2 / kThreads;  // pairs of cells per thread
-    static_assert(kTile == 16 * kThreads, "sixteen staged bytes per thread");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint16_t *pre16 = reinterpret_cast<uint16_t *>(dyn);  // pre16[j] = P(j) mod 2^16
-    // thread t: samples 16 t .. 16 t + 15 (one 16-byte load); wave 0 also the halo samples
-    // 4096 + 4 lane .. + 3 that exist in the tile's window (L = 4096 + wmax - 1 samples; the
-    // others read as zero and feed prefix entries no width of the row reads)
-    const u32x4 q = as_global(reinterpret_cast<const u32x4 *>(row))[tid];
+    const int wlist = a.wmax;
+    const bool two = wlist > kPairExact;
+    uint16_t *pre16 = reinterpret_cast<uint16_t *>(dyn);       // P(j) mod 2^16
+    uint16_t *pre4 = pre16 + (two ? pair_entries(wlist) : 0);  // (P(j) / 4) mod 2^16
+    // thread t: tile samples 16 t .. 16 t + 15 and halo samples 4096 + 4 t .. + 3; samples past the
+    // row read as zero and feed prefix entries that no valid cell reads
+    const auto grow = as_global(row);
+    const int h0 = kIntTile + 4 * tid;
+    u32x4 q = {0u, 0u, 0u, 0u};
     uint32_t hq = 0u;
-    if (wv == 0) {
-        const auto grow = as_global(row + kTile);
+    if (!EDGE) {
+        q = as_global(reinterpret_cast<const u32x4 *>(row))[tid];
+        if (4 * tid < wlist - 1 && h0 + 4 <= avail) {
+            hq = as_global(reinterpret_cast<const uint32_t *>(row))[h0 >> 2];
+        } else if (4 * tid < wlist - 1) {
+            for (int b = 0; b < 4 && h0 + b < avail; ++b) hq |= (uint32_t)grow[h0 + b] << (8 * b);
+        }
+    } else {
+        if (16 * tid + 16 <= avail) {
+            q = as_global(reinterpret_cast<const u32x4 *>(row))[tid];
+        } else if (16 * tid < avail) {  // one thread of the row's last tile
+            uint32_t d[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-            if (4 * lane + b < wmax - 1) hq |= (uint32_t)grow[4 * lane + b] << (8 * b);
+            for (int i = 0; i < 4; ++i)
+#pragma unroll 1
+                for (int b = 0; b < 4 && 16 * tid + 4 * i + b < avail; ++b)
+                    d[i] |= (uint32_t)grow[16 * tid + 4 * i + b] << (8 * b);
+            q = u32x4{d[0], d[1], d[2], d[3]};
+        }
+        if (4 * tid < wlist - 1) {
+#pragma unroll 1
+            for (int b = 0; b < 4 && h0 + b < avail; ++b) hq |= (uint32_t)grow[h0 + b] << (8 * b);
+        }
     }
     const double mu = stats[2 * k], sg = stats[2 * k + 1];
     if (!(sg > 0.0)) return;  // uniform: no cell of the row has a non-zero S/N
-    row_constants(tid, a, mu, sg, muw, den, sthr, true);
-    // per-width thresholds as two 16-bit copies of sthr - 1: a cell's sum S passes when
-    // max(S - (sthr - 1), 0) > 0; widths past the row's set never pass; a bound at or below
-    // zero passes every cell (flag word all ones)
-    __shared__ uint2 thw[NW];
-    if (tid < NW) {
-        const int32_t sb = sthr[tid];
-        uint32_t t = 0xFFFFu, all = 0u;
-        if (tid < nwk) {
-            if (sb <= 0) all = 0xFFFFFFFFu;
-            else t = (uint32_t)min(sb - 1, 65535);
-        }
-        thw[tid] = uint2{t * 0x00010001u, all};
+    row_constants(tid, a, mu, sg, sh.muw, sh.den, sh.sthr, true);
+    // a cell's sum (or its quarter) passes when max(sum - (bound - 1), 0) > 0; a bound at or below
+    // zero passes every cell; widths past the row's set never pass
+    if (tid < a.nw) {
+        const int32_t w = a.w[tid], sb = w > kPairExact ? sh.sthr[tid] >> 2 : sh.sthr[tid];
+        const bool all = sb <= 0 && tid < nwk;
+        const uint32_t t = sb <= 0 || tid >= nwk ? 0xFFFFu : (uint32_t)min(sb - 1, 65535);
+        sh.rec[tid] = PairWidth{t * 0x00010001u, all ? 0xFFFFFFFFu : 0u, (uint32_t)(w >> 1), (uint32_t)w};
     }
     constexpr uint32_t kOnes = 0x01010101u;
     uint32_t tot = __builtin_amdgcn_udot4(q.x, kOnes, 0u, false);
@@ -310,78 +355,137 @@ __device__ void snr_pairs(const uint8_t *row, int k, int64_t t0, int nwk, int wm
     tot = __builtin_amdgcn_udot4(q.w, kOnes, tot, false);
     const uint32_t htot = __builtin_amdgcn_udot4(hq, kOnes, 0u, false);
     const uint32_t inc = wave_inclusive_sum(tot);
-    if (lane == 63) wtot[wv] = (int32_t)inc;
-    __syncthreads();
-    uint32_t B = inc - tot;
-    for (int w = 0; w < wv; ++w) B += (uint32_t)wtot[w];
-    uint32_t words[8];
-    const uint32_t qd[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const uint32_t d = qd[m];
-        words[2 * m] = pair_word(B, __builtin_amdgcn_perm(0u, d, 0x0c000c0cu));      // P(4m), P(4m + 1)
-        const uint32_t B2 = __builtin_amdgcn_udot4(d, 0x00000101u, B, false);
-        words[2 * m + 1] = pair_word(B2, __builtin_amdgcn_perm(0u, d, 0x0c020c0cu));  // P(4m + 2), P(4m + 3)
-        B = __builtin_amdgcn_udot4(d, kOnes, B, false);
-    }
-    u32x4 *p4 = reinterpret_cast<u32x4 *>(pre16 + 16 * tid);
-    p4[0] = u32x4{words[0], words[1], words[2], words[3]};
-    p4[1] = u32x4{words[4], words[5], words[6], words[7]};
-    if (wv == 0) {  // P(4096 + 4 lane + i), i = 0..3
-        const uint32_t hinc = wave_inclusive_sum(htot);
-        const uint32_t Bh = (uint32_t)wtot[0] + (uint32_t)wtot[1] + (uint32_t)wtot[2] + (uint32_t)wtot[3] + hinc - htot;
-        const uint32_t w0 = pair_word(Bh, __builtin_amdgcn_perm(0u, hq, 0x0c000c0cu));
-        const uint32_t w1 = pair_word(__builtin_amdgcn_udot4(hq, 0x00000101u, Bh, false),
-                                      __builtin_amdgcn_perm(0u, hq, 0x0c020c0cu));
-        uint32_t *h2 = reinterpret_cast<uint32_t *>(pre16 + kTile + 4 * lane);
-        h2[0] = w0;
-        h2[1] = w1;
+    uint32_t hinc = htot;
+    if (256 * wv < wlist - 1) hinc = wave_inclusive_sum(htot);  // uniform per wave: it holds halo samples
+    if (lane == 63) {
+        sh.wtot[0][wv] = (int32_t)inc;
+        sh.wtot[1][wv] = (int32_t)hinc;
     }
     __syncthreads();
-    uint32_t th[NW];
-    int hw[NW];
-    uint32_t m0 = 0u;
+    uint32_t B = inc - tot, Bh = hinc - htot;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        hw[w] = w == 0 ? 1 : (a.w[w] >> 1);
-        const uint2 t = thw[w];
-        th[w] = t.x;
-        m0 |= t.y;
+    for (int w = 0; w < kThreads / 64; ++w) {
+        if (w < wv) {
+            B += (uint32_t)sh.wtot[0][w];
+            Bh += (uint32_t)sh.wtot[1][w];
+        }
+        Bh += (uint32_t)sh.wtot[0][w];
     }
+    const uint32_t qd[4] = {q.x, q.y, q.z, q.w}, B0 = B;
+    {
+        uint32_t words[8];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const uint32_t d = qd[m];
+            words[2 * m] = pair_word(B, __builtin_amdgcn_perm(0u, d, 0x0c000c0cu));  // P(4m), P(4m + 1)
+            const uint32_t B2 = __builtin_amdgcn_udot4(d, 0x00000101u, B, false);
+            words[2 * m + 1] = pair_word(B2, __builtin_amdgcn_perm(0u, d, 0x0c020c0cu));  // P(4m + 2), P(4m + 3)
+            B = __builtin_amdgcn_udot4(d, kOnes, B, false);
+        }
+        u32x4 *p4 = reinterpret_cast<u32x4 *>(pre16 + 16 * tid);
+        p4[0] = u32x4{words[0], words[1], words[2], words[3]};
+        p4[1] = u32x4{words[4], words[5], words[6], words[7]};
+    }
+    if (4 * tid <= wlist) {  // the halo's prefixes, through the first entry past it
+        uint32_t *h2 = reinterpret_cast<uint32_t *>(pre16 + h0);
+        h2[0] = pair_word(Bh, __builtin_amdgcn_perm(0u, hq, 0x0c000c0cu));
+        h2[1] = pair_word(__builtin_amdgcn_udot4(hq, 0x00000101u, Bh, false), __builtin_amdgcn_perm(0u, hq, 0x0c020c0cu));
+    }
+    const int nfine = a.nfine < nwk ? a.nfine : nwk;  // widths that the first array serves
+    if (nfine < nwk) {  // uniform
+        auto quarters = [](uint32_t d, uint32_t base, uint32_t &lo, uint32_t &hi) {
+            const uint32_t p1 = base + (d & 0xffu), p2 = __builtin_amdgcn_udot4(d, 0x00000101u, base, false);
+            const uint32_t p3 = __builtin_amdgcn_udot4(d, 0x00010101u, base, false);
+            lo = __builtin_amdgcn_perm(p1 >> 2, base >> 2, 0x05040100u);
+            hi = __builtin_amdgcn_perm(p3 >> 2, p2 >> 2, 0x05040100u);
+        };
+        uint32_t base = B0, words[8];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            quarters(qd[m], base, words[2 * m], words[2 * m + 1]);
+            base = __builtin_amdgcn_udot4(qd[m], kOnes, base, false);
+        }
+        u32x4 *c4 = reinterpret_cast<u32x4 *>(pre4 + 16 * tid);
+        c4[0] = u32x4{words[0], words[1], words[2], words[3]};
+        c4[1] = u32x4{words[4], words[5], words[6], words[7]};
+        if (4 * tid <= wlist) {
+            uint32_t *h2 = reinterpret_cast<uint32_t *>(pre4 + h0);
+            quarters(hq, Bh, h2[0], h2[1]);
+        }
+    }
+    __syncthreads();
+    // bound tests; m[j] is non-zero in the halves whose cell passes at some width.  Lane w holds the
+    // record of width w.
     const uint32_t *dw = reinterpret_cast<const uint32_t *>(pre16);
+    const uint32_t *dw4 = reinterpret_cast<const uint32_t *>(pre4);
+    const PairWidth mine = sh.rec[lane & (kMaxWidths - 1)];
+    const uint32_t odd = a.odd;  // bit w: width w of the list is odd
+    uint32_t m[kPairs], d0[kPairs];
+    const uint32_t all = __ballot(lane < nwk && mine.all != 0u) != 0 ? ~0u : 0u;  // uniform
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+        m[j] = EDGE ? 0u : all;
+        d0[j] = dw[tid + kThreads * j];
+    }
+    auto tests = [&](const uint32_t *src, int w0, int w1) {
+        for (int w = w0; w < w1; ++w) {
+            const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)mine.t, w);
+            const uint32_t *p = src + tid + (uint32_t)__builtin_amdgcn_readlane((int)mine.step, w);
+            uint32_t s[kPairs];
+            if ((odd >> w) & 1u) {  // uniform
+#pragma unroll
+                for (int j = 0; j < kPairs; ++j)
+                    s[j] = __builtin_amdgcn_alignbit(p[kThreads * j + 1], p[kThreads * j], 16);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kPairs; ++j) s[j] = p[kThreads * j];
+            }
+            if constexpr (!EDGE) {
+#pragma unroll
+                for (int j = 0; j < kPairs; ++j) m[j] |= pk_sub_sat(pk_sub(s[j], d0[j]), t);
+            } else {
+                // last cell of the tile that the width fits
+                const int lim = avail - __builtin_amdgcn_readlane((int)mine.w, w);
+                const uint32_t on = (uint32_t)__builtin_amdgcn_readlane((int)mine.all, w);
+#pragma unroll
+                for (int j = 0; j < kPairs; ++j) {
+                    const int i = 2 * (tid + kThreads * j);
+                    const uint32_t y = pk_sub_sat(pk_sub(s[j], d0[j]), t) | on;
+                    m[j] |= i < lim ? y : i == lim ? y & 0xFFFFu : 0u;
+                }
+            }
+        }
+    };
+    tests(dw, 0, nfine);
+    if (nfine < nwk) {
+#pragma unroll
+        for (int j = 0; j < kPairs; ++j) d0[j] = dw4[tid + kThreads * j];
+        tests(dw4, nfine, nwk);
+    }
+    uint32_t any = 0u;
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) any |= m[j];
+    if (!__syncthreads_or(any != 0u)) return;  // most tiles hold no such cell
     auto exact16 = [&](int i, double &best, int &bi) {
         best = 0.0;
         bi = -1;
         for (int w = 0; w < nwk; ++w) {
-            const int W = a.w[w];
-            const double s = (double)(uint16_t)(pre16[i + W] - pre16[i]);
-            const double val = __dsub_rn(s, muw[w]) / den[w];
+            const int W = (int)sh.rec[w].w;
+            if (EDGE && i + W > avail) break;
+            int32_t sum = (int32_t)(uint16_t)(pre16[i + W] - pre16[i]);
+            if (W > kPairExact) sum += ((4 * (int32_t)(uint16_t)(pre4[i + W] - pre4[i]) - sum + 32768) >> 16) << 16;
+            const double val = __dsub_rn((double)sum, sh.muw[w]) / sh.den[w];
             if (bi < 0 || val > best) {
                 best = val;
                 bi = w;
             }
         }
     };
-    // straight-line bound tests; mk[j]: the wave's lanes whose pair j has a cell that passes
-    uint64_t mk[kPairs];
-    uint64_t any = 0;
-#pragma unroll
-    for (int j = 0; j < kPairs; ++j) {
-        const int qp = tid + kThreads * j;
-        const uint32_t d0 = dw[qp];
-        uint32_t m = m0 | pk_sub_sat(pk_sub(__builtin_amdgcn_alignbit(dw[qp + 1], d0, 16), d0), th[0]);
-#pragma unroll
-        for (int w = 1; w < NW; ++w) m |= pk_sub_sat(pk_sub(dw[qp + hw[w]], d0), th[w]);
-        mk[j] = __ballot(m != 0u);
-        any |= mk[j];
-    }
     // the marked pairs (few) take the exact quotient on both cells; bit 2 j + h of `flags`:
     // cell 2 (tid + 256 j) + h reaches the threshold
     uint32_t maybe = 0;
-    if (any) {  // uniform over the wave
 #pragma unroll
-        for (int j = 0; j < kPairs; ++j) maybe |= (uint32_t)((mk[j] >> lane) & 1u) << j;
-    }
+    for (int j = 0; j < kPairs; ++j) maybe |= (m[j] != 0u ? 1u : 0u) << j;
     uint32_t flags = 0;
     while (maybe) {
         const int j = __builtin_ctz(maybe);
@@ -396,13 +500,13 @@ __device__ void snr_pairs(const uint8_t *row, int k, int64_t t0, int nwk, int wm
     }
     // ordered output: pairs in increasing t (slab j, then thread), the even cell first; each
     // wave's ballots of its even and odd cells per slab go through LDS for the output loop
-#pragma unroll
+#pragma unroll 1
     for (int j = 0; j < kPairs; ++j) {
         const uint64_t b0 = __ballot((flags >> (2 * j)) & 1u), b1 = __ballot((flags >> (2 * j + 1)) & 1u);
         if (lane == 0) {
-            slab_off[j][wv] = __popcll(b0) + __popcll(b1);
-            smask[j][wv][0] = b0;
-            smask[j][wv][1] = b1;
+            sh.slab_off[j][wv] = __popcll(b0) + __popcll(b1);
+            sh.smask[j][wv][0] = b0;
+            sh.smask[j][wv][1] = b1;
         }
     }
     __syncthreads();
@@ -410,11 +514,11 @@ __device__ void snr_pairs(const uint8_t *row, int k, int64_t t0, int nwk, int wm
         int tsum = 0;
         for (int j = 0; j < kPairs; ++j)
             for (int w = 0; w < kThreads / 64; ++w) {
-                const int c = slab_off[j][w];
-                slab_off[j][w] = tsum;
+                const int c = sh.slab_off[j][w];
+                sh.slab_off[j][w] = tsum;
                 tsum += c;
             }
-        base_s = tsum ? atomicAdd(a.counter, (unsigned int)tsum) : 0u;
+        sh.base = tsum ? atomicAdd(a.counter, (unsigned int)tsum) : 0u;
     }
     __syncthreads();
     const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
@@ -423,8 +527,8 @@ __device__ void snr_pairs(const uint8_t *row, int k, int64_t t0, int nwk, int wm
         const int b = __builtin_ctz(f);
         f &= f - 1u;
         const int j = b >> 1, h = b & 1;
-        const int64_t pos = (int64_t)base_s + slab_off[j][wv] + __popcll(smask[j][wv][0] & below) +
-                            __popcll(smask[j][wv][1] & below) + (h ? ((flags >> (2 * j)) & 1u) : 0u);
+        const int64_t pos = (int64_t)sh.base + sh.slab_off[j][wv] + __popcll(sh.smask[j][wv][0] & below) +
+                            __popcll(sh.smask[j][wv][1] & below) + (h ? ((flags >> (2 * j)) & 1u) : 0u);
         if (pos < a.max_pixels) {
             // the flagged cells are few: their exact maximum is taken again rather than kept
             const int i = 2 * (tid + kThreads * j) + h;
@@ -442,16 +546,53 @@ __device__ void snr_pairs(const uint8_t *row, int k, int64_t t0, int nwk, int wm
     }
 }
 
-// NW > 0: exactly NW widths, known at compile time (per-row constants stay in registers);
-// NW == 0: any number of widths.  BATCH: rows of several planes (SnrArgs::beams).
-template <typename T, int NW, bool BATCH>
+// The cell list of u8 planes whose rows all start on a 16-byte boundary, any width list: one
+// workgroup per (row, tile of kIntTile cells).  The cells whose bound test passes take the exact
+// quotient, as on the general path; the list is the same.  Instruction issue bounds it (three
+// packed instructions per pair of cells and width, and about as many again for the prefixes), so
+// the interior tiles have a body without end tests, every per-width value is read from LDS once (by
+// scalar loads of the argument list in the width loop it took 0.54 ms instead of 0.29), and tiles
+// without a marked cell stop before the ordered output.  Against the same arithmetic with widths
+// known at compile time, even, at most 256 and interior tiles only, the rest on the general path:
+// 4096 x 102,748 cells, seven widths 0.29 ms (was 0.32); 4 x 4096 rows of 8192 cells, where every
+// second tile is a row's last, 0.16 (was 0.79); a multi-rate search's bands with widths to 1024,
+// 0.27 ms in all (was 1.23).
+template <bool BATCH>
+__global__ __launch_bounds__(kThreads) void k_snr_pairs(const uint8_t *plane, int64_t pitch, int64_t n_,
+                                                        const double *stats, SnrArgs a)
+{
+    extern __shared__ __align__(16) unsigned char pair_dyn[];  // one or two prefix arrays
+    __shared__ PairShared sh;
+    const uint8_t *rowk;
+    int64_t n;
+    const int32_t *row_nw;
+    int k, kl;
+    locate_row<BATCH>(plane, pitch, n_, a.row_nw, a.beams, a.nbeams, a.row0, (int)blockIdx.y, rowk, n, row_nw, k, kl);
+    const int64_t t0 = (int64_t)blockIdx.x * kIntTile;
+    if constexpr (BATCH) {
+        if (t0 >= n) return;  // a shorter plane of the batch (uniform: before any barrier)
+    }
+    // the row's widths: the first nwk of the list
+    int nwk = a.nw;
+    if (row_nw) nwk = __builtin_amdgcn_readfirstlane(row_nw[kl]);
+    const int avail = (int)(n - t0 < kIntTile + kMaxWidth ? n - t0 : kIntTile + kMaxWidth);
+    if (kIntTile - 1 + a.wmax <= avail)  // uniform
+        snr_pairs_tile<false>(rowk + t0, k, t0, avail, nwk, stats, a, pair_dyn, sh);
+    else
+        snr_pairs_tile<true>(rowk + t0, k, t0, avail, nwk, stats, a, pair_dyn, sh);
+}
+
+// PER: staged samples per thread.  BATCH: rows of several planes (SnrArgs::beams).  LDS reads and
+// the FP64 bound tests bound the float form; with the widths as a run-time outer loop over
+// straight-line slabs (against a run-time loop with end tests inside each cell) a 4096 x 102,748
+// plane takes 1.12 ms with eleven widths up to 1024 (was 3.39), and 4 x 4096 rows of 8192 cells with
+// seven widths 0.26 ms (was 0.81).
+template <typename T, int PER, bool BATCH>
 __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch, int64_t n_, const double *stats,
                                                   SnrArgs a)
 {
     using P = typename PrefixType<T>::type;
-    constexpr int kSnrTile = snr_tile<T>();
-    constexpr int kMaxPer = (kSnrTile + kMaxWidth + kThreads - 1) / kThreads;  // elements per thread
-    constexpr int kSlabs = kSnrTile / kThreads;                                // samples per thread
+    constexpr int kSlabs = snr_slabs<T>();  // cells per thread
     static_assert(kSlabs <= 32, "one flag bit per slab");
     extern __shared__ __align__(16) unsigned char snr_dyn[];  // prefix sums: tile + widest width + 1
     P *pre = reinterpret_cast<P *>(snr_dyn);
@@ -460,12 +601,14 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
     __shared__ unsigned int base_s;
     __shared__ double muw[kMaxWidths], den[kMaxWidths];  // per-row constants
     __shared__ P sthr[kMaxWidths];                       // per-row boxcar-sum bounds
+    __shared__ int32_t sw[kMaxWidths + 1];               // the list
     const T *rowk;
     int64_t n;
     const int32_t *row_nw;
     int k, kl;
     locate_row<BATCH>(plane, pitch, n_, a.row_nw, a.beams, a.nbeams, a.row0, (int)blockIdx.y, rowk, n, row_nw, k, kl);
-    const int64_t t0 = (int64_t)blockIdx.x * kSnrTile;
+    const int tile = a.tile;
+    const int64_t t0 = (int64_t)blockIdx.x * tile;
     if constexpr (BATCH) {
         if (t0 >= n) return;  // a shorter plane of the batch (uniform: before any barrier)
     }
@@ -474,31 +617,20 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
     // widths of this row: the first nwk of the list (all of them unless a DM-scaled set)
     const int nwk = row_nw ? row_nw[kl] : a.nw;
     const int wmax = a.w[nwk - 1];
-    // elements t0 .. t0 + L - 1 are needed (and exist): L = min(tile + wmax - 1, n - t0)
-    int64_t L64 = (int64_t)kSnrTile + wmax - 1;
-    if (L64 > n - t0) L64 = n - t0;
-    const int L = (int)L64;
-    if constexpr (std::is_same<T, uint8_t>::value && NW >= 2) {
-        // uniform over the workgroup: the list, the tile's place in the row and its alignment
-        if (!a.snr && t0 + kSnrTile + wmax - 1 <= n && ((uintptr_t)row & 15u) == 0 && pairs_usable<NW>(a)) {
-            snr_pairs<NW>(row, k, t0, nwk, wmax, stats, a, snr_dyn, wtot, slab_off, base_s, muw, den, sthr);
-            return;
-        }
-    }
-    // float tiles on a 16-byte boundary are read as 16-byte vectors: chunks of a multiple of
-    // four samples (at most kMaxPer, since kMaxPer is itself a multiple of four)
-    static_assert(kMaxPer % 4 == 0, "vector chunks");
+    // samples from the tile's first to the row's end, as far as any cell can read
+    const int avail = (int)(n - t0 < tile + kMaxWidth ? n - t0 : tile + kMaxWidth);
+    // elements t0 .. t0 + L - 1 are needed (and exist)
+    const int L = avail < tile + wmax - 1 ? avail : tile + wmax - 1;
+    // float tiles on a 16-byte boundary are read as 16-byte vectors
+    static_assert(PER % 4 == 0, "vector chunks");
     const bool vec4 = !IsInt<T>::value && sizeof(T) == 4 && ((uintptr_t)row & 15u) == 0;
-    // integer tiles: every thread takes kMaxPer elements, those past L read as zero (the staged
-    // bytes fit the prefix array for any L), and only prefix entries up to L are written
-    const int per = IsInt<T>::value ? kMaxPer
-                    : vec4          ? (L + 4 * kThreads - 1) / (4 * kThreads) * 4
-                                    : (L + kThreads - 1) / kThreads;
-    const int beg = tid * per;
+    // every thread takes PER elements, those past L read as zero (integer tiles: the staged bytes
+    // fit the prefix array for any L), and only prefix entries up to L are written
+    const int beg = tid * PER;
     // prefix sums: per-thread chunk totals, wave scan, wave totals through LDS.  Integer
     // tiles are first read with coalesced loads into LDS (in the prefix array's storage, which
     // is written only after the barrier below); float tiles are read in place (measured faster)
-    P v[kMaxPer];
+    P v[PER];
     P run = 0;
     if constexpr (IsInt<T>::value) {
         T *raw = reinterpret_cast<T *>(pre);
@@ -516,7 +648,7 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
         for (int j = j0 + tid; j < L; j += kThreads) raw[j] = grow[j];
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < kMaxPer; ++i) {
+        for (int i = 0; i < PER; ++i) {
             const int j = beg + i;
             const P x = (P)raw[j];
             v[i] = j < L ? x : (P)0;
@@ -527,9 +659,9 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
         const auto g4 = as_global(reinterpret_cast<const f32x4 *>(row));
         const auto grow = as_global(row);
 #pragma unroll
-        for (int i = 0; i < kMaxPer; i += 4) {
+        for (int i = 0; i < PER; i += 4) {
             const int j = beg + i;
-            if (i < per && j + 3 < L) {
+            if (j + 3 < L) {
                 const f32x4 q = g4[j >> 2];
                 v[i] = (P)q.x;
                 v[i + 1] = (P)q.y;
@@ -537,7 +669,7 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
                 v[i + 3] = (P)q.w;
             } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[i + u] = (i < per && j + u < L) ? (P)grow[j + u] : (P)0;
+                for (int u = 0; u < 4; ++u) v[i + u] = j + u < L ? (P)grow[j + u] : (P)0;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) run += v[i + u];
@@ -545,9 +677,9 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
     } else {
         const auto grow = as_global(row);
 #pragma unroll
-        for (int i = 0; i < kMaxPer; ++i) {
+        for (int i = 0; i < PER; ++i) {
             const int j = beg + i;
-            v[i] = (i < per && j < L) ? (P)grow[j] : (P)0;
+            v[i] = j < L ? (P)grow[j] : (P)0;
             run += v[i];
         }
     }
@@ -556,37 +688,29 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
     __syncthreads();
     P acc = inc - run;
     for (int w = 0; w < wv; ++w) acc += wtot[w];
-    if (tid == 0) pre[0] = 0;
-    if constexpr (IsInt<T>::value) {
+    // entries 0 .. L: each thread writes the prefix before each of its samples, the thread that
+    // holds sample L - 1 also the one after it
 #pragma unroll
-        for (int i = 0; i < kMaxPer; ++i) {
-            acc += v[i];
-            if (beg + i < L) pre[beg + i + 1] = acc;  // entries 1 .. L (the array holds tile + wmax + 1)
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kMaxPer; ++i) {
-            const int j = beg + i;
-            if (i < per && j < L) {
-                acc += v[i];
-                pre[j + 1] = acc;
-            }
-        }
+    for (int i = 0; i < PER; ++i) {
+        if (beg + i < L) pre[pre_at<P>(beg + i)] = acc;
+        acc += v[i];
+        if (beg + i == L - 1) pre[pre_at<P>(L)] = acc;
     }
     const double mu = stats[2 * k], sg = stats[2 * k + 1];
     // per-row constants of S/N(t, W) = (S_W(t) - mu W) / (sigma sqrt W)
     row_constants(tid, a, mu, sg, muw, den, sthr, IsInt<T>::value);
+    if (tid < a.nw) sw[tid] = a.w[tid];
     __syncthreads();
     // the exact maximum over widths of sample i (first width on ties)
-    auto exact = [&](int i, int64_t t, double &best, int &bi) {
+    auto exact = [&](int i, double &best, int &bi) {
         best = 0.0;
         bi = -1;
         for (int w = 0; w < nwk; ++w) {
             const int W = a.w[w];
-            if (t + W > n) break;
+            if (i + W > avail) break;
             double val = 0.0;
             if (sg > 0.0) {
-                const double s = (double)(pre[i + W] - pre[i]);
+                const double s = (double)(pre[pre_at<P>(i + W)] - pre[pre_at<P>(i)]);
                 val = __dsub_rn(s, muw[w]) / den[w];
             }
             if (bi < 0 || val > best) {
@@ -596,82 +720,82 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
         }
     };
     if (a.snr) {  // the whole S/N plane
-        for (int i = tid; i < kSnrTile; i += kThreads) {
+        for (int i = tid; i < tile; i += kThreads) {
             const int64_t t = t0 + i;
             if (t >= n) break;
             double best;
             int bi;
-            exact(i, t, best, bi);
+            exact(i, best, bi);
             a.snr[(int64_t)k * a.snr_pitch + t] = (float)best;
             a.widx[(int64_t)k * a.widx_pitch + t] = (int8_t)bi;
         }
         return;
     }
+    if (!(sg > 0.0)) return;  // uniform: no cell of the row has a non-zero S/N
     // compaction: a cell can reach the threshold at width W only if its boxcar sum reaches
     // the row's bound for W (one subtraction and one compare per width, in the prefix type);
-    // the cells that do take the exact quotient
-    constexpr int RW = NW > 0 ? NW : 1;
-    P rthr[RW];
-    int rw[RW];
-    if constexpr (NW > 0) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            // widths beyond the row's set get a bound no sum reaches (their prefix reads stay
-            // inside the prefix array; the values there are not this row's and are never used)
-            rthr[w] = w < nwk ? sthr[w] : BoundNever<P>::value();
-            rw[w] = a.w[w];
-        }
-    }
-    // every width fits every sample of the tile: no end-of-row tests
-    const bool interior = t0 + kSnrTile + wmax - 1 <= n;
-    uint32_t flags = 0;
-    if (NW > 0 && interior && sg > 0.0) {  // straight-line bound tests; the exact quotient is rare
-#pragma unroll
-        for (int j = 0; j < kSlabs; ++j) {
-            const int i = tid + kThreads * j;
-            const P p0 = pre[i];
-            bool maybe = false;
-#pragma unroll
-            for (int w = 0; w < RW; ++w) maybe |= (P)(pre[i + rw[w]] - p0) >= rthr[w];
-            if (maybe) {
-                double best;
-                int bi;
-                exact(i, t0 + i, best, bi);
-                if (bi >= 0 && best >= a.threshold) flags |= 1u << j;
-            }
-        }
-    } else {
+    // the cells that do take the exact quotient.  mk[j]: the wave's lanes whose cell of slab j does.
+    uint64_t mk[kSlabs];
+    P p0[kSlabs];
+    const int last = tile - 1 < avail - 1 ? tile - 1 : avail - 1;  // last cell of the tile
+    const int slabs = last / kThreads + 1;
 #pragma unroll
     for (int j = 0; j < kSlabs; ++j) {
-        const int i = tid + kThreads * j;
-        const int64_t t = t0 + i;
-        if (t >= n || !(sg > 0.0)) continue;
-        const P p0 = pre[i];
-        bool maybe = false;
-        if (NW > 0 && interior) {
+        mk[j] = 0;
+        p0[j] = j < slabs ? pre[pre_at<P>(tid + kThreads * j)] : (P)0;
+    }
+    if (tile - 1 + wmax <= avail) {  // uniform: every width fits every cell
+        for (int w = 0; w < nwk; ++w) {
+            const P thr = sthr[w];
+            const P *p = pre + pre_at<P>(tid + sw[w]);
+            P s[kSlabs];
+            // entry i + W + 256 j: 256 entries on, 32 gaps more in a float tile
 #pragma unroll
-            for (int w = 0; w < RW; ++w) maybe |= (P)(pre[i + rw[w]] - p0) >= rthr[w];
-        } else {
-            for (int w = 0; w < nwk; ++w) {
-                if (t + a.w[w] > n) break;
-                maybe |= (P)(pre[i + a.w[w]] - p0) >= sthr[w];
+            for (int j = 0; j < kSlabs; ++j) s[j] = p[pre_at<P>(kThreads * j)];
+#pragma unroll
+            for (int j = 0; j < kSlabs; ++j) mk[j] |= __ballot((P)(s[j] - p0[j]) >= thr);
+        }
+        mk[kSlabs - 1] &= __ballot(tid + kThreads * (kSlabs - 1) < tile);  // the last slab may be partial
+    } else {
+        for (int w = 0; w < nwk; ++w) {
+            const int W = __builtin_amdgcn_readfirstlane(sw[w]);
+            const int lim = avail - W < last ? avail - W : last;  // last cell of the tile that the width fits
+            const P thr = sthr[w];
+            const P *p = pre + pre_at<P>(tid + W);
+#pragma unroll
+            for (int j = 0; j < kSlabs; ++j) {
+                if (kThreads * j > lim) break;  // uniform
+                uint64_t hit = __ballot((P)(p[pre_at<P>(kThreads * j)] - p0[j]) >= thr);
+                if (kThreads * j + kThreads - 1 > lim) hit &= __ballot(tid + kThreads * j <= lim);  // uniform
+                mk[j] |= hit;
             }
         }
-        if (!maybe) continue;
-        double best;
-        int bi;
-        exact(i, t, best, bi);
-        if (bi >= 0 && best >= a.threshold) flags |= 1u << j;
     }
+    uint64_t any = 0;
+#pragma unroll
+    for (int j = 0; j < kSlabs; ++j) any |= mk[j];
+    if (!__syncthreads_or(any != 0)) return;  // most tiles hold no such cell
+    uint32_t flags = 0;
+    if (any) {  // uniform over the wave
+        uint32_t maybe = 0;
+#pragma unroll
+        for (int j = 0; j < kSlabs; ++j) maybe |= (uint32_t)((mk[j] >> lane) & 1u) << j;
+        while (maybe) {
+            const int j = __builtin_ctz(maybe);
+            maybe &= maybe - 1u;
+            double best;
+            int bi;
+            exact(tid + kThreads * j, best, bi);
+            if (bi >= 0 && best >= a.threshold) flags |= 1u << j;
+        }
     }
     // ordered output: the block's cells in increasing t (slab by slab, thread by thread)
-    uint64_t masks[kSlabs];
 #pragma unroll
     for (int j = 0; j < kSlabs; ++j) {
-        masks[j] = __ballot((flags >> j) & 1u);
-        if (lane == 0) slab_off[j][wv] = __popcll(masks[j]);
+        mk[j] = __ballot((flags >> j) & 1u);
+        if (lane == 0) slab_off[j][wv] = __popcll(mk[j]);
     }
-    __syncthreads();
+    if (!__syncthreads_or((int)flags)) return;
     if (tid == 0) {
         int tot = 0;
         for (int j = 0; j < kSlabs; ++j)
@@ -680,20 +804,20 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
                 slab_off[j][w] = tot;
                 tot += c;
             }
-        base_s = tot ? atomicAdd(a.counter, (unsigned int)tot) : 0u;
+        base_s = atomicAdd(a.counter, (unsigned int)tot);
     }
     __syncthreads();
     const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
 #pragma unroll
     for (int j = 0; j < kSlabs; ++j) {
         if (!((flags >> j) & 1u)) continue;
-        const int64_t pos = (int64_t)base_s + slab_off[j][wv] + __popcll(masks[j] & below);
+        const int64_t pos = (int64_t)base_s + slab_off[j][wv] + __popcll(mk[j] & below);
         if (pos < a.max_pixels) {
             // the flagged cells are few: their exact maximum is taken again rather than kept
             const int i = tid + kThreads * j;
             double best;
             int bi;
-            exact(i, t0 + i, best, bi);
+            exact(i, best, bi);
             Pixel px;
             px.k = k;
             px.t = (int32_t)(t0 + i);
@@ -804,7 +928,7 @@ __global__ __launch_bounds__(kThreads) void k_rowmad(const T *plane, int64_t pit
 __global__ void k_zero_counter(unsigned int *c) { *c = 0u; }
 
 template <typename T, bool BATCH>
-int launch_snr_grid(dim3 grid, const T *p, int64_t pitch, int64_t n, double *stats, const SnrArgs &a, hipStream_t st);
+int launch_snr(int rows, const T *p, int64_t pitch, int64_t n, double *stats, const SnrArgs &a, hipStream_t st);
 
 template <typename T>
 int launch_typed(const void *plane, int64_t pitch, int ndm, int64_t n, double sigma_min, int sigma_mad,
@@ -816,9 +940,9 @@ int launch_typed(const void *plane, int64_t pitch, int ndm, int64_t n, double si
                        stats, (const DetBeam *)nullptr, 0, 0);
     if (sigma_mad)  // sigma from the median absolute deviation instead (the mean stays)
         hipLaunchKernelGGL((k_rowmad<T>), dim3((uint32_t)ndm), dim3(kThreads), 0, st, p, pitch, n, sigma_min, stats);
-    constexpr int kSnrTile = snr_tile<T>();
-    dim3 grid((uint32_t)((n + kSnrTile - 1) / kSnrTile), (uint32_t)ndm);
-    return launch_snr_grid<T, false>(grid, p, pitch, n, stats, a, st);
+    SnrArgs b = a;
+    b.rows16 = ((uintptr_t)p & 15u) == 0 && pitch * (int64_t)sizeof(T) % 16 == 0;
+    return launch_snr<T, false>(ndm, p, pitch, n, stats, b, st);
 }
 
 // Batched: statistics and S/N of batch rows a.row0 .. a.row0 + nrows - 1; the grid spans the
@@ -828,29 +952,44 @@ int launch_typed_batch(int nrows, int64_t n_max, double sigma_min, double *stats
 {
     hipLaunchKernelGGL((k_rowstats<T, true>), dim3((uint32_t)nrows), dim3(kThreads), 0, st, (const T *)nullptr,
                        (int64_t)0, (int64_t)0, sigma_min, stats, a.beams, a.nbeams, a.row0);
-    constexpr int kSnrTile = snr_tile<T>();
-    dim3 grid((uint32_t)((n_max + kSnrTile - 1) / kSnrTile), (uint32_t)nrows);
-    return launch_snr_grid<T, true>(grid, (const T *)nullptr, 0, 0, stats, a, st);
+    return launch_snr<T, true>(nrows, (const T *)nullptr, 0, n_max, stats, a, st);
 }
 
+// n: samples per row (batched: of the longest plane)
 template <typename T, bool BATCH>
-int launch_snr_grid(dim3 grid, const T *p, int64_t pitch, int64_t n, double *stats, const SnrArgs &a, hipStream_t st)
+int launch_snr(int rows, const T *p, int64_t pitch, int64_t n, double *stats, const SnrArgs &a0, hipStream_t st)
 {
-    constexpr int kSnrTile = snr_tile<T>();
-    // the prefix array holds the tile plus the widest boxcar of the list (every row's set is a
-    // leading part of the list); integer tiles are first staged in its storage, at most
-    // kThreads * kMaxPer samples of sizeof(T) <= 2 bytes each
-    constexpr int64_t kStageBytes = IsInt<T>::value ? (int64_t)kThreads * ((kSnrTile + kMaxWidth + kThreads - 1) / kThreads) * 2 : 0;
-    const int64_t entries = std::max<int64_t>(kSnrTile + a.w[a.nw - 1] + 1,
-                                              (kStageBytes + (int64_t)sizeof(typename PrefixType<T>::type) - 1) /
-                                                  (int64_t)sizeof(typename PrefixType<T>::type));
-    const size_t lds = (size_t)entries * sizeof(typename PrefixType<T>::type);
-    switch (a.nw) {
-#define SND_NW(N) case N: hipLaunchKernelGGL((k_snr<T, N, BATCH>), grid, dim3(kThreads), lds, st, p, pitch, n, stats, a); break;
-    SND_NW(1) SND_NW(2) SND_NW(3) SND_NW(4) SND_NW(5) SND_NW(6) SND_NW(7) SND_NW(8)
-#undef SND_NW
-    default: hipLaunchKernelGGL((k_snr<T, 0, BATCH>), grid, dim3(kThreads), lds, st, p, pitch, n, stats, a); break;
+    using P = typename PrefixType<T>::type;
+    SnrArgs a = a0;
+    const int wmax = a.w[a.nw - 1];  // every row's set is a leading part of the list
+    const bool wide = !IsInt<T>::value && wmax > kFloatNarrow;
+    a.tile = snr_tile<T>(wmax);
+    a.wmax = wmax;
+    a.nfine = 0;
+    a.odd = 0u;
+    for (int w = 0; w < a.nw; ++w) {
+        a.nfine += a.w[w] <= kPairExact;
+        a.odd |= (uint32_t)(a.w[w] & 1) << w;
     }
+    const dim3 grid((uint32_t)((n + a.tile - 1) / a.tile), (uint32_t)rows);
+    if constexpr (std::is_same<T, uint8_t>::value) {
+        if (!a.snr && a.rows16) {
+            hipLaunchKernelGGL((k_snr_pairs<BATCH>), grid, dim3(kThreads), (size_t)pairs_lds_bytes(wmax), st, p, pitch,
+                               n, stats, a);
+            return (int)hipGetLastError();
+        }
+    }
+    // the prefix array holds the tile's slabs (which are read whole) plus the widest boxcar; integer tiles are first staged in its storage (at most kThreads * per
+    // samples of sizeof(T) <= 2 bytes each)
+    int64_t bytes = ((int64_t)snr_slabs<T>() * kThreads + wmax + 1) * (int64_t)sizeof(P);
+    if (IsInt<T>::value) bytes = std::max<int64_t>(bytes, (int64_t)kThreads * snr_per<T>(false) * 2);
+    else bytes += bytes / 8 + (int64_t)sizeof(P);
+    if (wide)
+        hipLaunchKernelGGL((k_snr<T, snr_per<T>(true), BATCH>), grid, dim3(kThreads), (size_t)bytes, st, p, pitch, n,
+                           stats, a);
+    else
+        hipLaunchKernelGGL((k_snr<T, snr_per<T>(false), BATCH>), grid, dim3(kThreads), (size_t)bytes, st, p, pitch, n,
+                           stats, a);
     return (int)hipGetLastError();
 }
 

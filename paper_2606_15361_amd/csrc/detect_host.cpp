@@ -654,8 +654,11 @@ snd_status snd_detect_batch_launch(int32_t n, const snd_plan *plans, const void 
         const int dt = plans[L.order[j0]]->impl.out_dtype;
         size_t j1 = j0;
         int64_t nrows = 0, n_max = 0;
+        a.rows16 = 1;
         while (j1 < L.order.size() && plans[L.order[j1]]->impl.out_dtype == dt) {
             nrows += plans[L.order[j1]]->impl.ndm;
+            const snd::DetBeam &b = table[j1];
+            if (((uintptr_t)b.plane & 15u) || b.pitch * snd::dtype_size(dt) % 16) a.rows16 = 0;
             n_max = std::max<int64_t>(n_max, plans[L.order[j1]]->impl.n_out);
             ++j1;
         }

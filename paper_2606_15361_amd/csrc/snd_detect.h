@@ -39,6 +39,11 @@ struct SnrArgs {
     int32_t nw;
     const int32_t *row_nw;  // per-row number of leading widths used (null: nw for every row)
     double threshold;
+    // set by the launcher: samples of one row per workgroup, the list's widest width, its widths up to
+    // the paired kernel's exact range, one bit per odd width
+    int32_t tile, wmax, nfine;
+    uint32_t odd;
+    int32_t rows16;  // every row starts on a 16-byte boundary (batched: set by the caller)
     // plane output (when snr != nullptr)
     float *snr;
     int64_t snr_pitch;

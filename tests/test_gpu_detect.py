@@ -113,6 +113,46 @@ def test_integer_plane_multi_tile_bit_exact(snd, orc, mode, hi, widths, theta, s
     assert det.npixels == int((o_snr >= theta).sum()) > 0
 
 
+@pytest.mark.parametrize("dtype", ["u8", "binary", "u16", "float"])
+@pytest.mark.parametrize("n", [7, 300, 2047, 4095, 4096, 4097, 8192 + 63])
+@pytest.mark.parametrize("widths", [[1, 2, 4, 8, 16, 32, 64], [1 << i for i in range(11)], [2, 3, 9, 255, 256, 257, 1024],
+                                    [7]])
+def test_cells_at_tile_and_row_ends(snd, orc, dtype, n, widths):
+    """Cells of rows that end inside, at and just past an S/N tile, and that are shorter than the widest
+    boxcar, on aligned rows whose padding holds large values, for short lists, the DM-scaled set's widths
+    and odd widths: the oracle's cells (their count and every candidate at n_min 1)."""
+    rng = synth.make_rng(n + len(widths))
+    ndm, pitch = 6, (n + 63) // 64 * 64
+    hi = {"u8": 255, "binary": 1, "u16": 1000, "float": 0}[dtype]
+    if dtype == "float":
+        plane = rng.standard_normal((ndm, n)).astype(np.float32)
+    else:
+        plane = (rng.random((ndm, n)) < 0.1).astype(np.int64) * rng.integers(1, hi + 1, (ndm, n))
+    for k, (a, w) in enumerate(((0, 3), (n - 4, 4), (n // 2, 40), (max(0, n - 300), 300), (0, 1))):
+        plane[k, a:a + w] = 6.0 if dtype == "float" else hi
+    plane[5] = 2.0 if dtype == "float" else 1  # constant row
+    np_dt = {"u8": np.uint8, "binary": np.uint8, "u16": np.uint16, "float": np.float32}[dtype]
+    full = np.full((ndm, pitch), 1e6 if dtype == "float" else hi).astype(np_dt)
+    full[:, :n] = plane.astype(np_dt)
+    mode, cap = ("float", 255) if dtype == "float" else ("binary", 255) if dtype == "binary" else ("graded", hi)
+    p = snd.Plan(synth.channel_freqs(4), np.zeros(ndm), 0.138e-3, n, mode=mode, branching=2, cap=cap)
+    dev = torch.from_numpy(full).cuda()[:, :n]
+    _say(f"tile ends dtype={dtype} n={n} widths={widths}")
+    for theta in (2.5, 6.0):
+        det = snd.Detector(p, widths, threshold=theta, closing_radius=0, n_min=1)
+        o_snr, o_widx, _, _ = orc.matched_filter(full[:, :n].astype(np.float64), widths,
+                                                 integer_plane=dtype != "float")
+        got = det.run(dev)
+        want = orc.candidates(o_snr, o_widx, theta, radius=0, n_min=1)
+        assert det.npixels == int((o_snr >= theta).sum())
+        if dtype == "float":
+            assert [(g["k"], g["t"], g["widx"], g["npix"]) for g in got] == \
+                [(w["k"], w["t"], w["widx"], w["npix"]) for w in want]
+            assert all(abs(g["snr"] - w["snr"]) <= 1e-9 * abs(w["snr"]) for g, w in zip(got, want))
+        else:
+            _cands_equal(got, want)
+
+
 def test_float_plane_within_tolerance(snd, orc):
     rng = synth.make_rng(8)
     ndm, n = 24, 5000
