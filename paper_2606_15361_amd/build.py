@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsnd.so")
 BUILD = os.path.join(HERE, "_build")
 
-HIP_SOURCES = ["kernels.hip", "kernels_lds.hip", "kernels_fast_binary.hip", "kernels_fast_graded.hip",
+HIP_SOURCES = ["kernels.hip", "frontend.hip", "kernels_lds.hip", "kernels_fast_binary.hip", "kernels_fast_graded.hip",
                "kernels_fast_float.hip", "kernels_bits.hip", "detect.hip", "label.hip",
                "detect_noalloc.hip", "group_lin.hip", "group_pack.hip"]
 CXX_SOURCES = ["plan.cpp", "capi.cpp", "detect_host.cpp", "stream_host.cpp", "batch_host.cpp", "tune_host.cpp",

@@ -1,0 +1,617 @@
+// On-device front end for gfx950: delta encoders, storage cast, time scrunch, clipped channel
+// statistics, normalisation, channel flagging and zero-DM subtraction (Methods, "Input encoding",
+// "Multi-rate extension"; Results, "False-positive rate").
+//
+// Every kernel here streams a filterbank once or twice and is bound by memory, so each one keeps
+// several independent 16-byte (or whole-line) loads per lane in flight and writes whole dwords; rows
+// need no alignment beyond their element's (unaligned 16-byte accesses are native).
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "snd_internal.h"
+#include "stage_common.h"
+
+namespace snd {
+namespace {
+
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32u __attribute__((aligned(1)));
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
+
+__device__ inline f32x4u load4(global_ptr<const float> p) { return *reinterpret_cast<global_ptr<const f32x4u>>(p); }
+
+constexpr int kRow = 4096;  // samples of a row per workgroup: 256 threads, four 16-byte loads each
+
+// A 256-thread workgroup's kRow samples of a row from t0 (n: the row's samples): f(t, x) for every
+// whole group of four, one(t, x) for the samples of the last, partial one.
+template <typename F, typename G>
+__device__ inline void row_quads(const float *row, int64_t t0, int64_t n, F &&f, G &&one)
+{
+    const auto src = as_global(row);
+    const int64_t t = t0 + 4 * (int)threadIdx.x;
+    if (t0 + kRow <= n) {  // uniform
+        f32x4u v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = load4(src + t + 1024 * u);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) f(t + 1024 * u, v[u]);
+        return;
+    }
+    for (int u = 0; u < 4; ++u) {
+        const int64_t tu = t + 1024 * u;
+        if (tu + 4 <= n) f(tu, load4(src + tu));
+        else
+            for (int64_t i = tu; i < n; ++i) one(i, src[i]);
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// Delta encoder (Methods, "Input encoding"): level = number of thresholds z exceeds.
+// ---------------------------------------------------------------------------------------
+struct Thresholds { float v[8]; int n; };
+
+__device__ inline uint32_t level(const Thresholds &th, float x)
+{
+    uint32_t l = 0;
+    for (int j = 0; j < th.n; ++j) l += x > th.v[j];
+    return l;
+}
+
+// Channel-major input: four samples per dword store (one byte per lane and store took 0.30 ms for
+// 1024 x 131,072 samples, this 0.13).
+__global__ __launch_bounds__(256) void k_encode_cm(const float *z, int64_t zp, int64_t nsamp, Thresholds th,
+                                                   uint8_t *out, int64_t op)
+{
+    const int c = blockIdx.y;
+    const auto dst = as_global(out + (int64_t)c * op);
+    row_quads(
+        z + (int64_t)c * zp, (int64_t)blockIdx.x * kRow, nsamp,
+        [&](int64_t t, f32x4u x) {
+            const uint32_t w = level(th, x.x) | level(th, x.y) << 8 | level(th, x.z) << 16 | level(th, x.w) << 24;
+            *reinterpret_cast<global_ptr<u32u>>(dst + t) = w;
+        },
+        [&](int64_t t, float x) { dst[t] = (uint8_t)level(th, x); });
+}
+
+// Time-major input, transposed through LDS: a tile of 64 channels x 256 samples.  A lane reads one
+// channel of 64 consecutive samples (a wave reads whole 256-byte lines), packs four levels per dword
+// and writes them to its channel's LDS row; the rows leave as 256-byte stores (64 x 64 tiles of bytes
+// took 0.26 ms for 1024 x 131,072 samples, this 0.17).
+constexpr int kTmT = 256;            // samples per tile
+constexpr int kTmPitch = kTmT / 4 + 1;  // dwords per LDS row: odd, so that a column of lanes spreads over the banks
+
+__global__ __launch_bounds__(256) void k_encode_tm(const float *z, int64_t zp, int nchan, int64_t nsamp, Thresholds th,
+                                                   uint8_t *out, int64_t op)
+{
+    __shared__ uint32_t tile[64 * kTmPitch];
+    const int64_t tb = (int64_t)blockIdx.x * kTmT;
+    const int cb = blockIdx.y * 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = cb + lane;
+    const auto src = as_global(z) + c;
+    const bool inside = tb + kTmT <= nsamp && cb + 64 <= nchan;  // uniform
+#pragma unroll 1
+    for (int g = 0; g < 4; ++g) {  // 16 samples of the wave's 64 at a time
+        const int64_t t = tb + 64 * wave + 16 * g;
+        float x[16];
+        if (inside) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] = src[(t + i) * zp];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] = t + i < nsamp && c < nchan ? src[(t + i) * zp] : 0.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            tile[lane * kTmPitch + 16 * wave + 4 * g + q] = level(th, x[4 * q]) | level(th, x[4 * q + 1]) << 8 |
+                                                            level(th, x[4 * q + 2]) << 16 | level(th, x[4 * q + 3]) << 24;
+    }
+    __syncthreads();
+    const int64_t t = tb + 4 * lane;
+#pragma unroll 4
+    for (int i = 0; i < 16; ++i) {
+        const int r = 16 * wave + i;  // channel within the tile
+        if (cb + r >= nchan) break;
+        const uint32_t w = tile[r * kTmPitch + lane];
+        const auto dst = as_global(out + (int64_t)(cb + r) * op + t);
+        if (t + 4 <= nsamp) *reinterpret_cast<global_ptr<u32u>>(dst) = w;
+        else
+            for (int b = 0; b < 4 && t + b < nsamp; ++b) dst[b] = (uint8_t)(w >> (8 * b));
+    }
+}
+
+// Bits: a wave tests 1024 consecutive samples of a channel, 64 per ballot (sixteen loads in flight),
+// and writes their 32 words as one 128-byte store (one ballot and an 8-byte store per wave took
+// 0.27 ms for 1024 x 131,072 samples, this 0.10).
+__global__ __launch_bounds__(256) void k_encode_bits_cm(const float *z, int64_t zp, int64_t nsamp, float th,
+                                                        uint32_t *out, int64_t ow)
+{
+    const int c = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int64_t tb = (int64_t)blockIdx.x * kRow + (threadIdx.x >> 6) * 1024;  // first sample of the wave
+    const auto src = as_global(z + (int64_t)c * zp) + tb + lane;
+    float x[16];
+    if (tb + 1024 <= nsamp) {  // uniform per wave
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = src[64 * u];
+    } else {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = tb + lane + 64 * u < nsamp ? src[64 * u] : -__builtin_inff();
+    }
+    uint32_t w = 0;  // lane l: word l of the wave
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const uint64_t mask = __ballot(x[u] > th && tb + lane + 64 * u < nsamp);
+        w = lane == 2 * u ? (uint32_t)mask : lane == 2 * u + 1 ? (uint32_t)(mask >> 32) : w;
+    }
+    const int64_t wi = (tb >> 5) + lane;
+    if (lane < 32 && 32 * wi < nsamp) as_global(out + (int64_t)c * ow)[wi] = w;
+}
+
+// Bits from time-major input: a lane builds the words of one channel from the samples it reads (a
+// wave reads whole 256-byte lines), 32 samples each; the words of 64 channels x 1024 samples leave
+// through LDS as 128-byte runs of each row.
+__global__ __launch_bounds__(256) void k_encode_bits_tm(const float *z, int64_t zp, int nchan, int64_t nsamp,
+                                                        float th, uint32_t *out, int64_t ow)
+{
+    __shared__ uint32_t tile[64 * 33];
+    const int64_t tb = (int64_t)blockIdx.x * 1024;
+    const int cb = blockIdx.y * 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = cb + lane;
+    const auto src = as_global(z) + c;
+#pragma unroll 1
+    for (int k = 0; k < 8; ++k) {  // the wave's words 8 wave + k
+        const int64_t t = tb + 256 * wave + 32 * k;
+        uint32_t w = 0;
+        if (t + 32 <= nsamp && cb + 64 <= nchan) {  // uniform
+            float x[32];
+#pragma unroll
+            for (int i = 0; i < 32; ++i) x[i] = src[(t + i) * zp];
+#pragma unroll
+            for (int i = 0; i < 32; ++i) w |= (uint32_t)(x[i] > th) << i;
+        } else if (c < nchan) {
+            for (int i = 0; i < 32 && t + i < nsamp; ++i) w |= (uint32_t)(src[(t + i) * zp] > th) << i;
+        }
+        tile[lane * 33 + 8 * wave + k] = w;
+    }
+    __syncthreads();
+    const int wl = lane & 31;
+    const int64_t wi = (tb >> 5) + wl;
+    for (int r = 2 * wave + (lane >> 5); r < 64; r += 8)
+        if (cb + r < nchan && 32 * wi < nsamp) as_global(out + (int64_t)(cb + r) * ow)[wi] = tile[r * 33 + wl];
+}
+
+// Time scrunch: output t is the sum of s consecutive samples of one channel in order (FP32, no
+// contraction), scaled by r.  S > 0: s known at compile time; a thread's outputs are 256 apart and
+// each is S / 4 16-byte loads (S = 2: two neighbouring outputs per load).  One sample per load took
+// 0.20 ms for 1024 x 131,072 samples at S = 2, 4 and 8, this 0.13, 0.12 and 0.11.
+template <int S>
+__global__ __launch_bounds__(256) void k_scrunch(const float *z, int64_t zp, int64_t nout, int s_, float r, float *out,
+                                                 int64_t op)
+{
+    constexpr int U = S == 0 ? 1 : S <= 4 ? 8 : 32 / S;  // outputs per thread
+    const int c = blockIdx.y;
+    const int64_t t0 = (int64_t)blockIdx.x * 256 * U;
+    const auto src = as_global(z + (int64_t)c * zp);
+    const auto dst = as_global(out + (int64_t)c * op);
+    auto one = [&](int64_t t) {
+        const int s = S ? S : s_;
+        const auto p = src + t * s;
+        float acc = p[0];
+        for (int j = 1; j < s; ++j) acc = acc + p[j];
+        dst[t] = acc * r;
+    };
+    if constexpr (S >= 2) {
+        if (t0 + 256 * U <= nout) {  // uniform
+            constexpr int Q = S == 2 ? 1 : S / 4;     // loads per step
+            constexpr int N = S == 2 ? U / 2 : U;     // steps
+            f32x4u v[N][Q];
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    v[u][q] = load4(src + (S == 2 ? 2 * (t0 + 2 * (int)threadIdx.x + 512 * u)
+                                                  : S * (t0 + (int)threadIdx.x + 256 * u) + 4 * q));
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                if constexpr (S == 2) {
+                    const int64_t t = t0 + 2 * (int)threadIdx.x + 512 * u;
+                    dst[t] = (v[u][0].x + v[u][0].y) * r;
+                    dst[t + 1] = (v[u][0].z + v[u][0].w) * r;
+                } else {
+                    float acc = v[u][0].x;
+#pragma unroll
+                    for (int j = 1; j < S; ++j) acc = acc + v[u][j / 4][j % 4];
+                    dst[t0 + (int)threadIdx.x + 256 * u] = acc * r;
+                }
+            }
+            return;
+        }
+    }
+    for (int u = 0; u < U; ++u) {
+        const int64_t t = t0 + (int)threadIdx.x + 256 * u;
+        if (t < nout) one(t);
+    }
+}
+
+// Sum of one FP64 pair per thread over a workgroup of T threads, returned to every thread.
+template <int T>
+__device__ inline void block_sum2(double &a, double &b, double (*sh)[T / 64])
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o, 64);
+        b += __shfl_xor(b, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][threadIdx.x >> 6] = a;
+        sh[1][threadIdx.x >> 6] = b;
+    }
+    __syncthreads();
+    a = sh[0][0];
+    b = sh[1][0];
+#pragma unroll
+    for (int w = 1; w < T / 64; ++w) {
+        a += sh[0][w];
+        b += sh[1][w];
+    }
+    __syncthreads();
+}
+
+// Sigma-clip statistics of one channel per workgroup: a first FP64 pass about the channel's
+// first sample gives mu0 and sigma0, a second pass the same statistics of the clipped values
+// (about the clip range's centre, mu0).  Two workgroups of 16 waves fill a CU, four 16-byte loads
+// per lane in flight (256 threads with one 4-byte load each took 0.53 ms for 1024 x 131,072,
+// this 0.18).
+constexpr int kStatThreads = 1024;
+template <typename F>
+__device__ inline void stat_fold(global_ptr<const float> row, int64_t n, F &&f)
+{
+    const int tid = threadIdx.x;
+    const int64_t nv = n / 4;
+    int64_t i = tid;
+    for (; i + 3 * kStatThreads < nv; i += 4 * kStatThreads) {
+        f32x4u v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = load4(row + 4 * (i + u * kStatThreads));
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f(v[u][j]);
+    }
+    for (; i < nv; i += kStatThreads) {
+        const f32x4u v = load4(row + 4 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f(v[j]);
+    }
+    if (4 * nv + tid < n) f(row[4 * nv + tid]);
+}
+
+__global__ __launch_bounds__(kStatThreads) void k_chanstats(const float *p, int64_t pp, int64_t n, double clip,
+                                                            double *stats)
+{
+    __shared__ double sh[2][kStatThreads / 64];
+    const int c = blockIdx.x;
+    const auto row = as_global(p + (int64_t)c * pp);
+    const double shift = (double)row[0];
+    double a = 0.0, b = 0.0;
+    stat_fold(row, n, [&](float x) {
+        const double d = (double)x - shift;
+        a += d;
+        b += d * d;
+    });
+    block_sum2<kStatThreads>(a, b, sh);
+    const double dn = (double)n;
+    const double m1 = a / dn;
+    const double mu0 = shift + m1;
+    const double v0 = b / dn - m1 * m1;
+    const double s0 = v0 > 0.0 ? sqrt(v0) : 0.0;
+    const double lo = mu0 - clip * s0, hi = mu0 + clip * s0;
+    a = 0.0;
+    b = 0.0;
+    stat_fold(row, n, [&](float x) {
+        double v = (double)x;
+        v = v < lo ? lo : (v > hi ? hi : v);
+        const double d = v - mu0;
+        a += d;
+        b += d * d;
+    });
+    block_sum2<kStatThreads>(a, b, sh);
+    if (threadIdx.x == 0) {
+        const double m = a / dn;
+        const double v = b / dn - m * m;
+        stats[2 * c] = mu0 + m;
+        stats[2 * c + 1] = v > 0.0 ? sqrt(v) : 0.0;
+    }
+}
+
+// (p - mu) / sigma as one FP64 quotient, rounded once (1024 x 131,072 samples: 0.17 ms, 6.5 TB/s; one
+// sample per thread took 0.30).
+__global__ __launch_bounds__(256) void k_normalize(const float *p, int64_t pp, int64_t n, const double *stats,
+                                                   float *z, int64_t zp)
+{
+    const int c = blockIdx.y;
+    const double mu = stats[2 * c], sg = stats[2 * c + 1];
+    const auto dst = as_global(z + (int64_t)c * zp);
+    auto norm = [&](float x) { return (float)(((double)x - mu) / sg); };
+    row_quads(
+        p + (int64_t)c * pp, (int64_t)blockIdx.x * kRow, n,
+        [&](int64_t t, f32x4u x) {
+            *reinterpret_cast<global_ptr<f32x4u>>(dst + t) = f32x4u{norm(x.x), norm(x.y), norm(x.z), norm(x.w)};
+        },
+        [&](int64_t t, float x) { dst[t] = norm(x); });
+}
+
+// Zero-DM subtraction: one lane per sample t sums the channels in order in FP64 (a wave reads
+// whole lines of a channel row, kZdLoads rows in flight; one row at a time took 0.71 ms for
+// 1024 x 131,072, this 0.10); when the zero-DM S/N |sum| / sqrt(nchan) exceeds gamma, the channel mean
+// sum / nchan is subtracted from every channel, each result rounded once to FP32.  A few such
+// samples of a wave are corrected one by one, a lane per channel; many of them as the sums were read.
+constexpr int kZdLoads = 32;
+constexpr int kZdFew = 8;
+__global__ __launch_bounds__(64) void k_zero_dm(float *z, int64_t zp, int nchan, int64_t n, double gamma,
+                                                int32_t *count)
+{
+    const int lane = threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * 64 + lane;
+    const bool on = t < n;
+    const auto col = as_global(z) + (on ? t : n - 1);
+    double s = 0.0;
+    int c = 0;
+    for (; c + kZdLoads <= nchan; c += kZdLoads) {
+        float v[kZdLoads];
+#pragma unroll
+        for (int u = 0; u < kZdLoads; ++u) v[u] = col[(int64_t)(c + u) * zp];
+#pragma unroll
+        for (int u = 0; u < kZdLoads; ++u) s += (double)v[u];
+    }
+    for (; c < nchan; ++c) s += (double)col[(int64_t)c * zp];
+    const bool hit = on && __builtin_fabs(s) / __builtin_sqrt((double)nchan) > gamma;
+    uint64_t hits = __ballot(hit);
+    if (!hits) return;
+    if (count && lane == 0) atomicAdd(count, (int)__popcll(hits));
+    const double mean = s / (double)nchan;
+    if (__popcll(hits) <= kZdFew) {  // uniform
+        while (hits) {
+            const int h = __builtin_ctzll(hits);
+            hits &= hits - 1;
+            const double m = __shfl(mean, h, 64);
+            const auto p = as_global(z) + (int64_t)blockIdx.x * 64 + h;
+            for (int c0 = 0; c0 < nchan; c0 += 256) {
+                float v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    v[u] = c0 + lane + 64 * u < nchan ? p[(int64_t)(c0 + lane + 64 * u) * zp] : 0.0f;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (c0 + lane + 64 * u < nchan) p[(int64_t)(c0 + lane + 64 * u) * zp] = (float)((double)v[u] - m);
+            }
+        }
+        return;
+    }
+    if (!hit) return;
+    c = 0;
+    for (; c + 8 <= nchan; c += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = col[(int64_t)(c + u) * zp];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) col[(int64_t)(c + u) * zp] = (float)((double)v[u] - mean);
+    }
+    for (; c < nchan; ++c) col[(int64_t)c * zp] = (float)((double)col[(int64_t)c * zp] - mean);
+}
+
+// Windowed channel flagging by median absolute deviation, in two kernels.
+// k_chan_window_sigma: one workgroup per (channel, window of w samples): s = the population standard
+//   deviation over the window in FP64 (the mean, then the mean squared deviation).  Windows of up to
+//   kWinReg samples stay in registers between the two sums, so they are read once (two passes of one
+//   wave per window took 0.57 ms for 1024 x 131,072 in windows of 8192, this 0.19).  Writes sigma[window][channel].
+// k_flag_window: kFlagSlices workgroups per window, each finds m = the lower median of the window's
+//   s over the channels and MAD = the lower median of |s_c - m|, then takes its share of the channels:
+//   channel c is flagged when |s_c - m| > k * (kMad * MAD), kMad = 1 / Phi^-1(3/4), and its samples in
+//   the window are set to 0.  (One workgroup per window leaves most CUs idle while it zeroes: 0.17 ms, this 0.10.)
+constexpr double kFlagMadScale = 1.4826022185056018;
+constexpr int kWinQuads = 8;
+constexpr int kWinReg = 4 * 256 * kWinQuads;
+constexpr int kFlagSlices = 16;
+
+__global__ __launch_bounds__(256) void k_chan_window_sigma(const float *z, int64_t zp, int nchan, int64_t n,
+                                                           int64_t w, double *sigma)
+{
+    __shared__ double sh[2][4];
+    const int c = blockIdx.x, tid = threadIdx.x;
+    const int64_t b = blockIdx.y;
+    const int64_t t0 = b * w;
+    const int64_t len = n - t0 < w ? n - t0 : w;
+    const auto row = as_global(z + (int64_t)c * zp + t0);
+    double a = 0.0, q = 0.0, none = 0.0;
+    if (len <= kWinReg) {  // uniform
+        f32x4u v[kWinQuads];
+#pragma unroll
+        for (int u = 0; u < kWinQuads; ++u) {
+            const int t = 4 * (tid + 256 * u);
+            v[u] = f32x4u{0.0f, 0.0f, 0.0f, 0.0f};
+            if (t + 4 <= len) v[u] = load4(row + t);
+            else
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (t + j < len) v[u][j] = row[t + j];
+        }
+#pragma unroll
+        for (int u = 0; u < kWinQuads; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a += (double)v[u][j];
+        block_sum2<256>(a, none, sh);
+        const double mu = a / (double)len;
+#pragma unroll
+        for (int u = 0; u < kWinQuads; ++u) {
+            if (1024 * u >= len) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double d = (double)v[u][j] - mu;
+                if (4 * (tid + 256 * u) + j < len) q += d * d;
+            }
+        }
+    } else {
+        for (int64_t t = tid; t < len; t += 256) a += (double)row[t];
+        block_sum2<256>(a, none, sh);
+        const double mu = a / (double)len;
+        for (int64_t t = tid; t < len; t += 256) q += ((double)row[t] - mu) * ((double)row[t] - mu);
+    }
+    none = 0.0;
+    block_sum2<256>(q, none, sh);
+    if (tid == 0) sigma[b * nchan + c] = __builtin_sqrt(q / (double)len);
+}
+
+// The value of rank r (0-based, increasing) among the non-negative v[0..n) in LDS: the largest of the
+// values that at most r others lie below.  (Non-negative doubles order as their bits; NaNs never count.)
+__device__ inline double lds_rank_value(const double *v, int n, int r, unsigned long long *best)
+{
+    if (threadIdx.x == 0) *best = 0ull;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const double x = v[i];
+        int below = 0;
+#pragma unroll 8
+        for (int j = 0; j < n; ++j) below += v[j] < x;
+        if (below <= r && x == x) atomicMax(best, (unsigned long long)__double_as_longlong(x));
+    }
+    __syncthreads();
+    return __longlong_as_double((long long)*best);
+}
+
+__global__ __launch_bounds__(1024) void k_flag_window(float *z, int64_t zp, int nchan, int64_t n, int64_t w,
+                                                      double k, const double *sigma, uint8_t *flags, int64_t fp)
+{
+    extern __shared__ double sv[];  // [nchan]: the window's sigmas, then their deviations
+    __shared__ unsigned long long best;
+    const int64_t b = blockIdx.x;
+    const int64_t t0 = b * w;
+    const int64_t len = n - t0 < w ? n - t0 : w;
+    for (int c = threadIdx.x; c < nchan; c += blockDim.x) sv[c] = sigma[b * nchan + c];
+    const int r = (nchan - 1) / 2;
+    const double m = lds_rank_value(sv, nchan, r, &best);
+    __syncthreads();
+    for (int c = threadIdx.x; c < nchan; c += blockDim.x) sv[c] = __builtin_fabs(sv[c] - m);
+    const double thr = k * (kFlagMadScale * lds_rank_value(sv, nchan, r, &best));
+    const int c0 = (int)((int64_t)nchan * blockIdx.y / gridDim.y), c1 = (int)((int64_t)nchan * (blockIdx.y + 1) / gridDim.y);
+    if (flags)
+        for (int c = c0 + (int)threadIdx.x; c < c1; c += blockDim.x) flags[b * fp + c] = sv[c] > thr ? 1 : 0;
+    for (int c = c0; c < c1; ++c) {  // uniform: every thread sees the same flag
+        if (!(sv[c] > thr)) continue;
+        const auto row = as_global(z + (int64_t)c * zp + t0);
+        for (int64_t t = threadIdx.x; t < len; t += blockDim.x) row[t] = 0.0f;
+    }
+}
+
+// f32 rows to bf16 / f16, four samples per 8-byte store (1024 x 8192 samples: 17 -> 10 us).
+template <typename TO>
+__global__ __launch_bounds__(256) void k_cast(const float *src, int64_t sp, int64_t cols, TO *dst, int64_t dp)
+{
+    const int64_t r = blockIdx.y;
+    const auto out = as_global(dst + r * dp);
+    row_quads(
+        src + r * sp, (int64_t)blockIdx.x * kRow, cols,
+        [&](int64_t t, f32x4u x) {
+            *reinterpret_cast<global_ptr<u32x2u>>(out + t) =
+                u32x2u{store_bits<TO>(x.x) | store_bits<TO>(x.y) << 16, store_bits<TO>(x.z) | store_bits<TO>(x.w) << 16};
+        },
+        [&](int64_t t, float x) { Store<TO>::put(out + t, x); });
+}
+
+uint32_t blocks(int64_t n, int64_t per) { return (uint32_t)((n + per - 1) / per); }
+
+}  // namespace
+
+int launch_encode(const float *z, int64_t zp, int time_major, int nchan, int64_t nsamp, const float *thr, int nthr,
+                  uint8_t *out, int64_t op, void *stream)
+{
+    Thresholds th{};
+    th.n = nthr;
+    for (int i = 0; i < nthr; ++i) th.v[i] = thr[i];
+    hipStream_t st = (hipStream_t)stream;
+    if (time_major)
+        hipLaunchKernelGGL(k_encode_tm, dim3(blocks(nsamp, kTmT), blocks(nchan, 64)), dim3(256), 0, st, z, zp, nchan,
+                           nsamp, th, out, op);
+    else
+        hipLaunchKernelGGL(k_encode_cm, dim3(blocks(nsamp, kRow), (uint32_t)nchan), dim3(256), 0, st, z, zp, nsamp, th,
+                           out, op);
+    return (int)hipGetLastError();
+}
+
+int launch_encode_bits(const float *z, int64_t zp, int time_major, int nchan, int64_t nsamp, float thr, uint32_t *out,
+                       int64_t ow, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    if (time_major)
+        hipLaunchKernelGGL(k_encode_bits_tm, dim3(blocks(nsamp, 1024), blocks(nchan, 64)), dim3(256), 0, st, z, zp,
+                           nchan, nsamp, thr, out, ow);
+    else
+        hipLaunchKernelGGL(k_encode_bits_cm, dim3(blocks(nsamp, kRow), (uint32_t)nchan), dim3(256), 0, st, z, zp, nsamp,
+                           thr, out, ow);
+    return (int)hipGetLastError();
+}
+
+int launch_scrunch(const float *z, int64_t zp, int nchan, int64_t nout, int s, float r, float *out, int64_t op,
+                   void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+#define SND_SCRUNCH(S, U)                                                                                             \
+    hipLaunchKernelGGL(k_scrunch<S>, dim3(blocks(nout, 256 * U), (uint32_t)nchan), dim3(256), 0, st, z, zp, nout, s, \
+                       r, out, op)
+    switch (s) {  // the scrunch factors of the multi-rate bands
+    case 2: SND_SCRUNCH(2, 8); break;
+    case 4: SND_SCRUNCH(4, 8); break;
+    case 8: SND_SCRUNCH(8, 4); break;
+    case 16: SND_SCRUNCH(16, 2); break;
+    default: SND_SCRUNCH(0, 1); break;
+    }
+#undef SND_SCRUNCH
+    return (int)hipGetLastError();
+}
+
+int launch_chanstats(const float *p, int64_t pp, int nchan, int64_t n, double clip, double *stats, void *stream)
+{
+    hipLaunchKernelGGL(k_chanstats, dim3((uint32_t)nchan), dim3(kStatThreads), 0, (hipStream_t)stream, p, pp, n, clip,
+                       stats);
+    return (int)hipGetLastError();
+}
+
+int launch_normalize(const float *p, int64_t pp, int nchan, int64_t n, const double *stats, float *z, int64_t zp,
+                     void *stream)
+{
+    hipLaunchKernelGGL(k_normalize, dim3(blocks(n, kRow), (uint32_t)nchan), dim3(256), 0, (hipStream_t)stream, p, pp, n,
+                       stats, z, zp);
+    return (int)hipGetLastError();
+}
+
+int launch_zero_dm(float *z, int64_t zp, int nchan, int64_t n, double gamma, int32_t *count, void *stream)
+{
+    hipLaunchKernelGGL(k_zero_dm, dim3(blocks(n, 64)), dim3(64), 0, (hipStream_t)stream, z, zp, nchan, n, gamma, count);
+    return (int)hipGetLastError();
+}
+
+int launch_flag_channels(float *z, int64_t zp, int nchan, int64_t n, int64_t w, double k, double *sigma,
+                         uint8_t *flags, int64_t fp, void *stream)
+{
+    const uint32_t nwin = blocks(n, w);
+    hipLaunchKernelGGL(k_chan_window_sigma, dim3((uint32_t)nchan, nwin), dim3(256), 0, (hipStream_t)stream, z, zp, nchan,
+                       n, w, sigma);
+    hipLaunchKernelGGL(k_flag_window, dim3(nwin, (uint32_t)(nchan < kFlagSlices ? nchan : kFlagSlices)), dim3(1024),
+                       (size_t)nchan * sizeof(double), (hipStream_t)stream, z, zp, nchan, n, w, k, sigma, flags, fp);
+    return (int)hipGetLastError();
+}
+
+int launch_cast(const float *src, int64_t sp, int64_t rows, int64_t cols, void *dst, int64_t dp, int dst_dt, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    const dim3 grid(blocks(cols, kRow), (uint32_t)rows);
+    if (dst_dt == SND_DT_BF16) hipLaunchKernelGGL(k_cast<bf16_t>, grid, dim3(256), 0, st, src, sp, cols, (bf16_t *)dst, dp);
+    else if (dst_dt == SND_DT_F16) hipLaunchKernelGGL(k_cast<f16_t>, grid, dim3(256), 0, st, src, sp, cols, (f16_t *)dst, dp);
+    else return (int)hipErrorInvalidValue;
+    return (int)hipGetLastError();
+}
+
+}  // namespace snd

@@ -91,3 +91,44 @@ def test_flagging_and_zero_dm(snd, orc, nchan, n, window):
     want_z2, want_n = orc.zero_dm(want_z, 5.0)
     assert int(cnt.item()) == want_n and want_n >= 1  # at least the strong broadband spike
     assert np.array_equal(zt.cpu().numpy(), want_z2)
+
+
+@pytest.mark.parametrize("nchan,n", [(3, 1), (5, 67), (64, 255), (65, 1025), (70, 4096), (2, 4097), (130, 8195)])
+def test_row_ends_and_unaligned_rows(snd, orc, nchan, n):
+    """Encoders in both orders, casts, scrunch, normalisation and zero-DM at row lengths around a
+    workgroup's samples and channel counts around a 64-channel tile, on rows that start on any element
+    (a column offset into a wider block): the oracle's results, and no write past a row's end."""
+    rng = synth.make_rng(nchan * 10007 + n)
+    wide = rng.standard_normal((nchan, n + 5)).astype(np.float32)
+    wide[0, n // 2] = np.nan
+    block = torch.from_numpy(wide).cuda()
+    for off in (0, 1, 3):
+        z = wide[:, off:off + n]
+        zt = block[:, off:off + n]
+        th = [-0.5, 0.25, 1.0]
+        want = orc.encode(z, th)
+        for tm in (False, True):
+            guard = torch.full((nchan, n + 7), 77, dtype=torch.uint8, device="cuda")
+            src = block.t().contiguous()[off:off + n] if tm else zt
+            snd.encode(src, th, time_major=tm, out=guard[:, 2:2 + n])
+            g = guard.cpu().numpy()
+            assert np.array_equal(g[:, 2:2 + n], want) and np.all(g[:, :2] == 77) and np.all(g[:, 2 + n:] == 77)
+            words = torch.full((nchan, (n + 31) // 32 + 2), -1, dtype=torch.int32, device="cuda")
+            snd.encode_bits(src, 0.25, time_major=tm, out=words)
+            bits = np.unpackbits(words.cpu().numpy().view(np.uint8), axis=1, bitorder="little")
+            assert np.array_equal(bits[:, :n], orc.encode(z, [0.25]))
+            pad = (n + 31) // 32 * 32
+            assert np.all(bits[:, n:pad] == 0) and np.all(bits[:, pad:] == 1)
+        fin = np.nan_to_num(z)
+        ft = torch.nan_to_num(zt)
+        for dt, tt in (("bf16", torch.bfloat16), ("f16", torch.float16)):
+            assert torch.equal(snd.cast(zt, dt).cpu()[1:], torch.from_numpy(z[1:].copy()).to(tt))
+        for s in (1, 2, 3, 4, 8, 16):
+            if n // s:
+                assert np.array_equal(snd.scrunch(zt, s).cpu().numpy()[1:], orc.scrunch(z, s)[1:])
+        st = np.stack([fin.mean(1, dtype=np.float64), np.full(nchan, 1.5)], axis=1)
+        assert np.array_equal(snd.normalize(zt, torch.from_numpy(st).cuda()).cpu().numpy()[1:], orc.normalize(z, st)[1:])
+        for gamma in (1.0, 0.0):  # some samples of a wave corrected, then all of them
+            y = ft.clone()
+            snd.zero_dm(y, gamma)
+            assert np.array_equal(y.cpu().numpy(), orc.zero_dm(fin, gamma)[0])
