@@ -39,7 +39,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 # host part, streaming, batching, tuning, multi-rate, validation) and the detection kernels,
 # which the tree kernels do not include, do not change their traffic
 DIGEST_CPP = ("plan.cpp", "capi.cpp")
-DIGEST_SKIP = ("detect.hip", "frontend.hip", "detect_noalloc.hip", "label.hip", "snd_detect.h")
+DIGEST_SKIP = ("detect.hip", "frontend.hip", "fdmt.hip", "detect_noalloc.hip", "label.hip", "snd_detect.h")
 
 
 def source_digest():

@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "libsnd.so")
 BUILD = os.path.join(HERE, "_build")
 
 HIP_SOURCES = ["kernels.hip", "frontend.hip", "kernels_lds.hip", "kernels_fast_binary.hip", "kernels_fast_graded.hip",
-               "kernels_fast_float.hip", "kernels_bits.hip", "detect.hip", "label.hip",
+               "kernels_fast_float.hip", "kernels_bits.hip", "detect.hip", "label.hip", "fdmt.hip",
                "detect_noalloc.hip", "group_lin.hip", "group_pack.hip"]
 CXX_SOURCES = ["plan.cpp", "capi.cpp", "detect_host.cpp", "stream_host.cpp", "batch_host.cpp", "tune_host.cpp",
                "multirate_host.cpp", "validate_host.cpp", "fdmt_host.cpp", "subband_host.cpp"]

@@ -26,8 +26,8 @@
 #include "snd_internal.h"
 
 namespace snd {
-int launch_fdmt_merge(const float *src, int64_t src_pitch, float *dst, int64_t dst_pitch, const int32_t *tab,
-                      int64_t rows, int64_t n, void *stream);
+int launch_fdmt_pass(int k, const float *src, int64_t src_pitch, float *dst, int64_t dst_pitch,
+                     const int32_t *const *tabs, int64_t rows, int64_t n, void *stream);
 }
 
 struct snd_fdmt_s {
@@ -169,18 +169,27 @@ snd_status snd_fdmt_execute(snd_fdmt p, const float *d_in, int64_t in_pitch, flo
     float *buf[2] = {static_cast<float *>(d_ws), static_cast<float *>(d_ws) + p->max_rows * p->nsamp};
     const float *src = d_in;
     int64_t sp = in_pitch;
-    for (int32_t i = 0; i < p->iters; ++i) {
+    // Every pass but the first reads a plane of delay rows and all write one, so the passes are as few
+    // as they can be: four iterations in the first (its sources are the channels themselves, which stay
+    // cached) and up to three in each further one, evenly split.
+    const int32_t passes = p->iters <= 4 ? 1 : 1 + (p->iters - 4 + 2) / 3;
+    int32_t done = 0;
+    for (int32_t q = 0; q < passes; ++q) {
+        const int32_t k = p->iters / passes + (q < p->iters % passes);
+        const int32_t i = done + k - 1;  // the pass's last iteration
         const bool last = i == p->iters - 1;
-        float *dst = last ? d_out : buf[i & 1];
+        float *dst = last ? d_out : buf[q & 1];
         const int64_t dp = last ? out_pitch : p->nsamp;
-        int e = snd::launch_fdmt_merge(src, sp, dst, dp, p->d_tables + p->tab_off[(size_t)i], p->rows[(size_t)i],
-                                       p->nsamp, stream);
+        const int32_t *tabs[4];
+        for (int32_t j = 0; j < k; ++j) tabs[j] = p->d_tables + p->tab_off[(size_t)(i - j)];
+        int e = snd::launch_fdmt_pass(k, src, sp, dst, dp, tabs, p->rows[(size_t)i], p->nsamp, stream);
         if (e) {
             snd::set_error("FDMT merge launch: " + std::string(hipGetErrorString((hipError_t)e)));
             return SND_ERR_HIP;
         }
         src = dst;
         sp = dp;
+        done += k;
     }
     return SND_OK;
 }

@@ -43,6 +43,27 @@ def test_fdmt_small_exact(snd, orc, nchan, n, dm):
     assert np.sqrt(np.mean((yg - wg) ** 2) / np.mean(wg ** 2)) <= 1e-5
 
 
+@pytest.mark.parametrize("nchan", [2, 4, 8, 16, 32, 256, 512])
+@pytest.mark.parametrize("n", [255, 256, 1027])
+def test_fdmt_pass_splits_and_row_ends(snd, orc, nchan, n):
+    # one to nine iterations (every split into passes), rows that end inside, at and past a tile, a DM
+    # whose sweep takes most of the row (sources that run past its end), input and output rows that
+    # start on any element: integers, so every partial sum is exact
+    f = synth.channel_freqs(nchan)
+    bw = 16.0 / nchan
+    rng = synth.make_rng(nchan + n)
+    x = rng.integers(-8, 9, (nchan, n)).astype(np.float32)
+    block = torch.zeros((nchan, n + 3), device="cuda")
+    block[:, 1:1 + n] = torch.from_numpy(x)
+    for dm in (0.0, 0.8 * n / 14.17):
+        fd = snd.Fdmt(f, bw, 0.138e-3, dm, n)
+        out = torch.full((fd.n_delays, n + 5), -7.0, device="cuda")
+        fd.execute(block[:, 1:1 + n], out=out[:, 3:3 + n])
+        y = out.cpu().numpy()
+        assert np.array_equal(y[:, 3:3 + n], orc.fdmt(x, f, bw, 0.138e-3, dm).astype(np.float32))
+        assert np.all(y[:, :3] == -7.0) and np.all(y[:, 3 + n:] == -7.0)
+
+
 def test_fdmt_full_size_sampled_rows(snd, orc):
     # 1024 channels x 2^17 samples up to DM 2000: sampled rows against the direct sum over the
     # channel delays traced down the split rule
