@@ -149,8 +149,8 @@ typedef struct {
                                                regular level-1 nodes, 4 the same on bit rows,
                                                5 input-anchored on bit input, 6 LDS row groups
                                                summing float-mode rows as one sum each, 7 LDS
-                                               row groups forming graded levels on packed
-                                               16-bit counts */
+                                               row groups forming graded levels of regular
+                                               level-1 nodes on packed counts */
     int64_t stage_staged[SND_MAX_LEVELS];   /* LDS row groups: source elements staged per time
                                                tile summed over groups (0 otherwise) */
     int64_t stage_batches[SND_MAX_LEVELS];  /* LDS row groups: batches summed over groups */
@@ -191,9 +191,9 @@ snd_status snd_execute(snd_plan plan, const void *d_in, int64_t in_pitch, void *
  * before it, the last stage writes d_out.  Running stages 0 .. n_stages-1 in order on one
  * stream is exactly snd_execute.  Same arguments and errors as snd_execute.  Besides the node
  * rows, the workspace carries what a stage records for the next: for graded plans whose final
- * stage is the packed kernel (stage_kernel 7), stage 0 writes the largest leaf value there, and
- * the final stage picks its level-1 arithmetic from it, so a final stage must follow the
- * stage 0 that wrote its workspace (as in snd_execute).
+ * stage forms its levels on packed counts (stage_kernel 7, or 1 on u8 rows), stage 0 writes the
+ * largest leaf value there, and the final stage picks its lower levels' arithmetic from it, so a
+ * final stage must follow the stage 0 that wrote its workspace (as in snd_execute).
  */
 snd_status snd_execute_stage(snd_plan plan, int32_t stage, const void *d_in, int64_t in_pitch, void *d_out,
                              int64_t out_pitch, void *d_workspace, int64_t workspace_bytes, void *stream);

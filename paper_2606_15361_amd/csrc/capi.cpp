@@ -187,6 +187,9 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
         g.k_int = P.desc.k_int;
         g.cap = P.desc.cap;
         g.scale = scale;
+        g.wide_level = S.wide_level;
+        g.wide_inputs = S.wide_inputs;
+        g.wide_sub = S.wide_sub;
         if (bound && S.group_pack && si == 1 && P.bound_off >= 0)
             g.bound = reinterpret_cast<const uint32_t *>(ws + P.bound_off) + P.bound_n;
         pr.n_run = run.n_run;

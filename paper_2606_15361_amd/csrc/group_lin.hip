@@ -61,12 +61,12 @@ struct LinF32 : LinBase {
     static constexpr int V = kStep / 64;
     static constexpr int kState = R * V;
 
-    // the n inputs of every row of the wave from the batch at buf; the lane's offset word at w
+    // the n inputs of every row of the wave from the batch at buf; w: the lane's offset word
     static __device__ __forceinline__ void add_batch(float (&st)[kState], const unsigned char *buf,
-                                                     const unsigned char *w, int lane, const Carry &c,
+                                                     const uint32_t (&w)[1], int lane, const Carry &c,
                                                      const GroupArgs &)
     {
-        const uint32_t vw = *reinterpret_cast<const uint32_t *>(w);
+        const uint32_t vw = w[0];
         const int n = c.n;
         const unsigned char *lane_base = buf + 4 * lane;
         for (int i = 0; i < n; ++i) {
@@ -157,10 +157,10 @@ struct Lin16 : LinBase {
     // Row q's inputs that start a dword (the first even_q of its n words), then the others: two
     // loops per row without a branch per input, two inputs in flight.
     static __device__ __forceinline__ void add_batch(float (&st)[kState], const unsigned char *buf,
-                                                     const unsigned char *w, int lane, const Carry &c,
+                                                     const uint32_t (&w)[1], int lane, const Carry &c,
                                                      const GroupArgs &)
     {
-        const uint32_t vw = *reinterpret_cast<const uint32_t *>(w);
+        const uint32_t vw = w[0];
         const int n = c.n;
         const uint32_t even = c.even;
         // (1.0, 1.0) in bf16, materialised in a scalar register so that the compiler cannot encode

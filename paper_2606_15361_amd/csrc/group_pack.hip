@@ -1,24 +1,36 @@
-// Final stage of a graded-mode plan on u8 rows with regular level-1 nodes (Methods, "Tree
-// activation modes": every node's output is the sum of its inputs clipped at the cap, at every
-// level up to the root).
+// Final stage of a graded-mode plan on u8 rows (Methods, "Tree activation modes": every node's output
+// is the sum of its inputs clipped at the cap, at every level up to the root).  Integer arithmetic in
+// the tree's own order throughout, or where no clip can apply in an order that gives the same integer:
+// the result is the tree's, bit for bit.
 //
-// Staging is the table pipeline of the one-sum float kernel (group_tab.h).  Each wave computes
-// two DM rows over a tile of 1024 samples (32 DM-adjacent rows per workgroup) where the open
-// level sums of the shape allow (four inputs per level-1 node, depth <= 4), else four rows over
-// 512 samples; lane i owns samples 4 i + 256 v.  An input at LDS byte offset o is read as the two aligned
-// dwords that hold its four samples for the lane (one ds_read2_b32), and one byte permute per
-// pair picks them out as two 16-bit counts: (samples 0, 2) and (samples 1, 3), whichever byte of
-// the dword the input starts at.  Level sums are then formed two samples per instruction with
-// 32-bit adds (fan-in x cap < 2^16, so the halves never carry into each other) and clipped with
-// a packed 16-bit minimum; levels 2 .. D close with compile-time control as the plan's closing
-// counts say.  Integer arithmetic in the tree's own order: the result is the tree's, bit for bit.
+// Staging is the table pipeline of the one-sum float kernel (group_tab.h); each wave computes two DM
+// rows over 1008 samples, or four rows over 512 (depth 5, or level-1 nodes of eight inputs).  What
+// bounds the sums is instruction issue (vector and scalar) and the waits of only four waves per SIMD, so the
+// path is the one with the fewest instructions and reads per input that the plane's largest value m,
+// which the stage that wrote it reports, allows; it is chosen per launch:
 //
-// When the stage that wrote the input plane reports its largest value m and F1 m < 256, a
-// level-1 node's sums fit a byte per sample: each input's four samples are aligned into one
-// dword (v_alignbyte_b32, whatever its byte phase), the F1 dwords are added as four bytes at
-// once, and only the node's sum is split into 16-bit counts for the clip.  A sample position
-// that holds no valid output (past the last tile's valid length) may carry out of its byte, but
-// only into higher positions, which hold none either.
+// * Wide sums (PackWide; two-row shapes): with n inputs in the largest super node (at most 16, two
+//   levels of a tree of four) and n m < 256 no sum inside a super node passes a byte, and with the sums
+//   one level below it at most the cap no clip inside it does anything.  So its inputs are added four
+//   samples per instruction as the dwords that hold them, wherever their first sample sits in its dword:
+//   grouped by that byte phase, highest first, the running sum is moved down by the difference (one
+//   cross-lane move and one byte align) before the next group joins, at most three times per node
+//   instead of once per input, and every input costs one dword read, not two.  Only the node's sum is
+//   split into 16-bit counts, clipped and added to the levels above.  A lane needs its neighbour's dword
+//   for those moves, so 63 lanes own samples and the 64th only feeds the 63rd.  1024 channels x 4096 DMs
+//   x 102,748 samples: 4.9 ms (byte sums at level 1: 5.5); 1000 channels (a ragged tree) x 1021 DMs x
+//   32.9 k samples: 0.48 ms (1.22 on the general row-group kernel, one byte per LDS read).
+// * Byte sums at level 1 (BYTES; regular level-1 nodes of F1 inputs, F1 m < 256): each input's four
+//   samples are aligned into one dword (v_alignbyte_b32) from the two that hold them, the F1 dwords are
+//   added as four bytes at once, and the node's sum is split into 16-bit counts for the clip.
+// * Any plane: one byte permute per pair of samples picks them out of two dwords as 16-bit counts,
+//   (0, 2) and (1, 3); level sums are formed two samples per instruction (fan-in x cap < 2^16, so the
+//   halves never carry into each other) and clipped with a packed 16-bit minimum.  Levels close with
+//   compile-time control as the plan's closing counts say (PackGraded), or, where level-1 nodes are
+//   irregular, input by input (PackAny).
+//
+// A sample position that holds no valid output (past the last tile's valid length) may carry out of
+// its byte, but only into higher positions, which hold none either.
 #include <hip/hip_runtime.h>
 
 #include "group_tab.h"
@@ -45,7 +57,7 @@ struct PackGraded {
     using A = uint32_t;
     static constexpr int kRows = pack_rows(F1, D), kStep = pack_tile(F1, D), kWords = kPackWords,
                          kSmemWords = kPackSmemWords;
-    static constexpr int R = kRows, V = kStep / 256, K = 2 * V;
+    static constexpr int R = kRows, V = (kStep + 255) / 256, K = 2 * V;
     static constexpr int OUT = D - 1;  // slot of the root
     static constexpr int kState = D * R * K;
     static_assert(F1 >= 3, "three-input adds");
@@ -55,7 +67,7 @@ struct PackGraded {
     };
     static __device__ __forceinline__ Carry carry(const uint32_t (&blk)[kPackSmemWords])
     {
-        return Carry{blk[22], blk[23], (int)blk[kPackSmemWords - 1]};
+        return Carry{blk[kPackCloses], blk[kPackCloses + 1], (int)blk[kPackSmemWords - 1]};
     }
     static __device__ __forceinline__ A &at(A (&st)[kState], int j, int q, int k) { return st[(j * R + q) * K + k]; }
 
@@ -117,11 +129,10 @@ struct PackGraded {
     }
 
     // the level-1 nodes of one batch: for each, its F1 inputs per row, then the closes
-    static __device__ __forceinline__ void add_batch(A (&st)[kState], const unsigned char *buf, const unsigned char *w,
+    static __device__ __forceinline__ void add_batch(A (&st)[kState], const unsigned char *buf, const uint32_t (&w)[4],
                                                      int lane, const Carry &cr, const GroupArgs &s)
     {
-        const uint4 w4 = *reinterpret_cast<const uint4 *>(w);  // component q: row q's input `lane`
-        const uint32_t wq[4] = {w4.x, w4.y, w4.z, w4.w};
+        const uint32_t (&wq)[4] = w;  // component q: row q's input `lane`
         const uint32_t cap2 = (uint32_t)s.cap * 0x00010001u;
         const unsigned char *lane_base = buf + 4 * lane;
         const int nn = cr.n / F1;
@@ -209,44 +220,308 @@ struct PackGraded {
     }
 };
 
+// Two rows over four blocks of 252 samples: lane i owns samples 4 i + 252 v, lane 63 none.  U: levels
+// above the super nodes.  st[(j * 2 + q) * 8 + 2 v + h], j < max(U, 1): the open sums of those levels as
+// 16-bit counts of samples (h, h + 2) (U = 0: the root itself), then st[NB + 4 q + v]: the open super
+// node's byte sums.
+template <int U>
+struct PackWide {
+    using TI = uint8_t;
+    using TO = uint8_t;
+    using A = uint32_t;
+    static constexpr int kRows = 2, kStep = kPackWideTile, kWords = kPackWords, kSmemWords = kPackSmemWords;
+    static constexpr int V = 4, K = 2 * V, L = U > 0 ? U : 1;
+    static constexpr int NB = L * 2 * K, kState = NB + 2 * V;
+    struct Carry {
+        uint32_t part[kPackMaxParts / 2];
+        int n;
+    };
+    static __device__ __forceinline__ Carry carry(const uint32_t (&blk)[kPackSmemWords])
+    {
+        Carry c;
+#pragma unroll
+        for (int i = 0; i < kPackMaxParts / 2; ++i) c.part[i] = blk[kPackParts + i];
+        c.n = (int)blk[kPackSmemWords - 2];
+        return c;
+    }
+    // the sums moved down by `bytes` (1..3) byte positions, the next lane's low bytes coming in
+    static __device__ __forceinline__ void drop(uint32_t (&acc)[V], uint32_t bytes)
+    {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc[v], 0x130, 0xf, 0xf, true);  // wave_shl:1
+            acc[v] = __builtin_amdgcn_alignbyte(next, acc[v], bytes);
+        }
+    }
+    template <int C>
+    static __device__ __forceinline__ void load(uint32_t (&x)[C][V], uint32_t (&d)[C], uint32_t words, int k,
+                                                const unsigned char *lane_base)
+    {
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)words, k + u);
+            d[u] = o & 3u;
+            const uint32_t *p = reinterpret_cast<const uint32_t *>(lane_base + (o & ~3u));
+#pragma unroll
+            for (int v = 0; v < V; ++v) x[u][v] = p[63 * v];
+        }
+    }
+    template <int C>
+    static __device__ __forceinline__ void add(uint32_t (&acc)[V], const uint32_t (&x)[C][V], const uint32_t (&d)[C])
+    {
+        if constexpr (C == 4) {  // most groups of four hold one phase
+            if ((d[0] | d[1] | d[2] | d[3]) == 0u) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[v] = (acc[v] + x[0][v] + x[1][v]) + x[2][v] + x[3][v];
+                return;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < C; u += 2) {  // every branch is uniform
+            if (d[u]) drop(acc, d[u]);
+            if (u + 1 < C && d[u + 1] == 0) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[v] = acc[v] + x[u][v] + x[u + 1][v];
+                continue;
+            }
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[v] += x[u][v];
+            if (u + 1 < C) {
+                drop(acc, d[u + 1]);
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[v] += x[u + 1][v];
+            }
+        }
+    }
+    // levels J .. U above the super nodes, the last of which stays open (the root, clipped at the store)
+    template <int J>
+    static __device__ __forceinline__ void close_from(A (&st)[kState], int c, uint32_t cap2)
+    {
+        if constexpr (J < U) {
+            if (c > J) {
+#pragma unroll
+                for (int i = 0; i < 2 * K; ++i) {
+                    const uint32_t y = pk_min_u16(st[(J - 1) * 2 * K + i], cap2);
+                    st[(J - 1) * 2 * K + i] = 0;
+                    st[J * 2 * K + i] += y;
+                }
+                close_from<J + 1>(st, c, cap2);
+            }
+        }
+    }
+    static __device__ __forceinline__ void add_batch(A (&st)[kState], const unsigned char *buf, const uint32_t (&w)[4],
+                                                     int lane, const Carry &cr, const GroupArgs &s)
+    {
+        const uint32_t cap2 = (uint32_t)s.cap * 0x00010001u;
+        const unsigned char *lane_base = buf + 4 * lane;
+        int k = 0;  // first input of the part
+#pragma unroll 1
+        for (int i = 0; i < cr.n; ++i) {
+            const uint32_t word = i < 2 ? cr.part[0] : i < 4 ? cr.part[1] : i < 6 ? cr.part[2] : cr.part[3];
+            const uint32_t part = i & 1 ? word >> 16 : word & 0xffffu;
+            const int n = (int)(part & 31u), c = (int)((part >> 5) & 7u);
+            uint32_t acc[2][V];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[q][v] = 0u;
+            int j = 0;
+            for (; j + 4 <= n; j += 4) {  // four inputs of each row in flight
+                uint32_t x0[4][V], x1[4][V], d0[4], d1[4];
+                load(x0, d0, w[2], k + j, lane_base);
+                load(x1, d1, w[3], k + j, lane_base);
+                add(acc[0], x0, d0);
+                add(acc[1], x1, d1);
+            }
+            for (; j < n; ++j) {
+                uint32_t x0[1][V], x1[1][V], d0[1], d1[1];
+                load(x0, d0, w[2], k + j, lane_base);
+                load(x1, d1, w[3], k + j, lane_base);
+                add(acc[0], x0, d0);
+                add(acc[1], x1, d1);
+            }
+            k += n;
+            const uint32_t last[2] = {(part >> 8) & 3u, (part >> 10) & 3u};
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (last[q]) drop(acc[q], last[q]);
+#pragma unroll
+                for (int v = 0; v < V; ++v) st[NB + V * q + v] += acc[q][v];
+            }
+            if (c == 0) continue;  // the super node goes on in the next batch
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const uint32_t b = st[NB + V * q + v];
+                    st[NB + V * q + v] = 0u;
+                    st[q * K + 2 * v] += pk_min_u16(__builtin_amdgcn_perm(0u, b, 0x0c020c00u), cap2);
+                    st[q * K + 2 * v + 1] += pk_min_u16(__builtin_amdgcn_perm(0u, b, 0x0c030c01u), cap2);
+                }
+            close_from<1>(st, c, cap2);
+        }
+    }
+    static __device__ __forceinline__ void store(const A (&st)[kState], int q, uint8_t *drow, int lane, int vt,
+                                                 const GroupArgs &s)
+    {
+        const uint32_t cap2 = (uint32_t)s.cap * 0x00010001u;
+        auto d = as_global(drow);
+        const bool vec = (reinterpret_cast<uintptr_t>(drow) & 3u) == 0;
+        if (lane == 63) return;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const uint32_t x = pk_min_u16(st[((L - 1) * 2 + q) * K + 2 * v], cap2) |
+                               pk_min_u16(st[((L - 1) * 2 + q) * K + 2 * v + 1], cap2) << 8;
+            const int t = 4 * lane + 252 * v;
+            if (vec && t + 4 <= vt) {
+                *reinterpret_cast<__attribute__((address_space(1))) uint32_t *>(d + t) = x;
+            } else {
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (t + b < vt) d[t + b] = (uint8_t)(x >> (8 * b));
+            }
+        }
+    }
+};
+
+// Any nodes: 16-bit counts, input by input, as the inputs' closing counts say.  Two rows, lane i
+// owning samples 4 i + 256 v; st[(j * 2 + q) * 8 + 2 v + h]: the open sums of levels j + 1 = 1 .. D (the
+// root is clipped at the store).
+template <int D>
+struct PackAny {
+    using TI = uint8_t;
+    using TO = uint8_t;
+    using A = uint32_t;
+    static constexpr int kRows = 2, kStep = kPackWideTile, kWords = kPackWords, kSmemWords = kPackSmemWords;
+    static constexpr int V = 4, K = 2 * V, kState = D * 2 * K;
+    struct Carry {
+        uint32_t close[kPackMaxBatchEntries / 8];
+        int n;
+    };
+    static __device__ __forceinline__ Carry carry(const uint32_t (&blk)[kPackSmemWords])
+    {
+        Carry c;
+#pragma unroll
+        for (int i = 0; i < kPackMaxBatchEntries / 8; ++i) c.close[i] = blk[kPackCloses + i];
+        c.n = (int)blk[kPackSmemWords - 1];
+        return c;
+    }
+    template <int J>
+    static __device__ __forceinline__ void close_from(A (&st)[kState], int c, uint32_t cap2)
+    {
+        if constexpr (J < D) {
+            if (c >= J) {
+#pragma unroll
+                for (int i = 0; i < 2 * K; ++i) {
+                    const uint32_t y = pk_min_u16(st[(J - 1) * 2 * K + i], cap2);
+                    st[(J - 1) * 2 * K + i] = 0;
+                    st[J * 2 * K + i] += y;
+                }
+                close_from<J + 1>(st, c, cap2);
+            }
+        }
+    }
+    static __device__ __forceinline__ void add_batch(A (&st)[kState], const unsigned char *buf, const uint32_t (&w)[4],
+                                                     int lane, const Carry &cr, const GroupArgs &s)
+    {
+        const uint32_t cap2 = (uint32_t)s.cap * 0x00010001u;
+        const unsigned char *lane_base = buf + 4 * lane;
+#pragma unroll
+        for (int g = 0; g < kPackMaxBatchEntries / 8; ++g) {
+            uint32_t closes = cr.close[g];
+            for (int i = 8 * g; i < 8 * g + 8 && i < cr.n; ++i, closes >>= 4) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)(w[q]), i);
+                    const uint32_t sel = 0x0c020c00u + (o & 3u) * 0x00010001u;
+                    const uint32_t *p = reinterpret_cast<const uint32_t *>(lane_base + (o & ~3u));
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const uint32_t lo = p[64 * v], hi = p[64 * v + 1];
+                        st[q * K + 2 * v] += __builtin_amdgcn_perm(hi, lo, sel);
+                        st[q * K + 2 * v + 1] += __builtin_amdgcn_perm(hi, lo, sel + 0x00010001u);
+                    }
+                }
+                close_from<1>(st, (int)(closes & 15u), cap2);
+            }
+        }
+    }
+    static __device__ __forceinline__ void store(const A (&st)[kState], int q, uint8_t *drow, int lane, int vt,
+                                                 const GroupArgs &s)
+    {
+        const uint32_t cap2 = (uint32_t)s.cap * 0x00010001u;
+        auto d = as_global(drow);
+        const bool vec = (reinterpret_cast<uintptr_t>(drow) & 3u) == 0;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const uint32_t x = pk_min_u16(st[((D - 1) * 2 + q) * K + 2 * v], cap2) |
+                               pk_min_u16(st[((D - 1) * 2 + q) * K + 2 * v + 1], cap2) << 8;
+            const int t = 4 * lane + 256 * v;
+            if (vec && t + 4 <= vt) {
+                *reinterpret_cast<__attribute__((address_space(1))) uint32_t *>(d + t) = x;
+            } else {
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (t + b < vt) d[t + b] = (uint8_t)(x >> (8 * b));
+            }
+        }
+    }
+};
+
 }  // namespace
 
-template <int F1, int D>
+// F1 0: any nodes, U levels above the super nodes.  The bodies are separate, so that none holds
+// another's registers; the choice is per record (uniform per workgroup).
+template <int F1, int D, int U>
 __global__ __launch_bounds__(1024) void k_group_pack(GroupArgs s0, Multi m)
 {
     GroupArgs s;
     uint32_t bid, nblk;
     select_record(s0, m, s, bid, nblk);
-    // per record (uniform per workgroup); the two bodies are separate so that neither holds the
-    // other's registers
-    if (s.bound && (uint32_t)F1 * as_const(s.bound)[0] <= 255u)
-        group_tab_run<PackGraded<F1, D, true>>(s, bid, nblk);
-    else
-        group_tab_run<PackGraded<F1, D, false>>(s, bid, nblk);
+    const uint32_t most = s.bound ? as_const(s.bound)[0] : 0xffffu;  // largest value of the input plane
+    if constexpr (U >= 0) {
+        if ((uint32_t)s.wide_inputs * most <= 255u && (uint32_t)s.wide_sub * most <= (uint32_t)s.cap) {
+            group_tab_run<PackWide<U>>(s, bid, nblk);
+            return;
+        }
+    }
+    if constexpr (F1 == 0) {
+        group_tab_run<PackAny<D>>(s, bid, nblk);
+    } else {
+        if ((uint32_t)F1 * most <= 255u) group_tab_run<PackGraded<F1, D, true>>(s, bid, nblk);
+        else group_tab_run<PackGraded<F1, D, false>>(s, bid, nblk);
+    }
 }
 
 namespace {
 
-template <int F1, int D>
+template <int F1, int D, int U>
 int launch_pack(const GroupArgs &a, int64_t n_out, int lds, void *stream, const Multi &m, int64_t nb_multi)
 {
     const int64_t ntt = (n_out + pack_tile(F1, D) - 1) / pack_tile(F1, D);
     const int64_t nb = m.n > 0 ? nb_multi : (int64_t)a.ngroups * ntt;
     if (nb <= 0) return 0;
     if (nb > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_group_pack<F1, D>), dim3((uint32_t)nb), dim3(1024), lds, (hipStream_t)stream, a, m);
+    hipLaunchKernelGGL((k_group_pack<F1, D, U>), dim3((uint32_t)nb), dim3(1024), lds, (hipStream_t)stream, a, m);
     return (int)hipGetLastError();
 }
 
 }  // namespace
 
-// Every (inputs per level-1 node, depth) pair the plan builder admits for this kernel.
+// Every (inputs per level-1 node, depth) pair the plan builder admits for this kernel, and with
+// irregular nodes every (depth, levels above the super nodes).
 int launch_group_pack(const GroupArgs &a, int64_t n_out, int lds, void *stream, const Multi &m, int64_t nblocks)
 {
-#define SND_PACK(F, DD) \
-    if (a.f1 == F && a.depth == DD) return launch_pack<F, DD>(a, n_out, lds, stream, m, nblocks);
-    SND_PACK(4, 1) SND_PACK(4, 2) SND_PACK(4, 3) SND_PACK(4, 4) SND_PACK(4, 5)
-    SND_PACK(8, 1) SND_PACK(8, 2) SND_PACK(8, 3) SND_PACK(8, 4)
+    const int u = a.depth - a.wide_level;
+#define SND_PACK(F, DD, UU) \
+    if (a.f1 == F && a.depth == DD && (UU < 0 || u == UU)) \
+        return launch_pack<F, DD, UU>(a, n_out, lds, stream, m, nblocks);
+    SND_PACK(4, 1, 0) SND_PACK(4, 2, 0) SND_PACK(4, 3, 1) SND_PACK(4, 4, 2) SND_PACK(4, 5, -1)
+    SND_PACK(8, 1, -1) SND_PACK(8, 2, -1) SND_PACK(8, 3, -1) SND_PACK(8, 4, -1)
+    SND_PACK(0, 1, 0)
+    SND_PACK(0, 2, 0) SND_PACK(0, 2, 1)
+    SND_PACK(0, 3, 0) SND_PACK(0, 3, 1) SND_PACK(0, 3, 2)
+    SND_PACK(0, 4, 0) SND_PACK(0, 4, 1) SND_PACK(0, 4, 2) SND_PACK(0, 4, 3)
 #undef SND_PACK
     return (int)hipErrorInvalidValue;
 }

@@ -25,7 +25,7 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
     constexpr int ES = (int)sizeof(TI);
     constexpr int R = Sum::kRows, T = Sum::kStep, NW = Sum::kWords, NSM = Sum::kSmemWords;
     constexpr int WPL = NW / 64;  // offset words per lane
-    static_assert(WPL == 1 || WPL == 4, "one global_load_lds of 4 or 16 bytes per lane");
+    static_assert(WPL == 1 || WPL == 4, "one load of 4 or 16 bytes per lane");
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -43,7 +43,7 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
     const_ptr<int32_t> instrs = as_const(s.instrs);
     const int64_t pitch_bytes = s.src_pitch * (int64_t)ES;
     const int buf_bytes = s.buf_elems * ES;
-    const int stride = buf_bytes + kGroupRows * NW * 4;  // bytes of one buffer: windows, then offset words
+    const int stride = buf_bytes;  // bytes of one buffer
     const bool full = vt == T;  // full tiles copy from the chunk table; the last tile by window
 
     A st[Sum::kState];
@@ -55,8 +55,8 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
     // samples); chunk sources add their unit index
     const uint4 *tile_src = reinterpret_cast<const uint4 *>(srcb) + (uint32_t)(t0 * ES) / 16u + lane;
     // Copies of batch bb into buffer j: this wave's chunks of its windows (scalar words blk), or
-    // its windows one by one in the last tile, and the wave's offset words.
-    auto issue = [&](int bb, const uint32_t (&blk)[NSM], int j) {
+    // its windows one by one in the last tile; and the lane's offset words of the batch into w.
+    auto issue = [&](int bb, const uint32_t (&blk)[NSM], int j, uint32_t (&w)[WPL]) {
         unsigned char *buf_base = smem + j * stride;
         if (full) {
             const int nch = (int)blk[0];
@@ -71,9 +71,11 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
             issue_batch<TI>(batches, instrs, bb, wave, lane, srcb, pitch_bytes, t0, vt,
                             reinterpret_cast<TI *>(buf_base));
         }
-        const uint32_t *wp = s.lin + ((int64_t)bb * kGroupRows + wave) * NW + WPL * lane;
-        __builtin_amdgcn_global_load_lds(wp, (__attribute__((address_space(3))) void *)(buf_base + buf_bytes + 4 * NW * wave),
-                                         Sum::kWords / 16, 0, 0);
+        const auto wp = as_global(s.lin + ((int64_t)bb * kGroupRows + wave) * NW + WPL * lane);
+        typedef uint32_t words_t __attribute__((ext_vector_type(WPL)));
+        const words_t t = *reinterpret_cast<global_ptr<const words_t>>(wp);
+#pragma unroll
+        for (int i = 0; i < WPL; ++i) w[i] = t[i];
     };
     auto load_blk = [&](int bb, uint32_t (&blk)[NSM]) {
         const_ptr<uint32_t> p = smem_tab + ((int64_t)bb * kGroupRows + wave) * NSM;
@@ -83,10 +85,11 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
 
     const int b0 = as_const(s.batch_ptr)[g], b1 = as_const(s.batch_ptr)[g + 1];
     uint32_t blk[NSM];
+    uint32_t w[WPL] = {}, wn[WPL] = {};  // the wave's offset words of batches b and b + 1
     typename Sum::Carry cur{};
     if (b0 < b1) {
         load_blk(b0, blk);
-        issue(b0, blk, 0);
+        issue(b0, blk, 0, w);
         cur = Sum::carry(blk);
     }
     int slot = 0;
@@ -97,12 +100,14 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
         stage_barrier();  // everyone's have; everyone is done reading batch b - 1
         typename Sum::Carry nxt{};
         if (b + 1 < b1) {  // into the buffer of batch b - 1
-            issue(b + 1, blk, slot ^ 1);
+            issue(b + 1, blk, slot ^ 1, wn);
             nxt = Sum::carry(blk);
         }
         const unsigned char *buf_base = smem + slot * stride;
-        Sum::add_batch(st, buf_base, buf_base + buf_bytes + 4 * NW * wave + 4 * WPL * lane, lane, cur, s);
+        Sum::add_batch(st, buf_base, w, lane, cur, s);
         cur = nxt;
+#pragma unroll
+        for (int i = 0; i < WPL; ++i) w[i] = wn[i];
         slot ^= 1;
     }
 

@@ -106,15 +106,16 @@ bool valid_dtype_pair(int mode, int in_dt, int node_dt, int cap)
 // leaves the stage on the generic kernel) when one entry alone does not fit the LDS budget.
 // Variants: kGroupGeneric (any tree), kGroupFast (regular level-1 nodes, compile-time depth),
 // kGroupLin (float mode: every row is one sum over its inputs, with no activation in between),
-// kGroupPack (graded mode on u8 rows with regular level-1 nodes of 4 or 8 inputs: the linear
-// kernel's staging, levels formed on pairs of 16-bit counts).
+// kGroupPack (graded mode on u8 rows with regular level-1 nodes of 4 or 8 inputs, or of any nodes of up
+// to 16 inputs and depth <= 4: the linear kernel's staging, levels formed on bytes and pairs of 16-bit
+// counts).
 enum { kGroupGeneric = 0, kGroupFast = 1, kGroupLin = 2, kGroupPack = 3 };
 bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
 {
     const bool allow_fast = variant == kGroupFast || variant == kGroupPack;
     const bool lin = variant == kGroupLin;
     const bool pack = variant == kGroupPack;
-    const bool tab = lin || pack;  // kernels that copy by chunk tables and read offset words from LDS
+    const bool tab = lin || pack;  // kernels that copy by chunk tables and take offset words by lane
     // these kernels read a materialised plane of f32, bf16 or f16 rows (linear) or u8 rows
     // (packed), whose pitch their copy table holds; the packed kernel's 16-bit counts hold any
     // level sum (fan-in x cap < 2^16)
@@ -151,18 +152,39 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
         bool reg = f1 > 0 && ne % f1 == 0;
         for (int32_t e = 0; e < ne && reg; ++e)
             if (((S.ent[e].rowc >> 24) >= 1) != ((e + 1) % f1 == 0)) reg = false;
+        // level-1 nodes of two inputs each keep the specialised kernel, whose general path costs less
+        if (pack && reg && f1 == 2) return false;
         if (!allow_fast || !reg || !group_fast_supported(f1, S.depth) ||
             !group_fast_types(p.desc.mode, S.src_dtype, S.dst_dtype))
             f1 = 0;
     }
     if (lin) f1 = 0;
-    if (pack && !((f1 == 4 && S.depth <= 5) || (f1 == 8 && S.depth <= 4))) return false;
+    auto closes_at = [&](int32_t e) { return (int32_t)(S.ent[e].rowc >> 24); };  // identical for every row
+    int32_t wide_level = 0, wide_inputs = 0, wide_sub = 0;
+    if (pack) {
+        if (!((f1 == 4 && S.depth <= 5) || (f1 == 8 && S.depth <= 4))) f1 = 0;
+        if (f1 == 0 && S.depth > kPackAnyDepth) return false;
+        if (pack_rows(f1, S.depth) == 2) {  // the super nodes of the wide path
+            for (int32_t l = 1; l <= S.depth; ++l) {
+                int32_t most = 0, run = 0;  // inputs of the largest level-l node
+                for (int32_t e = 0; e < ne; ++e) {
+                    most = std::max(most, ++run);
+                    if (closes_at(e) >= l) run = 0;
+                }
+                if (most > kPackWideInputs) break;
+                wide_sub = wide_inputs;
+                wide_inputs = most;
+                wide_level = l;
+            }
+            if (wide_level == 0 && f1 == 0) return false;
+        }
+    }
     const bool bits = S.src_dtype == SND_DT_BITS;
     if (bits && !f1) return false;  // bit rows: specialised kernel only
     // samples a window holds beyond its span (its tile, plus one unit for the linear kernel on
     // 16-bit rows), and the tile step in time
     const int tile = lin    ? lin_cover(S.src_dtype)
-                     : pack ? pack_tile(f1, S.depth) + 16
+                     : pack ? (pack_rows(f1, S.depth) == 2 ? kPackReach : pack_tile(f1, S.depth) + 16)
                      : bits ? kGroupTileBits
                      : f1   ? kGroupTileFast
                             : kGroupTile;
@@ -205,7 +227,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     std::vector<Src> srcs;
     std::vector<int32_t> slot_of(gr);
     std::vector<Src> unit_srcs;
-    std::vector<int32_t> unit_nsrc;
+    std::vector<int32_t> unit_nsrc, unit_slot_of, slot_lds;
     // table kernels: copy chunks of the open batch
     int32_t batch_chunks = 0;
     auto lin_chunks = [&](const Src &s) {  // 64-unit copies of one window in a full tile
@@ -220,7 +242,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
         // windows of every input of this unit, then one decision where the batch ends
         unit_srcs.clear();
         unit_nsrc.clear();
-        std::vector<std::vector<int32_t>> unit_slot_of;
+        unit_slot_of.clear();
         for (int32_t e = eu; e < eu + unit; ++e) {
             rd.clear();
             for (int w = 0; w < gr; ++w) {
@@ -241,7 +263,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
             }
             unit_nsrc.push_back((int32_t)srcs.size());
             unit_srcs.insert(unit_srcs.end(), srcs.begin(), srcs.end());
-            unit_slot_of.push_back(slot_of);
+            unit_slot_of.insert(unit_slot_of.end(), slot_of.begin(), slot_of.end());
         }
         int64_t need = 0;
         for (const Src &s : unit_srcs) need += slot_elems(s.lo, s.hi - s.lo);
@@ -253,6 +275,11 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
             for (const Src &s : unit_srcs) unit_chunks += lin_chunks(s);
             if (unit_chunks > kGroupRows * kLinMaxChunks) return false;
             lin_full = batch_chunks + unit_chunks > kGroupRows * kLinMaxChunks || eu - e0 + unit > max_entries;
+            if (wide_level) {  // or its parts: one for each super node that an input of it completes, one for the rest
+                int32_t parts = 1;
+                for (int32_t e = e0; e + 1 < eu + unit; ++e) parts += closes_at(e) >= wide_level;
+                lin_full = lin_full || parts > kPackMaxParts;
+            }
         }
         if (elems + need > budget || nslot_batch + (int32_t)unit_srcs.size() > max_slots || lin_full) {
             // close the batch
@@ -267,7 +294,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
         size_t si0 = 0;
         for (int32_t e = eu; e < eu + unit; ++e) {
             const int32_t ns = unit_nsrc[(size_t)(e - eu)];
-            std::vector<int32_t> slot_lds((size_t)ns);
+            slot_lds.resize((size_t)ns);
             for (int32_t i = 0; i < ns; ++i) {
                 const Src &sr = unit_srcs[si0 + (size_t)i];
                 // 16-byte aligned footprint; the window starts `head` elements into it so that
@@ -277,8 +304,8 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
                 slots.insert(slots.end(), {(int32_t)sr.row, sr.lo, sr.hi - sr.lo, slot_lds[(size_t)i]});
                 elems += slot_elems(sr.lo, sr.hi - sr.lo);
             }
-            const std::vector<int32_t> &so = unit_slot_of[(size_t)(e - eu)];
-            const uint32_t closes = S.ent[e].rowc & ~kRowMask;  // identical for every row
+            const int32_t *so = &unit_slot_of[(size_t)((e - eu) * gr)];
+            const uint32_t closes = S.ent[e].rowc & ~kRowMask;
             for (int w = 0; w < gr; ++w) {
                 const int32_t r = grp_rows[(size_t)(g * gr + w)];
                 if (r < 0) {
@@ -313,7 +340,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     static_assert(lin_max_batch_entries(SND_DT_F32) <= 15 && lin_max_batch_entries(SND_DT_BF16) <= 15 &&
                       lin_rows(SND_DT_BF16) * 4 <= 32,
                   "per-row input counts are packed in 4 bits, one word per wave");
-    static_assert(kPackMaxBatchEntries / 4 <= 16 && kPackRowsMax <= 4, "packed kernel: two closes words, 16-byte words");
+    static_assert(kPackRowsMax <= 4 && kPackWideInputs < 32, "packed kernel: 16-byte words, 5-bit part sizes");
     if (tab) {
         // per (batch, wave) the offset words of the wave's rows, and its copy chunks as scalar words
         const int64_t nb_all = (int64_t)(batches.size() / 4);
@@ -328,17 +355,47 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
                 for (int w = 0; w < kGroupRows; ++w) {
                     uint32_t *words = &lin_tab[(size_t)((b * kGroupRows + w) * n_words)];
                     uint32_t *sm = &lin_smem[(size_t)((b * kGroupRows + w) * n_smem)];
-                    if (pack) {  // lane i, component q: input i of row q; then each node's closes
+                    if (pack) {
+                        // an input's LDS byte offset (padding rows read offset 0)
                         for (int q = 0; q < rpw; ++q) {
-                            const int32_t r = grp_rows[(size_t)(g * gr + w * rpw + q)];
-                            for (int32_t e = ex; e < ey && r >= 0; ++e)
-                                words[4 * (e - ex) + q] = ldsb_at(g, w * rpw + q, e) & kRowMask;
+                            const bool pad = grp_rows[(size_t)(g * gr + w * rpw + q)] < 0;
+                            const uint32_t *o = &ldsb_at(g, w * rpw + q, ex);
+                            for (int32_t k = 0; k < n; ++k) words[4 * k + q] = pad ? 0u : o[(size_t)k * rpw] & kRowMask;
                         }
-                        for (int32_t k = 0; k < n / f1; ++k) {
-                            const uint32_t c = S.ent[ex + k * f1 + f1 - 1].rowc >> 24;
+                        for (int32_t k = 0; k < n / unit; ++k) {
+                            const uint32_t c = (uint32_t)closes_at(ex + k * unit + unit - 1);
                             if (c > 15) return false;
-                            sm[22 + k / 8] |= c << (4 * (k % 8));
+                            sm[kPackCloses + k / 8] |= c << (4 * (k % 8));
                         }
+                        int32_t parts = 0;
+                        for (int32_t p0 = ex; p0 < ey && wide_level; ++parts) {
+                            int32_t p1 = p0;
+                            while (p1 + 1 < ey && closes_at(p1) < wide_level) ++p1;
+                            const int32_t c = closes_at(p1);
+                            uint32_t part = (uint32_t)(p1 + 1 - p0) | (uint32_t)(c >= wide_level ? c - wide_level + 1 : 0) << 5;
+                            for (int q = 0; q < rpw; ++q) {  // by phase, highest first
+                                int32_t at[5] = {0, 0, 0, 0, 0};  // at[3 - ph]: place of the next input of phase ph
+                                for (int32_t k = p0 - ex; k <= p1 - ex; ++k) ++at[4 - (int32_t)(words[4 * k + q] & 3u)];
+                                for (int i = 1; i < 5; ++i) at[i] += at[i - 1];
+                                int32_t phase = -1;
+                                uint32_t drop[4] = {0, 0, 0, 0};  // how far the sums drop before a phase's first input
+                                for (int32_t ph = 3; ph >= 0; --ph) {
+                                    if (at[4 - ph] == at[3 - ph]) continue;
+                                    drop[ph] = phase < 0 ? 0u : (uint32_t)(phase - ph);
+                                    phase = ph;
+                                }
+                                for (int32_t k = p0 - ex; k <= p1 - ex; ++k) {
+                                    const uint32_t o = words[4 * k + q], ph = o & 3u;
+                                    words[4 * (p0 - ex + at[3 - ph]++) + 2 + q] = (o & ~3u) | drop[ph];
+                                    drop[ph] = 0u;
+                                }
+                                part |= (uint32_t)phase << (8 + 2 * q);
+                            }
+                            if (parts >= kPackMaxParts) return false;
+                            sm[kPackParts + parts / 2] |= part << (16 * (parts % 2));
+                            p0 = p1 + 1;
+                        }
+                        sm[n_smem - 2] = (uint32_t)parts;
                         sm[n_smem - 1] = (uint32_t)n;
                         continue;
                     }
@@ -393,12 +450,13 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     S.group_rpw = rpw;
     S.group_lin = lin;
     S.group_pack = pack;
+    S.wide_level = wide_level;
+    S.wide_inputs = wide_inputs;
+    S.wide_sub = wide_sub;
     const int64_t buf_bytes = round_up(max_elems * eb / 8, 16);
     S.lds_buf_elems = (int32_t)(buf_bytes * 8 / eb);
     // general kernel: batches b+1, b+2 land while b is read; the others: b+1
-    S.lds_bytes = (int32_t)(lin    ? kLinBuffers * (buf_bytes + kLinWordBytes)
-                            : pack ? 2 * (buf_bytes + kPackWordBytes)
-                                   : (f1 ? kFastBuffers : kGroupBuffers) * buf_bytes);
+    S.lds_bytes = (int32_t)((lin ? kLinBuffers : pack ? 2 : f1 ? kFastBuffers : kGroupBuffers) * buf_bytes);
     S.grp_rows = std::move(grp_rows);
     S.batch_ptr = std::move(batch_ptr);
     S.batches = std::move(batches);
@@ -883,7 +941,8 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
         I.stage_alg_bytes[si] = S.alg_bytes;
         I.stage_rows[si] = S.rows;
         I.stage_entries[si] = (int64_t)S.ent.size();
-        I.stage_kernel[si] = S.kernel == kKernelGroupLds && S.group_pack                   ? 7
+        // (packed sums over irregular nodes count among the row groups for any tree)
+        I.stage_kernel[si] = S.kernel == kKernelGroupLds && S.group_pack && S.group_f1 > 0 ? 7
                              : S.kernel == kKernelGroupLds && S.group_lin                  ? 6
                              : S.kernel == kKernelAnchored && S.src_dtype == SND_DT_BITS ? 5
                              : S.kernel == kKernelGroupLds && S.src_dtype == SND_DT_BITS ? 4

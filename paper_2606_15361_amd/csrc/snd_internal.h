@@ -67,7 +67,7 @@ struct Stage {
                                     // closes << 24 (general kernel) or LDS byte offset (specialised kernel)
     std::vector<int32_t> node_closes;  // specialised kernel: levels completed by each level-1 node
     // Linear kernel (float mode: the final stage is one sum over its inputs, no activation).  Per
-    // (global batch index, wave): kLinWords offset words, copied to LDS with the batch: words
+    // (global batch index, wave): kLinWords offset words, one per lane: words
     // q * n .. q * n + n - 1 are the LDS byte offsets of the first samples of the n inputs of the
     // wave's row q (16-bit rows: those that start a dword first, each part in plan order); and
     // kLinSmemWords words read as scalars: the number of copy chunks of the wave, then for its
@@ -77,6 +77,9 @@ struct Stage {
     // tables (kPackWords and kPackSmemWords per batch and wave) in the same two vectors.
     bool group_lin = false;
     bool group_pack = false;
+    // packed kernel, two-row shapes: the super nodes' level and largest number of inputs, and that of
+    // the nodes one level below
+    int32_t wide_level = 0, wide_inputs = 0, wide_sub = 0;
     std::vector<uint32_t> lin;
     std::vector<uint32_t> lin_smem;
     int64_t off_grp_rows = 0, off_batch_ptr = 0, off_batches = 0, off_instrs = 0, off_ldsb = 0;
@@ -125,25 +128,37 @@ constexpr int kLinWords = 64;                  // offset words per (batch, wave)
 constexpr int kLinMaxChunks = 7;               // copy chunks per (batch, wave)
 constexpr int kLinSmemWords = 24;              // chunk count, 7 units, 7 LDS offsets, 7 lengths, counts, n
 constexpr int kLinBuffers = 2;                 // batch b + 1 lands while b is read
-constexpr int kLinWordBytes = kGroupRows * kLinWords * 4;  // each buffer's copy of its batch's offset words
-constexpr int kLinLdsBytes = (163840 / kLinBuffers - kLinWordBytes) / 16 * 16;  // window bytes per buffer
-// Packed kernel (graded mode on u8 rows, regular level-1 nodes of 4 or 8 inputs): the staging
-// and copy tables of the linear kernel; each wave computes pack_rows DM rows over tiles of
-// pack_tile samples: two rows over 1024 samples where the open level sums of the shape fit the
-// registers (four inputs per level-1 node, depth <= 4: 32-row groups), four rows over 512
-// samples otherwise (64-row groups).  Lane i owns samples 4 i + 256 v as two pairs of 16-bit
-// counts, and reads each input as two aligned dwords (its first four samples may start in
-// either), so windows stage one 16-byte unit beyond the tile.  Offset words: lane i, component
-// q of a 16-byte word holds input i of row q.  Scalar words: those of the linear kernel, then
-// the levels each level-1 node of the batch completes (4 bits per node, two words), then n.
-constexpr int pack_rows(int f1, int depth) { return f1 == 4 && depth <= 4 ? 2 : 4; }
-constexpr int pack_tile(int f1, int depth) { return pack_rows(f1, depth) == 2 ? 1024 : 512; }
+constexpr int kLinLdsBytes = 163840 / kLinBuffers;  // window bytes per buffer
+// Packed kernel (graded mode on u8 rows): the staging and copy tables of the linear kernel.  Each
+// wave computes pack_rows DM rows over tiles of pack_tile samples: two rows where the open level sums
+// of the shape fit the registers (regular level-1 nodes of four inputs and depth <= 4, or any nodes
+// of depth <= kPackAnyDepth: f1 0; 32-row groups), four rows over 512 samples otherwise (64-row
+// groups).  Windows stage one 16-byte unit beyond the tile's reach, since an input's first samples may
+// start anywhere in a dword.
+// Two-row shapes sum the inputs of whole nodes as bytes (the wide path, chosen per launch when the
+// input plane's bound allows it): the super nodes, of the highest level whose nodes have at most
+// kPackWideInputs inputs.  Its lanes own 63 dwords of samples and the 64th only feeds its neighbour, so
+// those tiles are 4 x 252 samples.
+// Offset words: lane i, component q of a 16-byte word holds input i of row q, in the tree's order;
+// two-row shapes keep in components 2 and 3 the inputs of rows 0 and 1 grouped by byte phase within
+// each part (a batch's share of one super node): the byte offset of the dword that holds the first
+// sample, and in its low two bits by how many bytes the phase drops from the input before.
+// Scalar words: the chunk words of the linear kernel; the levels each level-1 node (f1 0: each input)
+// of the batch completes, 4 bits each; the parts, 16 bits each (inputs, levels completed from the super
+// node on (0: it goes on in the next batch), last phase of rows 0 and 1); their number; the inputs.
+constexpr int kPackAnyDepth = 4;
+constexpr int kPackWideInputs = 16;
+constexpr int kPackWideTile = 4 * 4 * 63;
+constexpr int kPackMaxParts = 8;
+constexpr int pack_rows(int f1, int depth) { return f1 == 0 || (f1 == 4 && depth <= 4) ? 2 : 4; }
+constexpr int pack_tile(int f1, int depth) { return pack_rows(f1, depth) == 2 ? kPackWideTile : 512; }
+constexpr int kPackReach = 1024 + 16;          // samples a two-row window holds beyond its span
 constexpr int kPackRowsMax = 4;
 constexpr int kPackMaxBatchEntries = 64;
 constexpr int kPackWords = 256;                // offset words per (batch, wave)
-constexpr int kPackSmemWords = 25;
-constexpr int kPackWordBytes = kGroupRows * kPackWords * 4;
-constexpr int kPackLdsBytes = (163840 / 2 - kPackWordBytes) / 16 * 16;
+constexpr int kPackCloses = 22, kPackParts = kPackCloses + kPackMaxBatchEntries / 8;  // first words
+constexpr int kPackSmemWords = kPackParts + kPackMaxParts / 2 + 2;
+constexpr int kPackLdsBytes = 163840 / 2;
 inline bool group_fast_types(int mode, int src_dt, int dst_dt)
 {
     if (mode == SND_MODE_BINARY) return (src_dt == SND_DT_U8 || src_dt == SND_DT_BITS) && dst_dt == SND_DT_U8;
@@ -282,6 +297,7 @@ struct GroupArgs {
     int32_t src_is_input;
     int32_t k_leaf, k_int, cap;
     float scale;
+    int32_t wide_level, wide_inputs, wide_sub;  // packed graded kernel (see Stage); 0: no wide path
     // packed graded kernel: the largest value of its input plane, written by the stage that
     // produced it (k_bound_reduce); nullptr: no bound known, the kernel takes its general path
     const uint32_t *bound;
@@ -338,11 +354,13 @@ int launch_ring_put_bits(const uint32_t *chunk, int64_t chunk_words, uint32_t *r
 
 // Compile-time shape of the kernel instance that runs stage S: the depth class, or, for the
 // specialised row-group kernel, 1000 * (inputs per level-1 node) + depth; -1 for the linear
-// kernel; minus the specialised shape for the packed kernel.
+// kernel; minus the specialised shape for the packed kernel (irregular nodes: its depth and the
+// levels above its super nodes).
 inline int stage_shape(const Stage &S)
 {
     if (S.kernel == kKernelGroupLds && S.group_lin) return -1;
-    if (S.kernel == kKernelGroupLds && S.group_pack) return -(1000 * S.group_f1 + S.depth);
+    if (S.kernel == kKernelGroupLds && S.group_pack)
+        return -(S.group_f1 ? 1000 * S.group_f1 + S.depth : 16000 + 10 * (S.depth - S.wide_level) + S.depth);
     if (S.kernel == kKernelGroupLds && S.group_f1 > 0) return 1000 * S.group_f1 + S.depth;
     return depth_bucket(S.depth);
 }

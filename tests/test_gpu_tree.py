@@ -250,6 +250,44 @@ def test_graded_packed_byte_sums_at_the_bound(snd, orc, B, top, cap):
     assert np.array_equal(gpu_run(pg, x), y)
 
 
+@pytest.mark.parametrize("nchan,B,top,cap", [
+    (256, 4, 15, 255), (256, 4, 16, 255),              # regular nodes: 16 inputs of at most 15, or 16
+    (64, 4, 15, 255), (1024, 4, 9, 255),               # no level, two levels above the super nodes
+    (256, 4, 15, 60), (256, 4, 15, 59),                # the sums one level below reach the cap, or pass it
+    (250, 4, 15, 255), (250, 4, 16, 255), (999, 4, 15, 255), (999, 4, 40, 200),  # ragged levels, both paths
+    (97, 3, 28, 255), (97, 3, 29, 255),                # super nodes of nine inputs
+    (203, 5, 30, 255), (500, 8, 31, 90), (500, 8, 32, 255), (255, 16, 15, 255), (255, 16, 17, 255),
+    (5, 4, 60, 255), (3, 4, 60, 40), (17, 2, 40, 255),  # trees of one to four levels
+])
+def test_graded_packed_wide_sums_at_the_bound(snd, orc, nchan, B, top, cap):
+    """The packed kernel adds whole super nodes (up to 16 inputs) as bytes when no sum inside one can
+    pass a byte and no clip inside it can act, for regular and ragged trees, and forms every level on
+    16-bit counts otherwise.  Most of the block carries leaves of exactly `top` in the first sixteen
+    clusters, whose super node reaches the largest sum; the DM grid shifts inputs through every byte
+    phase; rows end inside a tile and inside a lane's samples; the workspace starts filled with 0xFF.
+    Bit-exact against the oracle and the generic kernels."""
+    rng, f, dms, _ = _case(nchan, 150, 31 + nchan + B + top)
+    d = orc.delays(f, dms, 0.138e-3)
+    nsamp = int(d.max()) + 2 * 1008 + 253
+    x = synth.random_levels(rng, nchan, nsamp, max(1, min(top // 4, 4)))
+    q, r = divmod(top, 4)
+    for c in range(min(nchan // 4 * 4, 64)):  # channel values of one cluster summing to top
+        x[c, 50:nsamp - 50] = q + (1 if c % 4 < r else 0)
+    want, _ = orc.snd_dedup(x, f, d, mode="graded", cluster=4, branching=B, cap=cap)
+    p = snd.Plan(f, dms, 0.138e-3, nsamp, mode="graded", branching=B, cap=cap)
+    _say(f"packed wide sums nchan={nchan} B={B} top={top} cap={cap} n_out={p.n_out} {p.info['stage_kernel']}")
+    xt = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    ws = p.workspace(xt.device)
+    ws.fill_(255)
+    out = p.empty_output(xt.device)
+    p.execute(xt, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    y = to_np(out)
+    assert np.array_equal(y, want.astype(y.dtype))
+    pg = snd.Plan(f, dms, 0.138e-3, nsamp, mode="graded", branching=B, cap=cap, generic_kernels=True)
+    assert np.array_equal(gpu_run(pg, x), y)
+
+
 @pytest.mark.parametrize("mode,node", [("float", "f32"), ("float", "bf16"), ("graded", "u8"), ("binary", "bits"),
                                        ("binary", "u8")])
 def test_tune_variants_identical(snd, orc, mode, node):
