@@ -18,8 +18,8 @@
 //   instead of once per input, and every input costs one dword read, not two.  Only the node's sum is
 //   split into 16-bit counts, clipped and added to the levels above.  A lane needs its neighbour's dword
 //   for those moves, so 63 lanes own samples and the 64th only feeds the 63rd.  1024 channels x 4096 DMs
-//   x 102,748 samples: 4.9 ms (byte sums at level 1: 5.5); 1000 channels (a ragged tree) x 1021 DMs x
-//   32.9 k samples: 0.48 ms (1.22 on the general row-group kernel, one byte per LDS read).
+//   x 102,748 samples: 4.5 ms (byte sums at level 1: 5.5); 1000 channels (a ragged tree) x 1021 DMs x
+//   32.9 k samples: 0.47 ms (1.22 on the general row-group kernel, one byte per LDS read).
 // * Byte sums at level 1 (BYTES; regular level-1 nodes of F1 inputs, F1 m < 256): each input's four
 //   samples are aligned into one dword (v_alignbyte_b32) from the two that hold them, the F1 dwords are
 //   added as four bytes at once, and the node's sum is split into 16-bit counts for the clip.

@@ -53,7 +53,7 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
     const_ptr<uint32_t> smem_tab = as_const(s.lin_smem);
     // this lane's 16-byte unit of the tile's first sample (t0 is a multiple of the unit's
     // samples); chunk sources add their unit index
-    const uint4 *tile_src = reinterpret_cast<const uint4 *>(srcb) + (uint32_t)(t0 * ES) / 16u + lane;
+    const uint4 *tile_src = reinterpret_cast<const uint4 *>(srcb) + ((int64_t)((uint32_t)(t0 * ES) / 16u) + lane - kChunkBias);
     // Copies of batch bb into buffer j: this wave's chunks of its windows (scalar words blk), or
     // its windows one by one in the last tile; and the lane's offset words of the batch into w.
     auto issue = [&](int bb, const uint32_t (&blk)[NSM], int j, uint32_t (&w)[WPL]) {
@@ -63,9 +63,10 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
 #pragma unroll
             for (int c = 0; c < kLinMaxChunks; ++c) {
                 if (c >= nch) break;
-                const uint4 *gp = tile_src + blk[1 + c];
-                auto lp = (__attribute__((address_space(3))) void *)(buf_base + blk[1 + kLinMaxChunks + c]);
-                if (lane < (int)blk[1 + 2 * kLinMaxChunks + c]) __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 0);
+                const uint32_t cw = blk[3 + 3 * c];
+                const uint4 *gp = tile_src + (lane < (int)((cw >> 16) & 127u) ? blk[1 + 3 * c] : blk[2 + 3 * c]);
+                auto lp = (__attribute__((address_space(3))) void *)(buf_base + 16u * (cw & 0xffffu));
+                if (lane < (int)(cw >> 24)) __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 0);
             }
         } else {
             issue_batch<TI>(batches, instrs, bb, wave, lane, srcb, pitch_bytes, t0, vt,

@@ -130,7 +130,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
         for (const Stage &Q : p.stages)
             if (!Q.final_stage && Q.dst_level == S.src_level) src_pitch = Q.pitch;
         const int64_t epu = 16 / dtype_size(S.src_dtype);  // elements per 16-byte unit
-        if (src_pitch <= 0 || src_pitch % epu != 0 || (S.src_rows * src_pitch) / epu >= (int64_t(1) << 32))
+        if (src_pitch <= 0 || src_pitch % epu != 0 || (S.src_rows * src_pitch) / epu >= (int64_t(1) << 32) - kChunkBias)
             return false;
     }
     const int64_t rows = S.rows;
@@ -228,16 +228,30 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     std::vector<int32_t> slot_of(gr);
     std::vector<Src> unit_srcs;
     std::vector<int32_t> unit_nsrc, unit_slot_of, slot_lds;
-    // table kernels: copy chunks of the open batch
-    int32_t batch_chunks = 0;
-    auto lin_chunks = [&](const Src &s) {  // 64-unit copies of one window in a full tile
-        const int64_t units = ((int64_t)(s.lo % epd) + (s.hi - s.lo) + tile + epd - 1) / epd;
-        return (int32_t)((units + 63) / 64);
+    // table kernels: copy chunks of the open batch (64 units from at most two windows each)
+    struct Chunks {
+        int32_t n = 0, units = 64, windows = 2;  // chunks; units and windows of the last one
+        // units of the window of u units, starting at its unit done, that join the last chunk
+        int32_t take(int32_t u, int32_t done)
+        {
+            if (units == 64 || (done == 0 && windows == 2)) {
+                ++n;
+                units = windows = 0;
+            }
+            if (done == 0 || windows == 0) ++windows;
+            const int32_t t = std::min(u - done, 64 - units);
+            units += t;
+            return t;
+        }
     };
+    auto window_units = [&](const Src &s) {  // 16-byte units of one window in a full tile
+        return (int32_t)(((int64_t)(s.lo % epd) + (s.hi - s.lo) + tile + epd - 1) / epd);
+    };
+    Chunks batch_chunks;
     for (int64_t g = 0; g < ng; ++g) {
         int32_t e0 = 0, s0 = (int32_t)(slots.size() / 4);
         int64_t elems = 0;
-        batch_chunks = 0;
+        batch_chunks = Chunks();
         for (int32_t eu = 0; eu < ne; eu += unit) {
         // windows of every input of this unit, then one decision where the batch ends
         unit_srcs.clear();
@@ -270,11 +284,14 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
         if (need > budget || (int32_t)unit_srcs.size() > max_slots) return false;
         const int32_t nslot_batch = (int32_t)(slots.size() / 4) - s0;
         bool lin_full = false;
-        int32_t unit_chunks = 0;
+        auto add_windows = [&](Chunks c) {
+            for (const Src &s : unit_srcs)
+                for (int32_t u = window_units(s), done = 0; done < u;) done += c.take(u, done);
+            return c;
+        };
         if (tab) {  // the batch's entries or the waves' copy chunks would overflow
-            for (const Src &s : unit_srcs) unit_chunks += lin_chunks(s);
-            if (unit_chunks > kGroupRows * kLinMaxChunks) return false;
-            lin_full = batch_chunks + unit_chunks > kGroupRows * kLinMaxChunks || eu - e0 + unit > max_entries;
+            if (add_windows(Chunks()).n > kGroupRows * kLinMaxChunks) return false;
+            lin_full = add_windows(batch_chunks).n > kGroupRows * kLinMaxChunks || eu - e0 + unit > max_entries;
             if (wide_level) {  // or its parts: one for each super node that an input of it completes, one for the rest
                 int32_t parts = 1;
                 for (int32_t e = e0; e + 1 < eu + unit; ++e) parts += closes_at(e) >= wide_level;
@@ -288,9 +305,9 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
             e0 = eu;
             s0 = (int32_t)(slots.size() / 4);
             elems = 0;
-            batch_chunks = 0;
+            batch_chunks = Chunks();
         }
-        batch_chunks += unit_chunks;
+        if (tab) batch_chunks = add_windows(batch_chunks);
         size_t si0 = 0;
         for (int32_t e = eu; e < eu + unit; ++e) {
             const int32_t ns = unit_nsrc[(size_t)(e - eu)];
@@ -416,23 +433,29 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
                     sm[n_smem - 1] = (uint32_t)n;
                 }
                 // copy chunks of the batch's windows for a full tile, dealt to the waves in turn
-                int32_t j = 0;
+                Chunks c;
                 for (int32_t si = bz; si < bw; ++si) {
                     const int32_t srow = slots[4 * (size_t)si], lo = slots[4 * (size_t)si + 1];
                     const int32_t span = slots[4 * (size_t)si + 2], lofs = slots[4 * (size_t)si + 3];
-                    const int32_t head = lo % epd;
-                    const int64_t units = ((int64_t)head + span + tile + epd - 1) / epd;
-                    const int64_t unit0 = ((int64_t)srow * src_pitch + lo - head) / epd;
-                    const int64_t lds0 = (int64_t)(lofs - head) * (eb / 8);
-                    for (int64_t u0 = 0; u0 < units; u0 += 64, ++j) {
-                        const int w = j % kGroupRows, c = j / kGroupRows;
-                        if (c >= kLinMaxChunks) return false;
-                        const int64_t nu = std::min<int64_t>(64, units - u0);
+                    const int32_t head = lo % epd, units = window_units({(uint32_t)srow, lo, lo + span});
+                    const int64_t unit0 = ((int64_t)srow * src_pitch + lo - head) / epd + kChunkBias;
+                    const int64_t lds0 = (int64_t)(lofs - head) / epd;
+                    for (int32_t done = 0; done < units;) {
+                        const int32_t first = done, t = c.take(units, done);
+                        const int w = (c.n - 1) % kGroupRows, k = (c.n - 1) / kGroupRows, lane = c.units - t;
+                        done += t;
+                        if (k >= kLinMaxChunks) return false;
                         uint32_t *sm = &lin_smem[(size_t)((b * kGroupRows + w) * n_smem)];
-                        sm[0] = (uint32_t)(c + 1);
-                        sm[1 + c] = (uint32_t)(unit0 + u0);
-                        sm[1 + kLinMaxChunks + c] = (uint32_t)(lds0 + 16 * u0);
-                        sm[1 + 2 * kLinMaxChunks + c] = (uint32_t)nu;
+                        uint32_t *cw = sm + 1 + 3 * k;
+                        sm[0] = (uint32_t)(k + 1);
+                        if (lane == 0) {  // the chunk starts here: no second window yet
+                            cw[0] = cw[1] = (uint32_t)(unit0 + first);
+                            cw[2] = (uint32_t)(lds0 + first) | 64u << 16;
+                        } else {
+                            cw[1] = (uint32_t)(unit0 + first - lane);
+                            cw[2] = (cw[2] & 0xffffu) | (uint32_t)lane << 16;
+                        }
+                        cw[2] = (cw[2] & 0xffffffu) | (uint32_t)c.units << 24;
                     }
                 }
             }
@@ -889,7 +912,8 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
     for (Stage &S : p.stages) {
         if (S.final_stage) continue;
         S.ws_off = ws;
-        ws = round_up(ws + dtype_bytes(S.dst_dtype, S.rows * S.pitch), 256);
+        // (the staged kernels copy whole 16-byte units, the last up to 64 bytes past a row's end)
+        ws = round_up(ws + dtype_bytes(S.dst_dtype, S.rows * S.pitch) + 64, 256);
     }
     // a graded u8 leaf plane read by the packed final stage: one bound word per leaf workgroup
     // and the reduced one after them
