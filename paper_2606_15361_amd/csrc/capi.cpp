@@ -213,6 +213,7 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
         g.nodes = reinterpret_cast<const int32_t *>(tb + S.off_nodes);
         g.tiles = reinterpret_cast<const int32_t *>(tb + S.off_tiles);
         g.row_lo = reinterpret_cast<const int32_t *>(tb + S.off_row_lo);
+        g.leaf = reinterpret_cast<const int32_t *>(tb + S.off_leaf);
         g.depth = S.depth;
         g.k_leaf = P.desc.k_leaf;
         g.k_int = P.desc.k_int;

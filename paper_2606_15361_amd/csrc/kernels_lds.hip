@@ -129,8 +129,54 @@ __global__ __launch_bounds__(1024) void k_group(GroupArgs s0, Multi m)
     }
 }
 
+// A leaf row's sub-tile from EU inputs of u8 levels, NW dwords per lane (dword lane + 64 w): every
+// input's samples are read as the two dwords that hold them, whatever the sample they start at
+// (byte offset at[u], uniform), and the counts stay packed, clipped at the cap.  (16-bit floats
+// the same way were slower, 1.20 ms against 1.06 for the leaf stage of eight bf16 beams: their
+// pairs have to be taken apart for the FP32 sums and rounded back one by one either way.)
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+template <int EU, int NW>
+__device__ __forceinline__ void leaf_dwords(const unsigned char *lds, const uint32_t (&at)[EU], global_ptr<uint32_t> dst,
+                                            int lane, int cap, uint32_t &vmax2)
+{
+    uint32_t d[EU][NW][2];
+#pragma unroll
+    for (int u = 0; u < EU; ++u) {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(lds + (at[u] & ~3u)) + lane;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            d[u][w][0] = p[64 * w];
+            d[u][w][1] = p[64 * w + 1];
+        }
+    }
+    const uint32_t cap2 = (uint32_t)cap * 0x00010001u;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        uint32_t sum[2] = {0u, 0u};  // samples (0, 2) and (1, 3) as 16-bit counts
+#pragma unroll
+        for (int u = 0; u < EU; ++u) {
+            const uint32_t sel = 0x0c020c00u + (at[u] & 3u) * 0x00010001u;
+            sum[0] += __builtin_amdgcn_perm(d[u][w][1], d[u][w][0], sel);
+            sum[1] += __builtin_amdgcn_perm(d[u][w][1], d[u][w][0], sel + 0x00010001u);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const u16x2 y = __builtin_elementwise_min(__builtin_bit_cast(u16x2, sum[h]), __builtin_bit_cast(u16x2, cap2));
+            vmax2 = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, vmax2), y));
+            sum[h] = __builtin_bit_cast(uint32_t, y);
+        }
+        dst[64 * w] = sum[0] | sum[1] << 8;
+    }
+}
+
+// Bound by the waits of a row: a wave has few sub-tiles per row to hide the row's table reads
+// behind, and one row is not enough stores in flight.  A one-level row's table words are one
+// 32-byte record, fetched a row ahead, and 64 VGPRs let two workgroups of 16 waves share a CU.
+// With that and the packed u8 sums the leaf stage went from 1.60 to 1.35 ms (u8, 1024 channels x
+// 4096 DMs x 131,072 samples; its stores alone need 0.9), 476 to 331 us (u8, 64 channels x 3000
+// DMs), and for eight beams of 8192 samples from 0.80 to 0.73 ms (u8) and 1.18 to 1.06 (bf16).
 template <int MODE, typename TI, typename TO, int MAXD>
-__global__ __launch_bounds__(64 * kAnchorWaves) void k_anchored(AnchorArgs s0, Multi m)
+__global__ __launch_bounds__(64 * kAnchorWaves, MAXD == 1 ? 8 : 4) void k_anchored(AnchorArgs s0, Multi m)
 {
     using A = typename Acc<MODE>::type;
     AnchorArgs s;
@@ -153,7 +199,7 @@ __global__ __launch_bounds__(64 * kAnchorWaves) void k_anchored(AnchorArgs s0, M
     const int rho_max = __builtin_amdgcn_readfirstlane(nd[4]);
     // graded u8 rows: the largest value this workgroup computes, for the packed final stage
     constexpr bool kBound = MODE == SND_MODE_GRADED && std::is_same<TO, uint8_t>::value;
-    uint32_t vmax = 0;
+    uint32_t vmax = 0, vmax2 = 0;  // vmax2: of pairs of 16-bit counts
     if (tau0 >= nd[5] + s.n_run) {  // past every row of the node in this run (uniform per block)
         if (kBound && s.bound_slots && tid == 0) s.bound_slots[bid] = 0;
         return;
@@ -189,26 +235,49 @@ __global__ __launch_bounds__(64 * kAnchorWaves) void k_anchored(AnchorArgs s0, M
         }
     }
     __syncthreads();
+    // one-level rows: everything a row needs in one record, the next row's on its way while one is
+    // summed
+    constexpr bool kLeaf = MAXD == 1 && !std::is_same<TO, bits_t>::value;
+    typedef int32_t rec_t __attribute__((ext_vector_type(8)));
+    const_ptr<rec_t> leaf = as_const(reinterpret_cast<const rec_t *>(s.leaf));
+    rec_t next{};
+    if (kLeaf && r0 + wave < r1) next = leaf[r0 + wave];
     for (int r = r0 + wave; r < r1; r += kAnchorWaves) {
-        const int lo = row_lo[r], len = row_len[r] - s.len_cut;
-        const uint32_t eb = row_ptr[r], ee = row_ptr[r + 1];
-        if constexpr (MAXD == 1 && !std::is_same<TO, bits_t>::value) if (ee - eb == (uint32_t)EU) {
-            // one-level rows of EU inputs (the leaf level of clusters of four channels): table
-            // words once per row, stores without per-sample tests inside the row
+        const rec_t rec = next;
+        if (kLeaf && r + kAnchorWaves < r1) next = leaf[r + kAnchorWaves];
+        const int lo = kLeaf ? rec[0] : row_lo[r], len = (kLeaf ? rec[1] : row_len[r]) - s.len_cut;
+        const uint32_t eb = kLeaf ? (uint32_t)rec[6] : row_ptr[r], ee = kLeaf ? eb + (uint32_t)rec[7] : row_ptr[r + 1];
+        if constexpr (kLeaf) if (ee - eb == (uint32_t)EU && c1 - c0 <= 256) {
+            // rows of EU inputs (the leaf level of clusters of four channels; a record's channel
+            // field has 8 bits): stores without per-sample tests inside the row
             // rows of 1- or 2-byte elements: lane i owns the PK consecutive samples PK i + j
             // + 64 PK w (j < PK) of a sub-tile, so that each store writes a whole dword
             constexpr int PK = sizeof(TO) < 4 ? 4 / (int)sizeof(TO) : 1;
             static_assert(V % PK == 0, "whole dwords per lane");
+            constexpr bool kPacked = MODE == SND_MODE_GRADED && sizeof(TI) == 1 && sizeof(TO) == 1;
             const TI *p[EU];
 #pragma unroll
             for (int u = 0; u < EU; ++u)
-                p[u] = lds - lo + PK * lane + ((int)(ent[2 * (eb + u)] & kRowMask) - c0) * wst +
-                       (int32_t)ent[2 * (eb + u) + 1];
+                p[u] = lds + PK * lane + (int)((uint32_t)rec[2 + u] >> 24) * wst + (rec[2 + u] & (int)kRowMask);
+            uint32_t at[EU];  // byte offset of each input's first sample at the window's start
+#pragma unroll
+            for (int u = 0; u < EU; ++u)
+                at[u] = (uint32_t)((int)((uint32_t)rec[2 + u] >> 24) * wst + (rec[2 + u] & (int)kRowMask)) * (uint32_t)sizeof(TI);
             // sample slot v of the lane: offset PK lane + off(v) in the sub-tile
             auto off = [](int v) { return (v % PK) + 64 * PK * (v / PK); };
             for (int sub = 0; sub < T; sub += ST) {
                 const int i0 = tau0 + sub - lo;  // output index at the sub-tile start
                 if (i0 >= len || i0 + ST <= 0) continue;
+                if constexpr (kPacked) {
+                    // sub-tiles inside the row, on a dword (uniform): inputs as dwords
+                    auto *row = static_cast<TO *>(s.dst) + (int64_t)r * s.dst_pitch + i0;
+                    if (i0 >= 0 && i0 + ST <= len && ((uintptr_t)row & 3u) == 0) {
+                        leaf_dwords<EU, V / PK>(smem + sub, at,
+                                                    as_global(reinterpret_cast<uint32_t *>(row)) + lane, lane, s.cap,
+                                                    vmax2);
+                        continue;
+                    }
+                }
                 A val[EU][V];
 #pragma unroll
                 for (int u = 0; u < EU; ++u)
@@ -334,6 +403,7 @@ __global__ __launch_bounds__(64 * kAnchorWaves) void k_anchored(AnchorArgs s0, M
     }
     if constexpr (kBound) {
         if (s.bound_slots) {  // uniform: every thread of the block gets here
+            vmax = max(vmax, max(vmax2 & 0xffffu, vmax2 >> 16));
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) vmax = max(vmax, (uint32_t)__shfl_xor((int)vmax, o, 64));
             // the staged window's first words, once every wave is done reading it (no static LDS,

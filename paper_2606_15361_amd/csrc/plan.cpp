@@ -559,11 +559,26 @@ bool build_anchored(const PlanImpl &p, Stage &S)
     }
     S.anchor_tile = tile;
     S.kernel = kKernelAnchored;
-    S.lds_bytes = (int32_t)round_up(lds_max, 16);
+    S.lds_bytes = (int32_t)round_up(lds_max + (bits ? 0 : 4), 16);  // inputs are read as whole dwords and the next one
     S.nodes = std::move(nodes);
     S.ntiles = (int64_t)(tiles.size() / 2);
     S.tiles = std::move(tiles);
     S.row_lo.assign(D.lo.begin(), D.lo.end());
+    if (S.depth == 1 && !bits) {
+        S.leaf.assign((size_t)(8 * S.rows), 0);
+        for (const NodeSpan &n : ns)
+            for (int64_t r = n.r0; r < n.r1; ++r) {
+                int32_t *w = &S.leaf[(size_t)(8 * r)];
+                const uint32_t e0 = S.row_ptr[r], cnt = S.row_ptr[r + 1] - e0;
+                w[0] = D.lo[r];
+                w[1] = S.row_len[r];
+                for (uint32_t u = 0; u < 4 && u < cnt; ++u)  // (used by rows of exactly four inputs, in LDS windows)
+                    w[2 + u] = (int32_t)(((S.ent[e0 + u].rowc & kRowMask) - (uint32_t)n.c0) << 24 |
+                                         (uint32_t)(S.ent[e0 + u].off - D.lo[r]));
+                w[6] = (int32_t)e0;
+                w[7] = (int32_t)cnt;
+            }
+    }
     return true;
 }
 
@@ -887,6 +902,7 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
         S.off_nodes = reserve((int64_t)S.nodes.size() * 4);
         S.off_tiles = reserve((int64_t)S.tiles.size() * 4);
         S.off_row_lo = reserve((int64_t)S.row_lo.size() * 4);
+        S.off_leaf = reserve((int64_t)S.leaf.size() * 4);
     }
     p.table.assign((size_t)off, 0);
     auto put = [&](int64_t o, const void *src, size_t bytes) {
@@ -907,6 +923,7 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
         put(S.off_nodes, S.nodes.data(), S.nodes.size() * 4);
         put(S.off_tiles, S.tiles.data(), S.tiles.size() * 4);
         put(S.off_row_lo, S.row_lo.data(), S.row_lo.size() * 4);
+        put(S.off_leaf, S.leaf.data(), S.leaf.size() * 4);
     }
     int64_t ws = 0;
     for (Stage &S : p.stages) {

@@ -90,8 +90,11 @@ struct Stage {
                                     // reach of its rows past n_out
     std::vector<int32_t> tiles;     // 2 ints per workgroup: node index, window start
     std::vector<int32_t> row_lo;    // [rows]
+    // 8 ints per row of a one-level stage (not on bit rows): row_lo, row_len, inputs (channel within the
+    // node << 24 | offset past row_lo; the first four), first entry, entries
+    std::vector<int32_t> leaf;
     int32_t anchor_tile = 0;        // reference samples per workgroup window
-    int64_t off_nodes = 0, off_tiles = 0, off_row_lo = 0;
+    int64_t off_nodes = 0, off_tiles = 0, off_row_lo = 0, off_leaf = 0;
     int64_t ntiles = 0;
 };
 
@@ -327,6 +330,7 @@ struct AnchorArgs {
     const int32_t *nodes;
     const int32_t *tiles;    // 2 ints per workgroup
     const int32_t *row_lo;
+    const int32_t *leaf;     // one-level stages, not on bit rows (see Stage)
     int32_t depth;
     int32_t k_leaf, k_int, cap;
     float scale;

@@ -288,6 +288,28 @@ def test_graded_packed_wide_sums_at_the_bound(snd, orc, nchan, B, top, cap):
     assert np.array_equal(gpu_run(pg, x), y)
 
 
+@pytest.mark.parametrize("nchan,n_out,cap,top", [(64, 1, 255, 255), (64, 511, 200, 255), (64, 512, 7, 255),
+                                                 (64, 513, 255, 40), (66, 2051, 255, 63), (64, 2045, 255, 255),
+                                                 (7, 1027, 255, 255), (256, 4100, 255, 255), (600, 700, 90, 200)])
+def test_graded_leaf_rows_as_dwords(snd, orc, nchan, n_out, cap, top):
+    """Leaf rows of four u8 inputs are summed as dwords inside a row and sample by sample at its ends:
+    every byte phase of the inputs, levels up to 255 (sums past the cap and past a byte), rows shorter
+    than, equal to and just past a 512-sample sub-tile, clusters of fewer channels at a ragged end, and
+    one leaf node of 600 channels.  Bit-exact against the oracle and the generic kernels."""
+    rng, f, dms, _ = _case(nchan, 90, 41 + nchan + n_out + cap)
+    d = orc.delays(f, dms, 0.138e-3)
+    cluster = 600 if nchan == 600 else 4
+    x = rng.integers(0, top + 1, size=(nchan, int(d.max()) + n_out), dtype=np.uint8)
+    want, _ = orc.snd_dedup(x, f, d, mode="graded", cluster=cluster, branching=4, cap=cap)
+    p = snd.Plan(f, dms, 0.138e-3, x.shape[1], mode="graded", cluster=cluster, branching=4, cap=cap)
+    _say(f"leaf dwords nchan={nchan} n_out={n_out} cap={cap} {p.info['stage_kernel']}")
+    y = gpu_run(p, x)
+    assert np.array_equal(y, want.astype(y.dtype))
+    pg = snd.Plan(f, dms, 0.138e-3, x.shape[1], mode="graded", cluster=cluster, branching=4, cap=cap,
+                  generic_kernels=True)
+    assert np.array_equal(gpu_run(pg, x), y)
+
+
 @pytest.mark.parametrize("mode,node", [("float", "f32"), ("float", "bf16"), ("graded", "u8"), ("binary", "bits"),
                                        ("binary", "u8")])
 def test_tune_variants_identical(snd, orc, mode, node):
