@@ -27,7 +27,7 @@
 
 namespace snd {
 int launch_fdmt_pass(int k, const float *src, int64_t src_pitch, float *dst, int64_t dst_pitch,
-                     const int32_t *const *tabs, int64_t rows, int64_t n, void *stream);
+                     const int32_t *const *tabs, int64_t rows, int64_t ngroups, int64_t n, void *stream);
 }
 
 struct snd_fdmt_s {
@@ -36,7 +36,9 @@ struct snd_fdmt_s {
     double dm_per_delay = 0.0;
     std::vector<int64_t> rows;      // [iters]: rows of each iteration's output
     std::vector<int64_t> tab_off;   // [iters]: int32 offset of each iteration's table
-    std::vector<int32_t> tables;    // per output row: source row U, source row L, delta_U, 0
+    std::vector<int64_t> groups;    // [iters]: groups of up to kFdmtRun neighbouring rows of one sub-band
+    std::vector<int32_t> tables;    // per output row: source row U, source row L, delta_U; entry g of an
+                                    // iteration also holds the first row of its group g
     const int32_t *d_tables = nullptr;
 };
 
@@ -106,6 +108,7 @@ snd_status snd_fdmt_create(int32_t nchan, const double *freq_mhz, double chan_bw
         }
         p->tab_off.push_back((int64_t)p->tables.size());
         p->rows.push_back(rows);
+        p->groups.push_back(0);
         p->max_rows = rows > p->max_rows ? rows : p->max_rows;
         for (int32_t s = 0; s < nsb; ++s) {
             const int32_t cu = s * w, cl = s * w + h;  // first channels of the upper and lower halves
@@ -126,6 +129,11 @@ snd_status snd_fdmt_create(int32_t nchan, const double *freq_mhz, double chan_bw
                 p->tables.insert(p->tables.end(), {(int32_t)ru_row, (int32_t)rl_row, (int32_t)du, 0});
             }
         }
+        // (a sub-band's delta_U and delta_L each step by 0 or 1 from row to row, their sum by at most
+        // 1, since 0 < ru < rs: a group's sources are runs of neighbouring rows)
+        for (int32_t s = 0; s < nsb; ++s)
+            for (int64_t d = 0; d < cnt[(size_t)s]; d += snd::kFdmtRun)
+                p->tables[(size_t)(p->tab_off.back() + 4 * p->groups.back()++ + 3)] = (int32_t)(base[(size_t)s] + d);
         prev_base = std::move(base);
         prev_n = std::move(cnt);
         ++p->iters;
@@ -170,9 +178,8 @@ snd_status snd_fdmt_execute(snd_fdmt p, const float *d_in, int64_t in_pitch, flo
     const float *src = d_in;
     int64_t sp = in_pitch;
     // Every pass but the first reads a plane of delay rows and all write one, so the passes are as few
-    // as they can be: four iterations in the first (its sources are the channels themselves, which stay
-    // cached) and up to three in each further one, evenly split.
-    const int32_t passes = p->iters <= 4 ? 1 : 1 + (p->iters - 4 + 2) / 3;
+    // as they can be, the iterations evenly split.
+    const int32_t passes = (p->iters + snd::kFdmtMaxIters - 1) / snd::kFdmtMaxIters;
     int32_t done = 0;
     for (int32_t q = 0; q < passes; ++q) {
         const int32_t k = p->iters / passes + (q < p->iters % passes);
@@ -180,9 +187,10 @@ snd_status snd_fdmt_execute(snd_fdmt p, const float *d_in, int64_t in_pitch, flo
         const bool last = i == p->iters - 1;
         float *dst = last ? d_out : buf[q & 1];
         const int64_t dp = last ? out_pitch : p->nsamp;
-        const int32_t *tabs[4];
+        const int32_t *tabs[snd::kFdmtMaxIters];
         for (int32_t j = 0; j < k; ++j) tabs[j] = p->d_tables + p->tab_off[(size_t)(i - j)];
-        int e = snd::launch_fdmt_pass(k, src, sp, dst, dp, tabs, p->rows[(size_t)i], p->nsamp, stream);
+        int e = snd::launch_fdmt_pass(k, src, sp, dst, dp, tabs, p->rows[(size_t)i], p->groups[(size_t)i],
+                                      p->nsamp, stream);
         if (e) {
             snd::set_error("FDMT merge launch: " + std::string(hipGetErrorString((hipError_t)e)));
             return SND_ERR_HIP;

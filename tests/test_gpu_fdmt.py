@@ -44,7 +44,7 @@ def test_fdmt_small_exact(snd, orc, nchan, n, dm):
 
 
 @pytest.mark.parametrize("nchan", [2, 4, 8, 16, 32, 256, 512])
-@pytest.mark.parametrize("n", [255, 256, 1027])
+@pytest.mark.parametrize("n", [227, 228, 229, 255, 256, 1027])
 def test_fdmt_pass_splits_and_row_ends(snd, orc, nchan, n):
     # one to nine iterations (every split into passes), rows that end inside, at and past a tile, a DM
     # whose sweep takes most of the row (sources that run past its end), input and output rows that
