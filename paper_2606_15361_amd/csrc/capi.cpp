@@ -130,7 +130,7 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
     const int32_t len_cut = (int32_t)(P.n_out - run.n_run);
     const uint8_t *tb = static_cast<const uint8_t *>(P.d_table);
     uint8_t *ws = static_cast<uint8_t *>(d_workspace);
-    const Stage &S = P.stages[si];
+    const Stage &S = si == kDirectStage ? P.direct[0] : P.stages[si];
     Prepared pr{};
     pr.kind = S.kernel;
     pr.mode = P.desc.mode;
@@ -138,7 +138,7 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
     pr.dst_dt = S.dst_dtype;
     pr.lds = S.lds_bytes;
     StageArgs &a = pr.st;
-    if (si == 0) {
+    if (S.src_level < 0) {
         a.src = d_in;
         a.src_pitch = in_pitch;
     } else {
@@ -288,6 +288,14 @@ snd_status snd_execute(snd_plan plan, const void *d_in, int64_t in_pitch, void *
 {
     snd_status s = check_exec(plan, d_in, in_pitch, d_out, out_pitch, d_workspace, workspace_bytes);
     if (s != SND_OK) return s;
+    // its copies are whole 16-byte units of the input rows
+    const auto &P = plan->impl;
+    if (!P.direct.empty() && reinterpret_cast<uintptr_t>(d_in) % 16 == 0) {
+        const int64_t pitch_bytes = in_pitch * snd::dtype_size(P.desc.in_dtype);
+        if (pitch_bytes % 16 == 0 && pitch_bytes < (int64_t(1) << 32))
+            return snd::run_stage(plan->impl, snd::kDirectStage, snd::full_run(P), d_in, in_pitch, d_out, out_pitch,
+                                  d_workspace, stream);
+    }
     for (size_t si = 0; si < plan->impl.stages.size(); ++si) {
         s = snd::run_stage(plan->impl, si, snd::full_run(plan->impl), d_in, in_pitch, d_out, out_pitch, d_workspace,
                            stream);

@@ -220,6 +220,7 @@ struct PlanImpl {
     std::vector<int32_t> delay;  // [ndm][nchan]
     std::vector<Level> lev;
     std::vector<Stage> stages;
+    std::vector<Stage> direct;   // at most one: the whole tree from the input, for plain executions
     std::vector<uint8_t> table;  // host image of the device tables
     int64_t workspace_bytes = 0;
     // graded plans of an input-anchored leaf stage and a packed final stage: workspace offset of
@@ -244,7 +245,8 @@ struct Run {
     int64_t ring_start;
 };
 inline Run full_run(const PlanImpl &p) { return Run{p.n_out, p.nsamp, 0, 0}; }
-// Enqueue stage si of one run (defined with the C ABI).
+// Enqueue stage si of one run (defined with the C ABI); kDirectStage: the stage in PlanImpl::direct.
+constexpr size_t kDirectStage = ~size_t(0);
 snd_status run_stage(PlanImpl &P, size_t si, const Run &run, const void *d_in, int64_t in_pitch, void *d_out,
                      int64_t out_pitch, void *d_workspace, void *stream);
 // Depth classes of the kernels whose open-level stack is sized at compile time.

@@ -310,6 +310,38 @@ def test_graded_leaf_rows_as_dwords(snd, orc, nchan, n_out, cap, top):
     assert np.array_equal(gpu_run(pg, x), y)
 
 
+@pytest.mark.parametrize("mode", ["float", "graded"])
+@pytest.mark.parametrize("nchan,B,ndm,n_out", [(64, 4, 200, 512), (64, 4, 65, 513), (64, 8, 63, 511), (64, 2, 130, 1),
+                                               (16, 4, 300, 1500), (128, 2, 64, 3000), (32, 8, 1, 100)])
+def test_sparse_dms_from_the_input(snd, orc, mode, nchan, B, ndm, n_out):
+    """DMs in equal ratios hardly share leaf rows, and a plain execution then takes the whole tree from
+    the input in one stage where its rows start on 16 bytes; from any other start the leaf plane is
+    written as before.  Both, and the generic kernels, give the same bits; the oracle's sums within the
+    FP32 tolerance (exactly, graded).  Groups and tiles that are partial, whole and just past whole."""
+    rng, f, _, _ = _case(nchan, 2, 51 + ndm)
+    dms = np.geomspace(2.0, 400.0, ndm)
+    d = orc.delays(f, dms, 0.138e-3)
+    nsamp = int(d.max()) + n_out
+    x = rng.standard_normal((nchan, nsamp)).astype(np.float32) if mode == "float" else \
+        rng.integers(0, 90, (nchan, nsamp), dtype=np.uint8)
+    kw = dict(mode=mode, branching=B, cap=200)
+    want, _ = orc.snd_dedup(x, f, d, cluster=4, **kw)
+    p = snd.Plan(f, dms, 0.138e-3, nsamp, **kw)
+    _say(f"sparse DMs mode={mode} nchan={nchan} B={B} ndm={ndm} n_out={n_out} {p.info['stage_kernel']}")
+    ys = []
+    for first, pitch in ((0, (nsamp + 31) // 16 * 16), (1, (nsamp + 31) // 16 * 16), (0, nsamp | 1)):
+        block = torch.zeros(nchan * pitch + 16, dtype=torch.from_numpy(x).dtype, device="cuda")
+        view = block[first:first + nchan * pitch].view(nchan, pitch)[:, :nsamp]
+        view.copy_(torch.from_numpy(x))
+        ys.append(to_np(p.execute(view)))
+    assert np.array_equal(ys[0], ys[1]) and np.array_equal(ys[0], ys[2])
+    pg = snd.Plan(f, dms, 0.138e-3, nsamp, generic_kernels=True, **kw)
+    if mode == "graded":
+        assert np.array_equal(ys[0], want.astype(ys[0].dtype)) and np.array_equal(gpu_run(pg, x), ys[0])
+    else:
+        assert rel_rms(ys[0], want) <= FP32_TOL and rel_rms(gpu_run(pg, x), ys[0]) <= FP32_TOL
+
+
 @pytest.mark.parametrize("mode,node", [("float", "f32"), ("float", "bf16"), ("graded", "u8"), ("binary", "bits"),
                                        ("binary", "u8")])
 def test_tune_variants_identical(snd, orc, mode, node):
