@@ -28,12 +28,23 @@ __device__ inline void wait_vmcnt(int n)
 #undef SND_VM
 }
 
+// One copy instruction: 16 bytes from base + voff (base uniform) to LDS for every active lane, at lds + 16
+// lane.  A buffer load and not global_load_lds: that one counts as a flat access, after which the
+// compiler waits for all of a wave's LDS reads wherever it needs one of them.  For planes, whose rows
+// start on 16 bytes.
+__device__ __forceinline__ void copy_lds16(const unsigned char *base, uint32_t voff, unsigned char *lds)
+{
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(base), 0, -1, 0x00027000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds, 16, (int)voff, 0, 0, 0);
+}
+
 // Asynchronous copy of this wave's windows of batch b (windows wave, wave + kGroupRows, ...)
 // into the LDS buffer `dst`, straight from global memory to LDS in 16-byte units, 64 units (one
 // per lane, 1 KB) per instruction.  A window's descriptor is (source row, element offset of its
 // 16-byte aligned footprint, LDS byte offset of the footprint, head + span); for a tile of vt
 // samples it covers head + span + vt elements.  Returns the number of copy instructions issued.
-template <typename TI>
+// PLANE: by buffer loads (see copy_lds16).
+template <typename TI, bool PLANE = false>
 __device__ inline int issue_batch(const_ptr<int32_t> batches, const_ptr<int32_t> instrs, int b, int wave, int lane,
                                   const unsigned char *srcb, int64_t pitch_bytes, int t0, int vt, TI *dst)
 {
@@ -51,6 +62,12 @@ __device__ inline int issue_batch(const_ptr<int32_t> batches, const_ptr<int32_t>
             unsigned char *lp = ldsb + lbyte;
             const int nu = ((hs + vt) * ES + 15) >> 4;  // 16-byte units of the window for this tile
             int u0 = 0;
+            if constexpr (PLANE) {
+                const auto row = reinterpret_cast<const unsigned char *>(gp - lane);
+                for (; u0 < nu; u0 += 64, ++n_ins)
+                    if (u0 + lane < nu) copy_lds16(row + 16 * u0, 16u * lane, lp + 16 * u0);
+                continue;
+            }
             for (; u0 + 64 <= nu; u0 += 64) {  // whole instructions, no mask
                 __builtin_amdgcn_global_load_lds(gp + u0, (__attribute__((address_space(3))) void *)(lp + 16 * u0), 16,
                                                  0, 0);

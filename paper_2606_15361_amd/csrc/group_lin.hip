@@ -4,12 +4,18 @@
 //
 // Staging is that of the other row-group kernels: 16 waves of 1024 threads, leaf windows copied
 // global -> LDS in double-buffered batches, full tiles by 64-unit chunks listed in the plan.  Each
-// wave sums eight DM rows over a tile of 512 samples (f32 rows: 128 DM-adjacent rows share the
-// staged windows) or four rows over 1024 samples (16-bit rows: 64-row groups).  Every read is a
-// dword at o + 4 i + 256 v for an input at LDS byte offset o (lane i, v = 0 .. 7), which pairs
-// into stride-64 reads of two dwords and needs 4-byte alignment only:
-//  * f32 rows: lane i owns samples i + 64 v, one per dword, and every input takes one path.
-//  * bf16 / f16 rows: lane i owns the sample pairs (2 i + 128 v, 2 i + 1 + 128 v), one dword.
+// wave sums four DM rows (64 DM-adjacent rows share the staged windows) over a tile of 1008 (f32) or
+// 1024 samples (16-bit rows):
+//  * f32 rows: lane i owns samples 4 i .. 4 i + 3 of four blocks of 252.  An input is read as the
+//    16-byte units that hold its samples (LDS gives 16-byte reads twice the bytes per clock of
+//    4- and 8-byte ones: 121 TB/s against 67 and 71 over the chip), and where its first sample is
+//    not the first of a unit, the adds take the last ones from the next lane (a DPP operand of the
+//    add; lane 63 has no next one, hence 252).  Four variants of the adds, one per place in the unit,
+//    behind uniform branches.  Sums alone went from 8.5 to 6.7 ms at 1024 channels x 4096 DMs x
+//    102,748 samples, the kernel from 8.9 to 8.2: the copies, 46 GB from a plane of 20 GB, take 6.1 by
+//    themselves, a batch holds 2.4 inputs, and its copies start only when the batch before is done.
+//  * bf16 / f16 rows: reads are dwords at o + 4 i + 256 v for an input at LDS byte offset o (v = 0 .. 7),
+//    which pair into stride-64 reads of two.  Lane i owns the sample pairs (2 i + 128 v, 2 i + 1 + 128 v).
 //    An input whose first sample sits in the upper half of a dword takes the upper half of that
 //    dword and the lower half of the next one (a second read); the branch on that is uniform.
 //    f16 samples are added by v_fma_mix_f32 with a multiplier of 1.0 (the f16 half widened
@@ -37,7 +43,8 @@ namespace {
 // The policies below index the sums of a wave in a plain array of the pipeline (a struct
 // holding them ended up in scratch memory).
 //
-// f32 rows: st[q * V + v] is sample lane + 64 v of row q.
+// f32 rows: st[4 (q * V + v) + j] is sample 252 v + 4 lane + j of row q.  The next input's units are read
+// while one is added.
 // Interface shared with the linear 16-bit sums: output element types, words per (batch, wave),
 // the batch's inputs n (and the 16-bit dword-phase counts) as per-batch scalars; each policy
 // sets its rows per wave and tile.
@@ -58,9 +65,30 @@ struct LinBase {
 struct LinF32 : LinBase {
     using TI = float;
     static constexpr int R = lin_rows(SND_DT_F32), kRows = R, kStep = lin_tile(SND_DT_F32);
-    static constexpr int V = kStep / 64;
-    static constexpr int kState = R * V;
+    static constexpr int V = kStep / kLinBlock;
+    static constexpr int kState = R * V * 4;
+    static_assert(kLinBlock == 4 * 63 && R % 2 == 0, "the last quad of a block only feeds its neighbour; rows in twos");
 
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    // a += the samples P .. P + 3 of the lane's quad x and its neighbour's
+    template <int P>
+    static __device__ __forceinline__ void add_at(float *a, const f32x4 (&x)[V])
+    {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (j + P < 4)
+                    a[4 * v + j] += x[v][j + P];
+                else
+                    a[4 * v + j] += __int_as_float(__builtin_amdgcn_update_dpp(
+                        0, __float_as_int(x[v][j + P - 4]), 0x130, 0xf, 0xf, true));  // wave_shl:1
+            }
+        // keeps the four variants' adds apart: merged behind the branch, each operand takes a move
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            asm volatile("; phase %4" : "+v"(a[4 * v]), "+v"(a[4 * v + 1]), "+v"(a[4 * v + 2]), "+v"(a[4 * v + 3]) : "i"(P));
+    }
     // the n inputs of every row of the wave from the batch at buf; w: the lane's offset word
     static __device__ __forceinline__ void add_batch(float (&st)[kState], const unsigned char *buf,
                                                      const uint32_t (&w)[1], int lane, const Carry &c,
@@ -68,22 +96,31 @@ struct LinF32 : LinBase {
     {
         const uint32_t vw = w[0];
         const int n = c.n;
-        const unsigned char *lane_base = buf + 4 * lane;
+        const unsigned char *base = buf + 16 * lane;
+        f32x4 x[2][V];
+        uint32_t o[2];
+        auto load = [&](int u, int k) {
+            o[u] = (uint32_t)__builtin_amdgcn_readlane((int)vw, k);
+            const unsigned char *p = base + (o[u] & ~15u);
+#pragma unroll
+            for (int v = 0; v < V; ++v) x[u][v] = *reinterpret_cast<const f32x4 *>(p + 4 * kLinBlock * v);
+        };
+        load(0, 0);
         for (int i = 0; i < n; ++i) {
 #pragma unroll
-            for (int q0 = 0; q0 < R; q0 += 2) {
-                float x[2][V];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)vw, (q0 + u) * n + i);
-                    const float *p = reinterpret_cast<const float *>(lane_base + o);
-#pragma unroll
-                    for (int v = 0; v < V; ++v) x[u][v] = p[64 * v];
-                }
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < V; ++v) st[(q0 + u) * V + v] += x[u][v];
+            for (int q = 0; q < R; ++q) {
+                const int u = q & 1;
+                if (q + 1 < R) load(u ^ 1, (q + 1) * n + i);
+                else if (i + 1 < n) load(u ^ 1, i + 1);
+                float *a = &st[4 * V * q];
+                uint32_t ph = o[u] & 12u;  // (read afresh by each test: a four-way branch takes moves of the sums)
+                if (ph == 0u) add_at<0>(a, x[u]);
+                asm volatile("" : "+s"(ph));
+                if (ph == 4u) add_at<1>(a, x[u]);
+                asm volatile("" : "+s"(ph));
+                if (ph == 8u) add_at<2>(a, x[u]);
+                asm volatile("" : "+s"(ph));
+                if (ph == 12u) add_at<3>(a, x[u]);
             }
         }
     }
@@ -91,9 +128,21 @@ struct LinF32 : LinBase {
                                                  const GroupArgs &s)
     {
         auto d = as_global(drow);
+        const bool vec = (reinterpret_cast<uintptr_t>(drow) & 15u) == 0;
 #pragma unroll
-        for (int v = 0; v < V; ++v)
-            if (lane + 64 * v < vt) d[lane + 64 * v] = st[q * V + v] * s.scale;
+        for (int v = 0; v < V; ++v) {
+            const float *a = &st[4 * (V * q + v)];
+            const int t = kLinBlock * v + 4 * lane;
+            if (lane == 63 || t >= vt) continue;
+            if (vec && t + 3 < vt) {
+                *reinterpret_cast<__attribute__((address_space(1))) f32x4 *>(d + t) =
+                    f32x4{a[0] * s.scale, a[1] * s.scale, a[2] * s.scale, a[3] * s.scale};
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (t + j < vt) d[t + j] = a[j] * s.scale;
+            }
+        }
     }
 };
 

@@ -51,9 +51,9 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
     for (int i = 0; i < Sum::kState; ++i) st[i] = 0;
 
     const_ptr<uint32_t> smem_tab = as_const(s.lin_smem);
-    // this lane's 16-byte unit of the tile's first sample (t0 is a multiple of the unit's
-    // samples); chunk sources add their unit index
-    const uint4 *tile_src = reinterpret_cast<const uint4 *>(srcb) + ((int64_t)((uint32_t)(t0 * ES) / 16u) + lane - kChunkBias);
+    // the tile's first sample of the plane's first row (t0 is a multiple of a 16-byte unit's samples);
+    // chunk sources add their unit index
+    const unsigned char *tile_src = srcb + ((int64_t)t0 * ES - 16 * kChunkBias);
     // Copies of batch bb into buffer j: this wave's chunks of its windows (scalar words blk), or
     // its windows one by one in the last tile; and the lane's offset words of the batch into w.
     auto issue = [&](int bb, const uint32_t (&blk)[NSM], int j, uint32_t (&w)[WPL]) {
@@ -64,12 +64,12 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
             for (int c = 0; c < kLinMaxChunks; ++c) {
                 if (c >= nch) break;
                 const uint32_t cw = blk[3 + 3 * c];
-                const uint4 *gp = tile_src + (lane < (int)((cw >> 16) & 127u) ? blk[1 + 3 * c] : blk[2 + 3 * c]);
-                auto lp = (__attribute__((address_space(3))) void *)(buf_base + 16u * (cw & 0xffffu));
-                if (lane < (int)(cw >> 24)) __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 0);
+                const uint32_t ua = blk[1 + 3 * c], ub = blk[2 + 3 * c], u = ua < ub ? ua : ub;
+                const uint32_t at = (uint32_t)lane + (lane < (int)((cw >> 16) & 127u) ? ua - u : ub - u);
+                if (lane < (int)(cw >> 24)) copy_lds16(tile_src + 16 * (uint64_t)u, 16u * at, buf_base + 16u * (cw & 0xffffu));
             }
         } else {
-            issue_batch<TI>(batches, instrs, bb, wave, lane, srcb, pitch_bytes, t0, vt,
+            issue_batch<TI, true>(batches, instrs, bb, wave, lane, srcb, pitch_bytes, t0, vt,
                             reinterpret_cast<TI *>(buf_base));
         }
         const auto wp = as_global(s.lin + ((int64_t)bb * kGroupRows + wave) * NW + WPL * lane);
@@ -105,6 +105,7 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
             nxt = Sum::carry(blk);
         }
         const unsigned char *buf_base = smem + slot * stride;
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): no scalar loads left, so that waits for LDS reads can count
         Sum::add_batch(st, buf_base, w, lane, cur, s);
         cur = nxt;
 #pragma unroll

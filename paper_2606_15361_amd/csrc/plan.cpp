@@ -231,12 +231,15 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     // table kernels: copy chunks of the open batch (64 units from at most two windows each)
     struct Chunks {
         int32_t n = 0, units = 64, windows = 2;  // chunks; units and windows of the last one
-        // units of the window of u units, starting at its unit done, that join the last chunk
-        int32_t take(int32_t u, int32_t done)
+        int64_t first = 0;                       // its first source unit
+        // units of the window of u units at source unit src, starting at its unit done, that join the last
+        // chunk (a chunk is one copy instruction: its lanes reach 2 GiB from the lower window)
+        int32_t take(int32_t u, int32_t done, int64_t src)
         {
-            if (units == 64 || (done == 0 && windows == 2)) {
+            if (units == 64 || (done == 0 && (windows == 2 || std::abs(src - first) >= kChunkReach))) {
                 ++n;
                 units = windows = 0;
+                first = src + done;
             }
             if (done == 0 || windows == 0) ++windows;
             const int32_t t = std::min(u - done, 64 - units);
@@ -286,7 +289,8 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
         bool lin_full = false;
         auto add_windows = [&](Chunks c) {
             for (const Src &s : unit_srcs)
-                for (int32_t u = window_units(s), done = 0; done < u;) done += c.take(u, done);
+                for (int32_t u = window_units(s), done = 0; done < u;)
+                    done += c.take(u, done, ((int64_t)s.row * src_pitch + s.lo) / epd);
             return c;
         };
         if (tab) {  // the batch's entries or the waves' copy chunks would overflow
@@ -441,7 +445,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
                     const int64_t unit0 = ((int64_t)srow * src_pitch + lo - head) / epd + kChunkBias;
                     const int64_t lds0 = (int64_t)(lofs - head) / epd;
                     for (int32_t done = 0; done < units;) {
-                        const int32_t first = done, t = c.take(units, done);
+                        const int32_t first = done, t = c.take(units, done, unit0);
                         const int w = (c.n - 1) % kGroupRows, k = (c.n - 1) / kGroupRows, lane = c.units - t;
                         done += t;
                         if (k >= kLinMaxChunks) return false;

@@ -41,6 +41,7 @@ static long check_stage(const PlanImpl &P, const Stage &S)
             CHECK(sm[0] <= (uint32_t)kLinMaxChunks && (int)sm[nsm - 1] == n);
             for (uint32_t c = 0; c < sm[0]; ++c) {
                 const uint32_t cw = sm[3 + 3 * c];
+                CHECK(std::labs((long)sm[2 + 3 * c] - (long)sm[1 + 3 * c]) <= kChunkReach + 64);
                 for (uint32_t lane = 0; lane < cw >> 24; ++lane) {
                     const long src = (long)(lane < ((cw >> 16) & 127u) ? sm[1 + 3 * c] : sm[2 + 3 * c]) + lane - kChunkBias;
                     const size_t dst = (cw & 0xffffu) + lane;
@@ -94,7 +95,7 @@ static long check_stage(const PlanImpl &P, const Stage &S)
 
 int main()
 {
-    struct Shape { int nchan, ndm, branching, mode, dt; double dm_max; };
+    struct Shape { int nchan, ndm, branching, mode, dt; double dm_max; int chunk = 5000; };
     const Shape shapes[] = {
         {1024, 300, 4, SND_MODE_GRADED, SND_DT_U8, 500.0}, {1000, 70, 4, SND_MODE_GRADED, SND_DT_U8, 100.0},
         {999, 33, 8, SND_MODE_GRADED, SND_DT_U8, 60.0},    {1024, 200, 8, SND_MODE_GRADED, SND_DT_U8, 300.0},
@@ -103,6 +104,7 @@ int main()
         {5, 40, 4, SND_MODE_GRADED, SND_DT_U8, 10.0},      {1024, 300, 4, SND_MODE_FLOAT, SND_DT_F32, 500.0},
         {1000, 129, 4, SND_MODE_FLOAT, SND_DT_BF16, 200.0}, {64, 260, 2, SND_MODE_FLOAT, SND_DT_F16, 60.0},
         {37, 300, 4, SND_MODE_FLOAT, SND_DT_F32, 700.0},
+        {64, 700, 4, SND_MODE_FLOAT, SND_DT_F32, 100.0, 4000000},  // windows of one batch gigabytes apart
     };
     long windows = 0;
     int stages = 0;
@@ -121,7 +123,7 @@ int main()
         d.mode = s.mode;
         d.cap = 255;
         d.in_dtype = d.node_dtype = s.dt;
-        d.chunk = 5000;
+        d.chunk = s.chunk;
         PlanImpl P;
         std::string err;
         CHECK(build_plan(d, P, err) == SND_OK);
@@ -131,5 +133,5 @@ int main()
         ++stages;
     }
     std::printf("%d stages, %ld windows\n", stages, windows);
-    return stages >= 9 ? 0 : 1;
+    return stages >= 10 ? 0 : 1;
 }
