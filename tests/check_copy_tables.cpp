@@ -104,7 +104,7 @@ int main()
         {5, 40, 4, SND_MODE_GRADED, SND_DT_U8, 10.0},      {1024, 300, 4, SND_MODE_FLOAT, SND_DT_F32, 500.0},
         {1000, 129, 4, SND_MODE_FLOAT, SND_DT_BF16, 200.0}, {64, 260, 2, SND_MODE_FLOAT, SND_DT_F16, 60.0},
         {37, 300, 4, SND_MODE_FLOAT, SND_DT_F32, 700.0},
-        {64, 700, 4, SND_MODE_FLOAT, SND_DT_F32, 100.0, 4000000},  // windows of one batch gigabytes apart
+        {64, 1500, 4, SND_MODE_FLOAT, SND_DT_F32, 100.0, 4000000},  // windows of one batch gigabytes apart
     };
     long windows = 0;
     int stages = 0;
