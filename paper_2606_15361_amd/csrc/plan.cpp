@@ -895,19 +895,26 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
     // windows of neighbouring DMs still overlap.  64 channels, 37,628 samples, 3000 DMs in equal ratios
     // (0.54 leaf rows per node and DM): 1.94 -> 0.60 ms (f32), 0.69 -> 0.59 (graded u8).  Where the final
     // stage runs by its tables the plane pays for itself (0.05 leaf rows per node and DM at 4096 DMs in
-    // equal steps; a table sum costs a quarter of an input sum of f32 per sample, and less on u8).
-    // The line: nodes of up to four channels, no table kernel, 0.4 leaf rows, and windows that serve four
-    // DMs on average (a window per DM would copy more than the plane).  Only types whose leaf rows
-    // hold the leaf sums exactly, so the results are the same.
+    // equal steps).  The lines, both sides measured over 33 to 1500 DMs in equal ratios: nodes of up to four
+    // channels, no table kernel, 0.4 leaf rows, and windows that serve four DMs on average (a window per DM
+    // would copy more than the plane).  Up to 256 channels in f32 (256 channels, 600 DMs x 39,413 samples:
+    // 1.53 -> 1.29 ms) and 128 on u8, whose leaf rows are a quarter of the bytes (128 channels: 0.33 -> 0.27;
+    // 256: 0.51 -> 0.54).  And enough work for the chip, in units of 64 DMs x 512 samples, since a workgroup
+    // walks every channel: 40 units 66 -> 48 us (f32, 128 channels), 48 -> 43 (u8), 10 units 33 -> 45 (u8).
+    // Only types whose leaf rows hold the leaf sums exactly, so the results are the same.
     p.direct.clear();
     if (p.stages.size() == 2 && d.stage_levels == 0 && d.chunk <= 0 && d.tune == 0 && d.cluster <= 4 &&
         ((d.mode == SND_MODE_FLOAT && d.in_dtype == SND_DT_F32 && d.node_dtype == SND_DT_F32) ||
          (d.mode == SND_MODE_GRADED && d.in_dtype == SND_DT_U8 && d.node_dtype == SND_DT_U8))) {
         const Stage &A = p.stages[0], &B = p.stages[1];
+        const bool is_float = d.mode == SND_MODE_FLOAT;
+        const int64_t units = ((nd + 63) / 64) * ((p.n_out + 511) / 512);
         if (A.kernel == kKernelAnchored && B.kernel == kKernelGroupLds && !B.group_lin && !B.group_pack &&
-            5 * A.rows >= 2 * (int64_t)p.lev[0].nnodes * nd) {
+            5 * A.rows >= 2 * (int64_t)p.lev[0].nnodes * nd && nc <= (is_float ? 256 : 128) && units >= 32 &&
+            4 * units >= nc) {
             Stage S;
-            if (make_stage(-1, top, S) == SND_OK && build_group_lds(p, S, kGroupFast) && S.group_f1) {
+            if (make_stage(-1, top, S) == SND_OK &&
+                (build_group_lds(p, S, kGroupFast) || (is_float && build_group_lds(p, S, kGroupGeneric)))) {
                 int64_t staged = 0;
                 for (size_t w = 0; w < S.slots.size(); w += 4) staged += S.slots[w + 2] + S.group_tile;
                 const int64_t four = (int64_t)nc * S.group_tile * kGroupRows * S.group_rpw / 4;
