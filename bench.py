@@ -397,9 +397,9 @@ def fdmt_leg(snd, torch, spec, zt, tree_ms, reps=3):
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / reps
-    # algorithmic bytes: every merge reads two source samples and writes one per output sample,
-    # over the rows of all merges
-    alg = fd.table_rows * spec.nsamp * 12
+    # algorithmic bytes: the block read once and the delay rows written once (the rows between the
+    # iterations stay in LDS within a pass)
+    alg = (fd.nchan + fd.n_delays) * spec.nsamp * 4
     rows = fd.n_delays
     value = rows * fd.n_out / (ms * 1e-3)
     del out, fd

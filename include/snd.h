@@ -100,7 +100,8 @@ typedef struct {
     int64_t nsamp;           /* input samples per channel per execute (ignored when chunk > 0) */
     uint32_t stage_levels;   /* bit l (l below the root level) set: tree level l is written to
                                 device memory and read by the next stage.  0 = library default
-                                (leaves only); SND_STAGE_NONE = no level written (the whole tree is
+                                (leaves only; snd_execute may evaluate a sparse DM grid from the
+                                input in one stage, with the same sums); SND_STAGE_NONE = no level written (the whole tree is
                                 evaluated from the input in one stage).  The output is identical
                                 for every choice. */
     int32_t generic_kernels; /* 1: run every stage on the generic stage kernel instead of the
