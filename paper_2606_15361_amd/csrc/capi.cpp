@@ -288,11 +288,14 @@ snd_status snd_execute(snd_plan plan, const void *d_in, int64_t in_pitch, void *
 {
     snd_status s = check_exec(plan, d_in, in_pitch, d_out, out_pitch, d_workspace, workspace_bytes);
     if (s != SND_OK) return s;
-    // its copies are whole 16-byte units of the input rows
+    // the one-stage schedule copies whole 16-byte units of the input rows, and reads them while it writes
+    // the output: not for a plane that takes the input's place
     const auto &P = plan->impl;
     if (!P.direct.empty() && reinterpret_cast<uintptr_t>(d_in) % 16 == 0) {
         const int64_t pitch_bytes = in_pitch * snd::dtype_size(P.desc.in_dtype);
-        if (pitch_bytes % 16 == 0 && pitch_bytes < (int64_t(1) << 32))
+        const int64_t out_bytes = ((P.ndm - 1) * out_pitch + P.n_out) * snd::dtype_size(P.out_dtype);
+        if (pitch_bytes % 16 == 0 && pitch_bytes < (int64_t(1) << 32) &&
+            !snd::ranges_overlap(d_in, P.nchan * pitch_bytes, d_out, out_bytes))
             return snd::run_stage(plan->impl, snd::kDirectStage, snd::full_run(P), d_in, in_pitch, d_out, out_pitch,
                                   d_workspace, stream);
     }

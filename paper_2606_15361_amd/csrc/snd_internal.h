@@ -249,6 +249,12 @@ inline Run full_run(const PlanImpl &p) { return Run{p.n_out, p.nsamp, 0, 0}; }
 constexpr size_t kDirectStage = ~size_t(0);
 snd_status run_stage(PlanImpl &P, size_t si, const Run &run, const void *d_in, int64_t in_pitch, void *d_out,
                      int64_t out_pitch, void *d_workspace, void *stream);
+// Whether the byte ranges [a, a + na) and [b, b + nb) share memory.
+inline bool ranges_overlap(const void *a, int64_t na, const void *b, int64_t nb)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + (uintptr_t)nb && y < x + (uintptr_t)na;
+}
 // Depth classes of the kernels whose open-level stack is sized at compile time.
 inline int depth_bucket(int d) { return d <= 1 ? 1 : d <= 2 ? 2 : d <= 4 ? 4 : d <= 8 ? 8 : 16; }
 void set_error(const std::string &msg);

@@ -574,3 +574,31 @@ def test_config2_full_size_sampled(snd, orc, mode):
     if mode == "graded":
         row0 = to_np(y[0, :2000])
         assert np.array_equal(row0, np.minimum(x[:, :2000].astype(np.int64).sum(0), 255))
+
+
+@pytest.mark.parametrize("mode", ["float", "graded"])
+def test_sparse_dms_plane_in_place_of_the_block(snd, mode):
+    """A plane may take the memory of the block it comes from, over a sparse DM grid too, whose plain
+    execution reads the input while it writes the plane (the workspace keeps its 0xFF fill): with shared
+    memory the leaf plane is written first, as for any other grid, and the bits are the same."""
+    nchan, ndm, n_out = 64, 700, 1500
+    f = synth.channel_freqs(nchan)
+    dms = np.geomspace(2.0, 400.0, ndm)
+    nsamp = n_out + 16 * 400
+    p = snd.Plan(f, dms, 0.138e-3, nsamp, mode=mode)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    dt = p.out_dtype  # input and output rows are of one type
+    pitch = (nsamp + 63) // 64 * 64
+    x = torch.randn((nchan, pitch), device="cuda", generator=gen) if mode == "float" else \
+        torch.randint(0, 60, (nchan, pitch), dtype=torch.uint8, device="cuda", generator=gen)
+    ws = p.workspace(x.device)
+    ws.fill_(255)
+    want = p.execute(x[:, :nsamp], workspace=ws)
+    assert bool((ws == 255).all())
+    mem = torch.zeros(ndm * pitch + 2 * nchan * pitch, dtype=dt, device="cuda")
+    for at in (0, 300 * pitch + 64, ndm * pitch - 64):  # at the plane's start, inside it, across its end
+        block = mem[at:at + nchan * pitch].view(nchan, pitch)
+        block.copy_(x)
+        out = mem[:ndm * pitch].view(ndm, pitch)[:, :p.n_out]
+        p.execute(block[:, :nsamp], out=out, workspace=ws)
+        assert torch.equal(out, want)
