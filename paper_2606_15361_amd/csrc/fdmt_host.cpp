@@ -178,8 +178,13 @@ snd_status snd_fdmt_execute(snd_fdmt p, const float *d_in, int64_t in_pitch, flo
     const float *src = d_in;
     int64_t sp = in_pitch;
     // Every pass but the first reads a plane of delay rows and all write one, so the passes are as few
-    // as they can be, the iterations evenly split.
-    const int32_t passes = (p->iters + snd::kFdmtMaxIters - 1) / snd::kFdmtMaxIters;
+    // as they can be, the iterations evenly split.  An output that takes the input's memory needs a plane
+    // between the two (a single iteration has none).
+    int32_t passes = (p->iters + snd::kFdmtMaxIters - 1) / snd::kFdmtMaxIters;
+    if (passes == 1 && p->iters > 1 &&
+        snd::ranges_overlap(d_in, ((p->nchan - 1) * in_pitch + p->nsamp) * (int64_t)sizeof(float), d_out,
+                            ((p->n_delays - 1) * out_pitch + p->nsamp) * (int64_t)sizeof(float)))
+        passes = 2;
     int32_t done = 0;
     for (int32_t q = 0; q < passes; ++q) {
         const int32_t k = p->iters / passes + (q < p->iters % passes);

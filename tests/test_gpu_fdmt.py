@@ -64,6 +64,23 @@ def test_fdmt_pass_splits_and_row_ends(snd, orc, nchan, n):
         assert np.all(y[:, :3] == -7.0) and np.all(y[:, 3 + n:] == -7.0)
 
 
+@pytest.mark.parametrize("nchan", [4, 8, 32, 64])
+def test_fdmt_output_in_place_of_the_block(snd, nchan):
+    # up to 32 channels are one pass from the input to the output: with shared memory the rows go through
+    # the workspace, as they do for more channels
+    n = 3000
+    fd = snd.Fdmt(synth.channel_freqs(nchan), 16.0 / nchan, 0.138e-3, 60.0, n)
+    x = torch.from_numpy(synth.make_rng(nchan).integers(-8, 9, (nchan, n)).astype(np.float32)).cuda()
+    want = fd.execute(x)
+    mem = torch.zeros((fd.n_delays + nchan) * n, device="cuda")
+    out = mem[:fd.n_delays * n].view(fd.n_delays, n)
+    for at in (0, 5 * n + 4, fd.n_delays * n - 64):
+        block = mem[at:at + nchan * n].view(nchan, n)
+        block.copy_(x)
+        fd.execute(block, out=out)
+        assert torch.equal(out, want)
+
+
 def test_fdmt_full_size_sampled_rows(snd, orc):
     # 1024 channels x 2^17 samples up to DM 2000: sampled rows against the direct sum over the
     # channel delays traced down the split rule
