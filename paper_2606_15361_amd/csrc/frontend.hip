@@ -404,65 +404,100 @@ __global__ __launch_bounds__(64) void k_zero_dm(float *z, int64_t zp, int nchan,
 }
 
 // Windowed channel flagging by median absolute deviation, in two kernels.
-// k_chan_window_sigma: one workgroup per (channel, window of w samples): s = the population standard
-//   deviation over the window in FP64 (the mean, then the mean squared deviation).  Windows of up to
-//   kWinReg samples stay in registers between the two sums, so they are read once (two passes of one
-//   wave per window took 0.57 ms for 1024 x 131,072 in windows of 8192, this 0.19).  Writes sigma[window][channel].
+// k_chan_window_sigma: one wave per (channel, window of w samples): s = the population standard
+//   deviation over the window, each of its two FP64 sums (samples, then squared deviations from
+//   the mean) taken as 64 interleaved partial sums -- lane j sums samples j, j + 64, ... in
+//   order -- added in lane order.  Windows of up to 64 U samples stay in registers between the two
+//   sums, so they are read once, with all their loads in flight; longer ones (U = 0) are read twice.
+//   (Flagging 1024 x 131,072 samples in windows of 8192 took 0.71 ms with one load in flight, 0.18 this
+//   way; with every window past 512 read twice 0.23, and 0.89 instead of 0.70 in windows of 1000.)
+//   Writes sigma[window][channel].
 // k_flag_window: kFlagSlices workgroups per window, each finds m = the lower median of the window's
 //   s over the channels and MAD = the lower median of |s_c - m|, then takes its share of the channels:
 //   channel c is flagged when |s_c - m| > k * (kMad * MAD), kMad = 1 / Phi^-1(3/4), and its samples in
 //   the window are set to 0.  (One workgroup per window leaves most CUs idle while it zeroes: 0.17 ms, this 0.10.)
 constexpr double kFlagMadScale = 1.4826022185056018;
-constexpr int kWinQuads = 8;
-constexpr int kWinReg = 4 * 256 * kWinQuads;
 constexpr int kFlagSlices = 16;
 
-__global__ __launch_bounds__(256) void k_chan_window_sigma(const float *z, int64_t zp, int nchan, int64_t n,
-                                                           int64_t w, double *sigma)
+__device__ inline double wave_sum_in_lane_order(double v, double *lds64)
 {
-    __shared__ double sh[2][4];
-    const int c = blockIdx.x, tid = threadIdx.x;
-    const int64_t b = blockIdx.y;
-    const int64_t t0 = b * w;
-    const int64_t len = n - t0 < w ? n - t0 : w;
-    const auto row = as_global(z + (int64_t)c * zp + t0);
-    double a = 0.0, q = 0.0, none = 0.0;
-    if (len <= kWinReg) {  // uniform
-        f32x4u v[kWinQuads];
+    const int lane = threadIdx.x & 63;
+    lds64[lane] = v;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double s = 0.0;
+#pragma unroll 8
+    for (int j = 0; j < 64; ++j) s += lds64[j];
+    __builtin_amdgcn_wave_barrier();
+    return s;
+}
+
+// f(x) for the lane's samples of the window in order, from registers (v) or from memory
+template <int U, typename F>
+__device__ inline void window_fold(global_ptr<const float> row, int64_t len, const float (&v)[U > 0 ? U : 1], F &&f)
+{
+    const int lane = threadIdx.x & 63;
+    if constexpr (U > 0) {
 #pragma unroll
-        for (int u = 0; u < kWinQuads; ++u) {
-            const int t = 4 * (tid + 256 * u);
-            v[u] = f32x4u{0.0f, 0.0f, 0.0f, 0.0f};
-            if (t + 4 <= len) v[u] = load4(row + t);
-            else
+        for (int u0 = 0; u0 < U; u0 += 8) {
+            if (64 * (u0 + 8) <= len) {  // uniform
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (t + j < len) v[u][j] = row[t + j];
-        }
+                for (int u = u0; u < u0 + 8; ++u) f(v[u]);
+            } else if (64 * u0 < len) {
 #pragma unroll
-        for (int u = 0; u < kWinQuads; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a += (double)v[u][j];
-        block_sum2<256>(a, none, sh);
-        const double mu = a / (double)len;
-#pragma unroll
-        for (int u = 0; u < kWinQuads; ++u) {
-            if (1024 * u >= len) break;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double d = (double)v[u][j] - mu;
-                if (4 * (tid + 256 * u) + j < len) q += d * d;
+                for (int u = u0; u < u0 + 8; ++u)
+                    if (lane + 64 * u < len) f(v[u]);
             }
         }
     } else {
-        for (int64_t t = tid; t < len; t += 256) a += (double)row[t];
-        block_sum2<256>(a, none, sh);
-        const double mu = a / (double)len;
-        for (int64_t t = tid; t < len; t += 256) q += ((double)row[t] - mu) * ((double)row[t] - mu);
+        int64_t t = lane;
+        for (; t + 64 * 31 < len; t += 64 * 32) {
+            float x[32];
+#pragma unroll
+            for (int u = 0; u < 32; ++u) x[u] = row[t + 64 * u];
+#pragma unroll
+            for (int u = 0; u < 32; ++u) f(x[u]);
+        }
+        for (; t < len; t += 64) f(row[t]);
     }
-    none = 0.0;
-    block_sum2<256>(q, none, sh);
-    if (tid == 0) sigma[b * nchan + c] = __builtin_sqrt(q / (double)len);
+}
+
+template <int U>
+__global__ __launch_bounds__(256) void k_chan_window_sigma(const float *z, int64_t zp, int nchan, int64_t n,
+                                                           int64_t w, double *sigma)
+{
+    __shared__ double part[4][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int c = blockIdx.x * 4 + wave;
+    const int64_t b = blockIdx.y;
+    if (c >= nchan) return;  // whole waves
+    const int64_t t0 = b * w;
+    const int64_t len = n - t0 < w ? n - t0 : w;
+    const auto row = as_global(z + (int64_t)c * zp + t0);
+    float v[U > 0 ? U : 1];
+    if constexpr (U > 0) {
+#pragma unroll
+        for (int u0 = 0; u0 < U; u0 += 8) {
+            if (64 * (u0 + 8) <= len) {  // uniform
+#pragma unroll
+                for (int u = u0; u < u0 + 8; ++u) v[u] = row[lane + 64 * u];
+            } else if (64 * u0 < len) {
+#pragma unroll
+                for (int u = u0; u < u0 + 8; ++u) v[u] = lane + 64 * u < len ? row[lane + 64 * u] : 0.0f;
+            }
+        }
+    }
+    double a = 0.0;
+    window_fold<U>(row, len, v, [&](float x) { a += (double)x; });
+    const double mu = wave_sum_in_lane_order(a, part[wave]) / (double)len;
+    double q = 0.0;
+    window_fold<U>(row, len, v, [&](float x) {
+        const double d = (double)x - mu;
+        q += d * d;
+    });
+    const double qs = wave_sum_in_lane_order(q, part[wave]);
+    if (lane == 0) sigma[b * nchan + c] = __builtin_sqrt(qs / (double)len);
 }
 
 // The value of rank r (0-based, increasing) among the non-negative v[0..n) in LDS: the largest of the
@@ -597,8 +632,10 @@ int launch_flag_channels(float *z, int64_t zp, int nchan, int64_t n, int64_t w, 
                          uint8_t *flags, int64_t fp, void *stream)
 {
     const uint32_t nwin = blocks(n, w);
-    hipLaunchKernelGGL(k_chan_window_sigma, dim3((uint32_t)nchan, nwin), dim3(256), 0, (hipStream_t)stream, z, zp, nchan,
-                       n, w, sigma);
+    const auto sigmas = w <= 512 ? k_chan_window_sigma<8> : w <= 2048 ? k_chan_window_sigma<32>
+                        : w <= 8192 ? k_chan_window_sigma<128> : k_chan_window_sigma<0>;
+    hipLaunchKernelGGL(sigmas, dim3(blocks(nchan, 4), nwin), dim3(256), 0, (hipStream_t)stream, z, zp, nchan, n, w,
+                       sigma);
     hipLaunchKernelGGL(k_flag_window, dim3(nwin, (uint32_t)(nchan < kFlagSlices ? nchan : kFlagSlices)), dim3(1024),
                        (size_t)nchan * sizeof(double), (hipStream_t)stream, z, zp, nchan, n, w, k, sigma, flags, fp);
     return (int)hipGetLastError();

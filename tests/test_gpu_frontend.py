@@ -132,3 +132,41 @@ def test_row_ends_and_unaligned_rows(snd, orc, nchan, n):
             y = ft.clone()
             snd.zero_dm(y, gamma)
             assert np.array_equal(y.cpu().numpy(), orc.zero_dm(fin, gamma)[0])
+
+
+@pytest.mark.parametrize("nchan,n,window", [(5, 1000, 1), (130, 700, 63), (9, 1300, 64), (64, 2000, 100), (1100, 900, 257),
+                                            (3, 4099, 512), (66, 5000, 513), (5, 9000, 2048), (6, 20000, 2049),
+                                            (3, 17000, 8191), (65, 16384, 8192), (3, 30000, 8193), (2, 70001, 30000)])
+def test_flagging_sums_in_the_stated_order(snd, orc, nchan, n, window):
+    """The window sigmas are those of 64 interleaved FP64 partial sums, partial j over samples j, j + 64, ...
+    in order, added in order of j, to the last bit: windows shorter and longer than a wave, around the sizes
+    a wave holds in registers and past them, on rows that start on any element; and the oracle's flags."""
+    z = synth.make_rng(nchan + n + window).standard_normal((nchan, n + 1)).astype(np.float32) * 3.0
+    z[0, n // 2] = 1e6
+    z = z[:, 1:]
+    block = torch.zeros((nchan, n + 3), device="cuda")
+    zt = block[:, 1:1 + n]
+    zt.copy_(torch.from_numpy(z))
+    flags, sig = snd.flag_channels(zt, window, k=4.0, return_sigma=True)
+
+    def ordered(v):  # [nchan][samples] float64
+        part = np.zeros((nchan, 64))
+        for i in range(0, v.shape[1], 64):
+            part[:, :v[:, i:i + 64].shape[1]] += v[:, i:i + 64]
+        s = np.zeros(nchan)
+        for j in range(64):
+            s = s + part[:, j]
+        return s
+
+    got = sig.cpu().numpy()
+    for b in range(got.shape[0]):
+        x = z[:, b * window:(b + 1) * window].astype(np.float64)
+        d = x - (ordered(x) / x.shape[1])[:, None]
+        assert np.array_equal(got[b], np.sqrt(ordered(d * d) / x.shape[1])), b
+    want_z, want_f = orc.flag_channels(np.ascontiguousarray(z), window, k=4.0)
+    ok = np.all(_flag_threshold_margin(got, 4.0) > 1e-9, axis=1)  # windows with no channel on the threshold
+    assert np.array_equal(flags.cpu().numpy()[ok], want_f[ok])
+    y = zt.cpu().numpy()
+    for b in np.flatnonzero(ok):
+        assert np.array_equal(y[:, b * window:(b + 1) * window], want_z[:, b * window:(b + 1) * window])
+    assert not block[:, 0].any() and not block[:, 1 + n:].any()
