@@ -412,12 +412,15 @@ __global__ __launch_bounds__(64) void k_zero_dm(float *z, int64_t zp, int nchan,
 //   (Flagging 1024 x 131,072 samples in windows of 8192 took 0.71 ms with one load in flight, 0.18 this
 //   way; with every window past 512 read twice 0.23, and 0.89 instead of 0.70 in windows of 1000.)
 //   Writes sigma[window][channel].
-// k_flag_window: kFlagSlices workgroups per window, each finds m = the lower median of the window's
-//   s over the channels and MAD = the lower median of |s_c - m|, then takes its share of the channels:
-//   channel c is flagged when |s_c - m| > k * (kMad * MAD), kMad = 1 / Phi^-1(3/4), and its samples in
-//   the window are set to 0.  (One workgroup per window leaves most CUs idle while it zeroes: 0.17 ms, this 0.10.)
+// k_flag_window: each workgroup of a window finds m = the lower median of the window's s over the
+//   channels and MAD = the lower median of |s_c - m|, then takes its share of the channels: channel c is
+//   flagged when |s_c - m| > k * (kMad * MAD), kMad = 1 / Phi^-1(3/4), and its samples in the window are
+//   set to 0.  Few windows take several workgroups each (one leaves most CUs idle while it zeroes: 0.17 ms
+//   for 16 windows of 1024 channels, with sixteen 0.10), up to kFlagBlocks in all, one on each CU; since
+//   each repeats the medians, more windows than that take one (512 windows of 256 samples: 4.3 ms
+//   with sixteen each, 0.50).
 constexpr double kFlagMadScale = 1.4826022185056018;
-constexpr int kFlagSlices = 16;
+constexpr uint32_t kFlagSlices = 16, kFlagBlocks = 256;
 
 __device__ inline double wave_sum_in_lane_order(double v, double *lds64)
 {
@@ -636,8 +639,11 @@ int launch_flag_channels(float *z, int64_t zp, int nchan, int64_t n, int64_t w, 
                         : w <= 8192 ? k_chan_window_sigma<128> : k_chan_window_sigma<0>;
     hipLaunchKernelGGL(sigmas, dim3(blocks(nchan, 4), nwin), dim3(256), 0, (hipStream_t)stream, z, zp, nchan, n, w,
                        sigma);
-    hipLaunchKernelGGL(k_flag_window, dim3(nwin, (uint32_t)(nchan < kFlagSlices ? nchan : kFlagSlices)), dim3(1024),
-                       (size_t)nchan * sizeof(double), (hipStream_t)stream, z, zp, nchan, n, w, k, sigma, flags, fp);
+    uint32_t slices = kFlagBlocks / nwin;
+    slices = slices < 1 ? 1 : slices > kFlagSlices ? kFlagSlices : slices;
+    if (slices > (uint32_t)nchan) slices = (uint32_t)nchan;
+    hipLaunchKernelGGL(k_flag_window, dim3(nwin, slices), dim3(1024), (size_t)nchan * sizeof(double),
+                       (hipStream_t)stream, z, zp, nchan, n, w, k, sigma, flags, fp);
     return (int)hipGetLastError();
 }
 

@@ -170,3 +170,22 @@ def test_flagging_sums_in_the_stated_order(snd, orc, nchan, n, window):
     for b in np.flatnonzero(ok):
         assert np.array_equal(y[:, b * window:(b + 1) * window], want_z[:, b * window:(b + 1) * window])
     assert not block[:, 0].any() and not block[:, 1 + n:].any()
+
+
+@pytest.mark.parametrize("nchan,n,window", [(300, 3000, 10), (257, 2001, 20), (40, 700, 5), (1000, 5003, 39), (5, 60, 20)])
+def test_flagging_many_short_windows(snd, orc, nchan, n, window):
+    """Windows that share their channels among several workgroups or take one each, with hot and dead
+    channels at the ends of the shares: the oracle's flags and zeroed samples."""
+    z = synth.make_rng(nchan * n + window).standard_normal((nchan, n)).astype(np.float32)
+    z[0] *= 40.0
+    z[-1] = 0.0
+    z[nchan // 2, : n // 2] *= 25.0
+    zt = torch.from_numpy(z).cuda()
+    flags = snd.flag_channels(zt, window, k=6.0).cpu().numpy()
+    want_z, want_f, sig = orc.flag_channels(z, window, k=6.0, return_sigma=True)
+    ok = np.all(_flag_threshold_margin(sig, 6.0) > 1e-9, axis=1)
+    assert ok.any() and want_f[ok].any()
+    assert np.array_equal(flags[ok], want_f[ok])
+    y = zt.cpu().numpy()
+    for b in np.flatnonzero(ok):
+        assert np.array_equal(y[:, b * window:(b + 1) * window], want_z[:, b * window:(b + 1) * window])
