@@ -279,6 +279,26 @@ snd_status run_stage(PlanImpl &P, size_t si, const Run &run, const void *d_in, i
     return s;
 }
 
+snd_status run_block(PlanImpl &P, const void *d_in, int64_t in_pitch, void *d_out, int64_t out_pitch,
+                     void *d_workspace, void *stream)
+{
+    const Run run = full_run(P);
+    // the one-stage schedule copies whole 16-byte units of the input rows, and reads them while it writes
+    // the output: not for a plane that takes the input's place
+    if (!P.direct.empty() && reinterpret_cast<uintptr_t>(d_in) % 16 == 0) {
+        const int64_t pitch_bytes = in_pitch * dtype_size(P.desc.in_dtype);
+        const int64_t out_bytes = ((P.ndm - 1) * out_pitch + P.n_out) * dtype_size(P.out_dtype);
+        if (pitch_bytes % 16 == 0 && pitch_bytes < (int64_t(1) << 32) &&
+            !ranges_overlap(d_in, P.nchan * pitch_bytes, d_out, out_bytes))
+            return run_stage(P, kDirectStage, run, d_in, in_pitch, d_out, out_pitch, d_workspace, stream);
+    }
+    for (size_t si = 0; si < P.stages.size(); ++si) {
+        const snd_status s = run_stage(P, si, run, d_in, in_pitch, d_out, out_pitch, d_workspace, stream);
+        if (s != SND_OK) return s;
+    }
+    return SND_OK;
+}
+
 }  // namespace snd
 
 extern "C" {
@@ -288,23 +308,7 @@ snd_status snd_execute(snd_plan plan, const void *d_in, int64_t in_pitch, void *
 {
     snd_status s = check_exec(plan, d_in, in_pitch, d_out, out_pitch, d_workspace, workspace_bytes);
     if (s != SND_OK) return s;
-    // the one-stage schedule copies whole 16-byte units of the input rows, and reads them while it writes
-    // the output: not for a plane that takes the input's place
-    const auto &P = plan->impl;
-    if (!P.direct.empty() && reinterpret_cast<uintptr_t>(d_in) % 16 == 0) {
-        const int64_t pitch_bytes = in_pitch * snd::dtype_size(P.desc.in_dtype);
-        const int64_t out_bytes = ((P.ndm - 1) * out_pitch + P.n_out) * snd::dtype_size(P.out_dtype);
-        if (pitch_bytes % 16 == 0 && pitch_bytes < (int64_t(1) << 32) &&
-            !snd::ranges_overlap(d_in, P.nchan * pitch_bytes, d_out, out_bytes))
-            return snd::run_stage(plan->impl, snd::kDirectStage, snd::full_run(P), d_in, in_pitch, d_out, out_pitch,
-                                  d_workspace, stream);
-    }
-    for (size_t si = 0; si < plan->impl.stages.size(); ++si) {
-        s = snd::run_stage(plan->impl, si, snd::full_run(plan->impl), d_in, in_pitch, d_out, out_pitch, d_workspace,
-                           stream);
-        if (s != SND_OK) return s;
-    }
-    return SND_OK;
+    return snd::run_block(plan->impl, d_in, in_pitch, d_out, out_pitch, d_workspace, stream);
 }
 
 snd_status snd_execute_stage(snd_plan plan, int32_t stage, const void *d_in, int64_t in_pitch, void *d_out,

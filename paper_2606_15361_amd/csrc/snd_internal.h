@@ -249,6 +249,10 @@ inline Run full_run(const PlanImpl &p) { return Run{p.n_out, p.nsamp, 0, 0}; }
 constexpr size_t kDirectStage = ~size_t(0);
 snd_status run_stage(PlanImpl &P, size_t si, const Run &run, const void *d_in, int64_t in_pitch, void *d_out,
                      int64_t out_pitch, void *d_workspace, void *stream);
+// Enqueue a plain execution of the whole block (snd_execute past its argument checks): the stage in
+// PlanImpl::direct where there is one and the buffers allow it, else the stages in order.
+snd_status run_block(PlanImpl &P, const void *d_in, int64_t in_pitch, void *d_out, int64_t out_pitch,
+                     void *d_workspace, void *stream);
 // Whether the byte ranges [a, a + na) and [b, b + nb) share memory.
 inline bool ranges_overlap(const void *a, int64_t na, const void *b, int64_t nb)
 {

@@ -17,11 +17,12 @@ snd_status tfail(snd_status s, const std::string &msg)
     return s;
 }
 
-// One pass of plan P over the block: a single run, or runs of P.n_out output samples at
-// increasing time offsets until n_total outputs are written.
+// One pass of plan P over the block: a single run, as snd_execute makes it, or runs of P.n_out output
+// samples at increasing time offsets until n_total outputs are written.
 snd_status pass(snd::PlanImpl &P, int64_t n_total, const uint8_t *in, int64_t in_pitch, int64_t in_es, uint8_t *out,
                 int64_t out_pitch, int64_t out_es, void *ws, hipStream_t st)
 {
+    if (P.n_out == n_total) return snd::run_block(P, in, in_pitch, out, out_pitch, ws, st);
     for (int64_t t = 0; t < n_total; t += P.n_out) {
         const int64_t n = std::min<int64_t>(P.n_out, n_total - t);
         const snd::Run run{n, P.max_delay + n, 0, 0};

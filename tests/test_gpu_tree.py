@@ -602,3 +602,37 @@ def test_sparse_dms_plane_in_place_of_the_block(snd, mode):
         out = mem[:ndm * pitch].view(ndm, pitch)[:, :p.n_out]
         p.execute(block[:, :nsamp], out=out, workspace=ws)
         assert torch.equal(out, want)
+
+
+def test_tuner_times_the_schedule_that_executes(snd):
+    """Over a sparse DM grid a plain execution of the default schedule takes the whole tree from the
+    input, and so does the tuner's timing of that candidate (its workspace keeps the 0xFF fill); from rows
+    that do not start on 16 bytes both write the leaf plane.  A candidate with a tune word is timed on its
+    own stages."""
+    import ctypes as C
+    from paper_2606_15361_amd import _capi as capi
+    from paper_2606_15361_amd.plan import make_desc
+    nchan, ndm = 64, 700
+    f, dms = synth.channel_freqs(nchan), np.geomspace(2.0, 400.0, ndm)
+    nsamp = 8000
+    d, _f, _d, _, _ = make_desc(f, dms, 0.138e-3, nsamp, mode="float")
+    block = torch.randn((nchan, nsamp + 8), device="cuda")
+    for tune, first, in_one in ((0, 0, True), (0, 1, False), (16, 0, False)):
+        p = snd.Plan(f, dms, 0.138e-3, nsamp, mode="float", tune=tune)
+        x = block[:, first:first + nsamp]
+        ws = torch.full_like(p.workspace(x.device), 255)
+        tables = torch.empty(p.info["table_bytes"], dtype=torch.uint8, device="cuda")
+        want = p.execute(x, workspace=ws)
+        assert bool((ws == 255).all()) == in_one
+        ws.fill_(255)
+        out = torch.zeros_like(want)
+        cand, best = (capi.TuneCandidate * 1)(), C.c_int32(-1)
+        cand[0].tune = tune
+        capi.check(capi.lib().snd_autotune(C.byref(d), cand, 1, C.c_void_p(x.data_ptr()), x.stride(0),
+                                           C.c_void_p(out.data_ptr()), out.stride(0), C.c_void_p(ws.data_ptr()),
+                                           ws.numel(), C.c_void_p(tables.data_ptr()), tables.numel(), 2,
+                                           C.byref(best), None))
+        torch.cuda.synchronize()
+        assert best.value == 0 and cand[0].ms > 0
+        assert bool((ws == 255).all()) == in_one
+        assert torch.equal(out, want)
