@@ -901,6 +901,11 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
     // 1.53 -> 1.29 ms) and 128 on u8, whose leaf rows are a quarter of the bytes (128 channels: 0.33 -> 0.27;
     // 256: 0.51 -> 0.54).  And enough work for the chip, in units of 64 DMs x 512 samples, since a workgroup
     // walks every channel: 40 units 66 -> 48 us (f32, 128 channels), 48 -> 43 (u8), 10 units 33 -> 45 (u8).
+    // On the general row-group kernel (irregular nodes, or windows too large for the specialised one) only in
+    // float, and from 64 channels on only where the tree does not grow past the four open levels that the
+    // final stage gets by with (600 DMs x 30,000 samples: 128 channels by fours 541 -> 373 us, by twos, deeper
+    // either way, 683 -> 635, by threes 542 -> 624; 64 channels by twos 322 -> 327, 37 by twos 220 -> 206).
+    // On u8 rows it reads one byte at a time: 128 channels by twos 206 -> 481 us, 100 302 -> 386, 37 106 -> 160.
     // Only types whose leaf rows hold the leaf sums exactly, so the results are the same.
     p.direct.clear();
     if (p.stages.size() == 2 && d.stage_levels == 0 && d.chunk <= 0 && d.tune == 0 && d.cluster <= 4 &&
@@ -914,7 +919,8 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
             4 * units >= nc) {
             Stage S;
             if (make_stage(-1, top, S) == SND_OK &&
-                (build_group_lds(p, S, kGroupFast) || (is_float && build_group_lds(p, S, kGroupGeneric)))) {
+                (build_group_lds(p, S, kGroupFast) || (is_float && build_group_lds(p, S, kGroupGeneric))) &&
+                (S.group_f1 > 0 || (is_float && (S.depth <= 4 || B.depth > 4 || nc < 64)))) {
                 int64_t staged = 0;
                 for (size_t w = 0; w < S.slots.size(); w += 4) staged += S.slots[w + 2] + S.group_tile;
                 const int64_t four = (int64_t)nc * S.group_tile * kGroupRows * S.group_rpw / 4;
