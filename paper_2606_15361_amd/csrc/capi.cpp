@@ -130,7 +130,7 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
     const int32_t len_cut = (int32_t)(P.n_out - run.n_run);
     const uint8_t *tb = static_cast<const uint8_t *>(P.d_table);
     uint8_t *ws = static_cast<uint8_t *>(d_workspace);
-    const Stage &S = si == kDirectStage ? P.direct[0] : P.stages[si];
+    const Stage &S = si == kDirectStage ? P.direct[0] : si == kAloneStage ? P.alone[0] : P.stages[si];
     Prepared pr{};
     pr.kind = S.kernel;
     pr.mode = P.desc.mode;
@@ -142,7 +142,7 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
         a.src = d_in;
         a.src_pitch = in_pitch;
     } else {
-        const Stage &Q = P.stages[si - 1];
+        const Stage &Q = P.stages[(S.final_stage ? P.stages.size() - 1 : si) - 1];
         a.src = ws + Q.ws_off;
         a.src_pitch = Q.pitch;
     }
@@ -273,7 +273,9 @@ snd_status run_stage(PlanImpl &P, size_t si, const Run &run, const void *d_in, i
     static const char *kStageNames[] = {"snd stage 0", "snd stage 1", "snd stage 2", "snd stage 3",
                                         "snd stage 4", "snd stage 5", "snd stage 6", "snd stage 7"};
     roctxRangePushA(si < 8 ? kStageNames[si] : "snd stage");
-    const Prepared pr = prepare_stage(P, si, run, d_in, in_pitch, d_out, out_pitch, d_workspace, true);
+    const bool alone = !P.alone.empty();  // (that final stage reads no bound)
+    if (alone && si + 1 == P.stages.size()) si = kAloneStage;
+    const Prepared pr = prepare_stage(P, si, run, d_in, in_pitch, d_out, out_pitch, d_workspace, !alone);
     const snd_status s = launch_prepared(pr, stream, Multi{nullptr, nullptr, 0}, 0);
     roctxRangePop();
     return s;

@@ -209,6 +209,8 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return p.dm[a] < p.dm[b]; });
     const int64_t ng = (rows + gr - 1) / gr;
+    if (pack && f1 == 0 && p.desc.chunk <= 0 && ng * ((p.n_out + tile_step - 1) / tile_step) < kPackAnyBlocks)
+        return false;
     std::vector<int32_t> grp_rows((size_t)(ng * gr), -1);
     for (int64_t i = 0; i < rows; ++i) grp_rows[(size_t)i] = order[(size_t)i];
     std::vector<int32_t> batch_ptr(1, 0), batches, slots;
@@ -873,12 +875,20 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
     }
 
     // ---------------- kernel choice per stage ----------------
+    p.alone.clear();
     for (Stage &S : p.stages) {
         S.kernel = kKernelGeneric;
         if (d.generic_kernels) continue;
         if (S.final_stage && (build_group_lds(p, S, kGroupLin) || build_group_lds(p, S, kGroupPack) ||
-                              build_group_lds(p, S, kGroupFast) || (!bits && build_group_lds(p, S, kGroupGeneric))))
+                              build_group_lds(p, S, kGroupFast) || (!bits && build_group_lds(p, S, kGroupGeneric)))) {
+            if (d.chunk > 0 && S.group_pack && S.group_f1 == 0 &&
+                S.ngroups * ((p.n_out + S.group_tile - 1) / S.group_tile) < kPackAnyBlocks) {
+                Stage A = S;
+                if (build_group_lds(p, A, kGroupFast) || build_group_lds(p, A, kGroupGeneric))
+                    p.alone.push_back(std::move(A));
+            }
             continue;
+        }
         if (!S.final_stage && S.src_level < 0 && !build_anchored(p, S) && (d.tune & 15u)) {
             err = "the requested leaf-stage window does not fit the LDS";
             return SND_ERR_UNSUPPORTED;
@@ -934,6 +944,7 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
     std::vector<Stage *> in_table;
     for (Stage &S : p.stages) in_table.push_back(&S);
     for (Stage &S : p.direct) in_table.push_back(&S);
+    for (Stage &S : p.alone) in_table.push_back(&S);
     int64_t off = 0;
     auto reserve = [&](int64_t bytes) {
         int64_t o = off;

@@ -168,6 +168,13 @@ constexpr int kPackMaxParts = 8;
 constexpr int pack_rows(int f1, int depth) { return f1 == 0 || (f1 == 4 && depth <= 4) ? 2 : 4; }
 constexpr int pack_tile(int f1, int depth) { return pack_rows(f1, depth) == 2 ? kPackWideTile : 512; }
 constexpr int kPackReach = 1024 + 16;          // samples a two-row window holds beyond its span
+// Irregular nodes take the packed kernel only in launches of at least this many workgroups, about half
+// the CUs: its groups are twice as wide and its tiles four times as long as the general row-group
+// kernel's, which leaves CUs idle on smaller grids.  (Streaming plans below that keep both: a push of
+// several beams shares one grid.)  Final stage of 1000 channels: 100 DMs x 9042 samples (36
+// workgroups) 84 us on the general kernel, 185 packed; 64 DMs x 30,014 (60) 99 and 155; 300 x 9042 (90)
+// 142 and 150; 100 x 30,042 (120) 188 and 186; 600 x 9042 (171) 233 and 138.
+constexpr int64_t kPackAnyBlocks = 128;
 constexpr int kPackRowsMax = 4;
 constexpr int kPackMaxBatchEntries = 64;
 constexpr int kPackWords = 256;                // offset words per (batch, wave)
@@ -221,6 +228,8 @@ struct PlanImpl {
     std::vector<Level> lev;
     std::vector<Stage> stages;
     std::vector<Stage> direct;   // at most one: the whole tree from the input, for plain executions
+    std::vector<Stage> alone;    // at most one: the final stage for launches of this plan alone, where
+                                 // stages.back() is for grids shared by several beams (kPackAnyBlocks)
     std::vector<uint8_t> table;  // host image of the device tables
     int64_t workspace_bytes = 0;
     // graded plans of an input-anchored leaf stage and a packed final stage: workspace offset of
@@ -245,8 +254,9 @@ struct Run {
     int64_t ring_start;
 };
 inline Run full_run(const PlanImpl &p) { return Run{p.n_out, p.nsamp, 0, 0}; }
-// Enqueue stage si of one run (defined with the C ABI); kDirectStage: the stage in PlanImpl::direct.
-constexpr size_t kDirectStage = ~size_t(0);
+// Enqueue stage si of one run (defined with the C ABI), the final one from PlanImpl::alone where there is
+// one; kDirectStage: the stage in PlanImpl::direct.
+constexpr size_t kDirectStage = ~size_t(0), kAloneStage = kDirectStage - 1;
 snd_status run_stage(PlanImpl &P, size_t si, const Run &run, const void *d_in, int64_t in_pitch, void *d_out,
                      int64_t out_pitch, void *d_workspace, void *stream);
 // Enqueue a plain execution of the whole block (snd_execute past its argument checks): the stage in

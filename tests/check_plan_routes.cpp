@@ -12,6 +12,7 @@ struct Shape {
     int mode, dt, nchan, branching, ndm;
     double dm_lo, dm_max;  // equal ratios from dm_lo > 0, else equal steps from 0
     int64_t n_out;
+    bool chunk = false;
 };
 
 static PlanImpl plan_of(const Shape &s)
@@ -35,7 +36,8 @@ static PlanImpl plan_of(const Shape &s)
     d.k_int = 1;
     d.cap = 255;
     d.in_dtype = d.node_dtype = s.dt;
-    d.nsamp = s.n_out + (int64_t)(14.3 * s.dm_max);
+    if (s.chunk) d.chunk = (int32_t)s.n_out;
+    else d.nsamp = s.n_out + (int64_t)(14.3 * s.dm_max);
     PlanImpl P;
     std::string err;
     if (build_plan(d, P, err) != SND_OK) {
@@ -75,5 +77,16 @@ int main()
     EXPECT(P.direct.empty(), F, F32, 64, 2, 600, 2.0, 800.0, 30000);
     // grids that share their leaf rows keep the leaf plane
     EXPECT(P.direct.empty(), F, F32, 64, 4, 600, 0.0, 100.0, 30000);
+    // irregular nodes: the packed kernel where its workgroups fill half the chip; streaming plans below that
+    // hold both, for pushes alone and in shared grids
+    EXPECT(!P.stages[1].group_pack && P.alone.empty(), G, U8, 1000, 4, 20, 0.0, 100.0, 9000);
+    EXPECT(!P.stages[1].group_pack && P.alone.empty(), G, U8, 1000, 4, 300, 0.0, 300.0, 9000);
+    EXPECT(!P.stages[1].group_pack && P.alone.empty(), G, U8, 300, 3, 600, 0.0, 300.0, 2500);
+    EXPECT(P.stages[1].group_pack && P.alone.empty(), G, U8, 1000, 4, 600, 0.0, 300.0, 9000);
+    EXPECT(P.stages[1].group_pack && P.alone.empty(), G, U8, 100, 4, 200, 0.0, 300.0, 30000);
+    EXPECT(P.stages[1].group_pack && P.alone.size() == 1 && !P.alone[0].group_pack, G, U8, 1000, 4, 300, 0.0, 300.0,
+           8192, true);
+    EXPECT(P.stages[1].group_pack && P.alone.empty(), G, U8, 1000, 4, 1000, 0.0, 300.0, 8192, true);
+    EXPECT(P.stages[1].group_pack && P.alone.empty(), G, U8, 1024, 4, 20, 0.0, 100.0, 8192, true);
     return bad;
 }

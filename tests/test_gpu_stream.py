@@ -339,3 +339,44 @@ def test_stream_bit_input_any_chunks(snd, orc):
     tail = np.concatenate(yc, axis=1)
     assert np.array_equal(tail, plain[:, plain.shape[1] - tail.shape[1]:])
     assert a.state(0) == dict(received=total, next_chunk=len(lengths), emitted=total - plan.max_delay)
+
+
+def test_ragged_graded_beams_alone_and_batched(snd, orc):
+    """Graded beams over irregular trees: a beam's push alone runs its small final stage on the general
+    kernel, a batched push on the packed one with each beam's own bound.  Chunks shorter than, equal to and
+    ragged against the plan's, history fill included, levels within the byte sums' bound and past it: both
+    equal the oracle on the whole block, bit for bit."""
+    beams = [(250, 4, 120, 1500, 3, 255), (97, 3, 300, 2100, 7, 255), (250, 4, 64, 1500, 40, 200),
+             (500, 8, 90, 1009, 4, 90), (64, 4, 100, 1500, 4, 255)]  # the last one regular
+    plans, srcs, wants = [], [], []
+    for i, (nchan, B, ndm, chunk, top, cap) in enumerate(beams):
+        f, dms = synth.channel_freqs(nchan), np.linspace(0.0, 60.0, ndm)
+        plans.append(snd.Plan(f, dms, 0.138e-3, None, mode="graded", branching=B, cap=cap, chunk=chunk))
+        x = synth.random_levels(synth.make_rng(900 + i), nchan, 6000, top)
+        srcs.append(torch.from_numpy(np.ascontiguousarray(x)).cuda())
+        wants.append(orc.snd_dedup(x, f, orc.delays(f, dms, 0.138e-3), mode="graded", cluster=4, branching=B,
+                                   cap=cap)[0])
+    for batched in (False, True):
+        st = snd.Stream(1 << 34)
+        for i, p in enumerate(plans):
+            st.admit(i, p)
+        ws = torch.full((max(p.info["workspace_bytes"] for p in plans),), 255, dtype=torch.uint8, device="cuda")
+        pos, idx, rows = [0] * len(beams), [0] * len(beams), [[] for _ in beams]
+        rng = synth.make_rng(31)
+        while any(q < 6000 for q in pos):
+            items = []
+            for i, p in enumerate(plans):
+                L = min(p.n_out, 6000 - pos[i], int(rng.choice([p.n_out, 1008, 700, 253, 1])))
+                if L > 0:
+                    items.append((i, idx[i], srcs[i][:, pos[i]:pos[i] + L], p.empty_output("cuda")))
+                    pos[i] += L
+                    idx[i] += 1
+            got = st.push(items, batched=True) if batched else st.push(items, workspace=ws)
+            torch.cuda.synchronize()
+            for (i, _, _, out), (_, n, status) in zip(items, got):
+                assert status == 0
+                rows[i].append(to_np(out[:, :n]))
+        for i, p in enumerate(plans):
+            y = np.concatenate(rows[i], axis=1)
+            assert y.shape[1] == 6000 - p.max_delay
+            assert np.array_equal(y, wants[i][:, :y.shape[1]].astype(y.dtype)), (batched, i)

@@ -636,3 +636,33 @@ def test_tuner_times_the_schedule_that_executes(snd):
         assert best.value == 0 and cand[0].ms > 0
         assert bool((ws == 255).all()) == in_one
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("nchan,B,top,cap", [
+    (250, 4, 15, 255), (250, 4, 16, 255), (999, 4, 15, 255), (999, 4, 40, 200),  # ragged levels, both paths
+    (97, 3, 28, 255), (97, 3, 29, 255),                # super nodes of nine inputs
+    (203, 5, 30, 255), (500, 8, 31, 90), (500, 8, 32, 255), (255, 16, 15, 255), (255, 16, 17, 255),
+    (5, 4, 60, 255), (3, 4, 60, 40), (17, 2, 40, 255),  # trees of one to four levels
+])
+def test_graded_ragged_packed_grid(snd, orc, nchan, B, top, cap):
+    """Irregular nodes take the packed kernel only in grids that fill half the chip: 470 DMs over nine
+    tiles and a partial one, with leaves at the bound of its byte sums and past it, as in the bound test
+    above; and in a run of its own of the same tree's small grid, which takes the general kernel, the same
+    rows.  Bit-exact against the oracle."""
+    rng, f, _, _ = _case(nchan, 2, 61 + nchan + B + top)
+    dms = np.linspace(0.0, 40.0, 470)
+    d = orc.delays(f, dms, 0.138e-3)
+    nsamp = int(d.max()) + 9 * 1008 + 253
+    x = synth.random_levels(rng, nchan, nsamp, max(1, min(top // 4, 4)))
+    q, r = divmod(top, 4)
+    for c in range(min(nchan // 4 * 4, 64)):
+        x[c, 50:nsamp - 50] = q + (1 if c % 4 < r else 0)
+    want, _ = orc.snd_dedup(x, f, d, mode="graded", cluster=4, branching=B, cap=cap)
+    xt = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    for step in (1, 9):
+        p = snd.Plan(f, dms[::step], 0.138e-3, nsamp, mode="graded", branching=B, cap=cap)
+        _say(f"ragged packed grid nchan={nchan} B={B} top={top} cap={cap} ndm={p.ndm} n_out={p.n_out}")
+        ws = p.workspace(xt.device)
+        ws.fill_(255)
+        y = to_np(p.execute(xt, workspace=ws))
+        assert np.array_equal(y[:, :want.shape[1]], want[::step].astype(y.dtype))
