@@ -135,9 +135,10 @@ __global__ __launch_bounds__(1024) void k_group(GroupArgs s0, Multi m)
 // the same way were slower, 1.20 ms against 1.06 for the leaf stage of eight bf16 beams: their
 // pairs have to be taken apart for the FP32 sums and rounded back one by one either way.)
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-template <int EU, int NW>
+// EDGE: the sub-tile's sample i0 is the row's first or earlier, or its last lies past the row's len.
+template <int EU, int NW, bool EDGE>
 __device__ __forceinline__ void leaf_dwords(const unsigned char *lds, const uint32_t (&at)[EU], global_ptr<uint32_t> dst,
-                                            int lane, int cap, uint32_t &vmax2)
+                                            int lane, int cap, int i0, int len, uint32_t &vmax2)
 {
     uint32_t d[EU][NW][2];
 #pragma unroll
@@ -165,7 +166,16 @@ __device__ __forceinline__ void leaf_dwords(const unsigned char *lds, const uint
             vmax2 = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, vmax2), y));
             sum[h] = __builtin_bit_cast(uint32_t, y);
         }
-        dst[64 * w] = sum[0] | sum[1] << 8;
+        const uint32_t word = sum[0] | sum[1] << 8;
+        const int i = i0 + 4 * (lane + 64 * w);
+        if (!EDGE || (i >= 0 && i + 4 <= len)) {
+            dst[64 * w] = word;
+        } else {
+            const auto d = reinterpret_cast<global_ptr<uint8_t>>(dst + 64 * w);
+#pragma unroll 1
+            for (int b = 0; b < 4; ++b)
+                if (i + b >= 0 && i + b < len) d[b] = (uint8_t)(word >> (8 * b));
+        }
     }
 }
 
@@ -174,7 +184,7 @@ __device__ __forceinline__ void leaf_dwords(const unsigned char *lds, const uint
 // 32-byte record, fetched a row ahead, and 64 VGPRs let two workgroups of 16 waves share a CU.
 // With that and the packed u8 sums the leaf stage went from 1.60 to 1.35 ms (u8, 1024 channels x
 // 4096 DMs x 131,072 samples; its stores alone need 0.9), 476 to 331 us (u8, 64 channels x 3000
-// DMs), and for eight beams of 8192 samples from 0.80 to 0.73 ms (u8) and 1.18 to 1.06 (bf16).
+// DMs; row ends by the same dwords: 100 channels, 600 rows of 580 samples 38 us, one by one 40, now 36), and for eight beams of 8192 samples from 0.80 to 0.73 ms (u8) and 1.18 to 1.06 (bf16).
 template <int MODE, typename TI, typename TO, int MAXD>
 __global__ __launch_bounds__(64 * kAnchorWaves, MAXD == 1 ? 8 : 4) void k_anchored(AnchorArgs s0, Multi m)
 {
@@ -269,14 +279,15 @@ __global__ __launch_bounds__(64 * kAnchorWaves, MAXD == 1 ? 8 : 4) void k_anchor
                 const int i0 = tau0 + sub - lo;  // output index at the sub-tile start
                 if (i0 >= len || i0 + ST <= 0) continue;
                 if constexpr (kPacked) {
-                    // sub-tiles inside the row, on a dword (uniform): inputs as dwords
+                    // inputs as dwords; every sub-tile starts on one, since leaf rows' anchors and pitch
+                    // are multiples of 64 samples
                     auto *row = static_cast<TO *>(s.dst) + (int64_t)r * s.dst_pitch + i0;
-                    if (i0 >= 0 && i0 + ST <= len && ((uintptr_t)row & 3u) == 0) {
-                        leaf_dwords<EU, V / PK>(smem + sub, at,
-                                                    as_global(reinterpret_cast<uint32_t *>(row)) + lane, lane, s.cap,
-                                                    vmax2);
-                        continue;
-                    }
+                    const auto d = as_global(reinterpret_cast<uint32_t *>(row)) + lane;
+                    if (i0 >= 0 && i0 + ST <= len)
+                        leaf_dwords<EU, V / PK, false>(smem + sub, at, d, lane, s.cap, i0, len, vmax2);
+                    else
+                        leaf_dwords<EU, V / PK, true>(smem + sub, at, d, lane, s.cap, i0, len, vmax2);
+                    continue;
                 }
                 A val[EU][V];
 #pragma unroll
