@@ -209,8 +209,9 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return p.dm[a] < p.dm[b]; });
     const int64_t ng = (rows + gr - 1) / gr;
-    if (pack && f1 == 0 && p.desc.chunk <= 0 && ng * ((p.n_out + tile_step - 1) / tile_step) < kPackAnyBlocks)
-        return false;
+    const bool small = pack && ng * ((p.n_out + tile_step - 1) / tile_step) < kPackMinBlocks;
+    bool idle = small && f1 == 0;
+    if (idle && p.desc.chunk <= 0) return false;
     std::vector<int32_t> grp_rows((size_t)(ng * gr), -1);
     for (int64_t i = 0; i < rows; ++i) grp_rows[(size_t)i] = order[(size_t)i];
     std::vector<int32_t> batch_ptr(1, 0), batches, slots;
@@ -287,6 +288,8 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
         int64_t need = 0;
         for (const Src &s : unit_srcs) need += slot_elems(s.lo, s.hi - s.lo);
         if (need > budget || (int32_t)unit_srcs.size() > max_slots) return false;
+        idle = idle || (small && need > kPackRoom);
+        if (idle && p.desc.chunk <= 0) return false;
         const int32_t nslot_batch = (int32_t)(slots.size() / 4) - s0;
         bool lin_full = false;
         auto add_windows = [&](Chunks c) {
@@ -482,6 +485,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     S.wide_level = wide_level;
     S.wide_inputs = wide_inputs;
     S.wide_sub = wide_sub;
+    S.pack_idle = idle;
     const int64_t buf_bytes = round_up(max_elems * eb / 8, 16);
     S.lds_buf_elems = (int32_t)(buf_bytes * 8 / eb);
     // general kernel: batches b+1, b+2 land while b is read; the others: b+1
@@ -881,8 +885,7 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
         if (d.generic_kernels) continue;
         if (S.final_stage && (build_group_lds(p, S, kGroupLin) || build_group_lds(p, S, kGroupPack) ||
                               build_group_lds(p, S, kGroupFast) || (!bits && build_group_lds(p, S, kGroupGeneric)))) {
-            if (d.chunk > 0 && S.group_pack && S.group_f1 == 0 &&
-                S.ngroups * ((p.n_out + S.group_tile - 1) / S.group_tile) < kPackAnyBlocks) {
+            if (S.pack_idle) {
                 Stage A = S;
                 if (build_group_lds(p, A, kGroupFast) || build_group_lds(p, A, kGroupGeneric))
                     p.alone.push_back(std::move(A));

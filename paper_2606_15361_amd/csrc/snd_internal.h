@@ -80,6 +80,7 @@ struct Stage {
     // packed kernel, two-row shapes: the super nodes' level and largest number of inputs, and that of
     // the nodes one level below
     int32_t wide_level = 0, wide_inputs = 0, wide_sub = 0;
+    bool pack_idle = false;  // packed kernel, in a launch of its own: fewer workgroups than it pays for
     std::vector<uint32_t> lin;
     std::vector<uint32_t> lin_smem;
     int64_t off_grp_rows = 0, off_batch_ptr = 0, off_batches = 0, off_instrs = 0, off_ldsb = 0;
@@ -168,13 +169,16 @@ constexpr int kPackMaxParts = 8;
 constexpr int pack_rows(int f1, int depth) { return f1 == 0 || (f1 == 4 && depth <= 4) ? 2 : 4; }
 constexpr int pack_tile(int f1, int depth) { return pack_rows(f1, depth) == 2 ? kPackWideTile : 512; }
 constexpr int kPackReach = 1024 + 16;          // samples a two-row window holds beyond its span
-// Irregular nodes take the packed kernel only in launches of at least this many workgroups, about half
-// the CUs: its groups are twice as wide and its tiles four times as long as the general row-group
-// kernel's, which leaves CUs idle on smaller grids.  (Streaming plans below that keep both: a push of
-// several beams shares one grid.)  Final stage of 1000 channels: 100 DMs x 9042 samples (36
-// workgroups) 84 us on the general kernel, 185 packed; 64 DMs x 30,014 (60) 99 and 155; 300 x 9042 (90)
-// 142 and 150; 100 x 30,042 (120) 188 and 186; 600 x 9042 (171) 233 and 138.
-constexpr int64_t kPackAnyBlocks = 128;
+// Irregular nodes, and regular ones whose windows nearly fill a buffer (more than kPackRoom bytes for one
+// node: a batch is then one node), take the packed kernel only in launches of at least this many
+// workgroups, about half the CUs: its groups are wider and its tiles longer than the other row-group
+// kernels', which leaves CUs idle on smaller grids.  (Streaming plans below that keep both: a push of
+// several beams shares one grid.)  Final stage of 1000 channels, against the general kernel: 100 DMs x 9042
+// samples (36 workgroups) 84 us, packed 185; 64 DMs x 30,014 (60) 99 and 155; 300 x 9042 (90) 142 and 150;
+// 100 x 30,042 (120) 188 and 186; 600 x 9042 (171) 233 and 138.  Of 256 channels, regular, DMs 1.3 apart,
+// against the specialised kernel: 600 x 2640 (57) 40 and 51; 200 x 30,047 (210) 76 and 52.
+constexpr int kPackRoom = 59 * 1024;
+constexpr int64_t kPackMinBlocks = 128;
 constexpr int kPackRowsMax = 4;
 constexpr int kPackMaxBatchEntries = 64;
 constexpr int kPackWords = 256;                // offset words per (batch, wave)
@@ -229,7 +233,7 @@ struct PlanImpl {
     std::vector<Stage> stages;
     std::vector<Stage> direct;   // at most one: the whole tree from the input, for plain executions
     std::vector<Stage> alone;    // at most one: the final stage for launches of this plan alone, where
-                                 // stages.back() is for grids shared by several beams (kPackAnyBlocks)
+                                 // stages.back() is for grids shared by several beams (kPackMinBlocks)
     std::vector<uint8_t> table;  // host image of the device tables
     int64_t workspace_bytes = 0;
     // graded plans of an input-anchored leaf stage and a packed final stage: workspace offset of

@@ -88,5 +88,13 @@ int main()
            8192, true);
     EXPECT(P.stages[1].group_pack && P.alone.empty(), G, U8, 1000, 4, 1000, 0.0, 300.0, 8192, true);
     EXPECT(P.stages[1].group_pack && P.alone.empty(), G, U8, 1024, 4, 20, 0.0, 100.0, 8192, true);
+    // regular nodes whose windows nearly fill a buffer, likewise
+    EXPECT(P.stages[1].group_pack, G, U8, 256, 4, 600, 0.0, 300.0, 2640);
+    EXPECT(!P.stages[1].group_pack && P.stages[1].group_f1 == 4, G, U8, 256, 4, 600, 0.0, 780.0, 2640);
+    EXPECT(!P.stages[1].group_pack && P.stages[1].group_f1 == 4, G, U8, 256, 4, 16, 0.0, 100.0, 9018);
+    EXPECT(!P.stages[1].group_pack && P.stages[1].group_f1 == 4, G, U8, 64, 4, 300, 0.0, 100.0, 535);
+    EXPECT(P.stages[1].group_pack && P.alone.empty(), G, U8, 256, 4, 600, 0.0, 780.0, 9000);
+    EXPECT(P.stages[1].group_pack && P.alone.size() == 1 && P.alone[0].group_f1 == 4, G, U8, 256, 4, 600, 0.0, 780.0,
+           2640, true);
     return bad;
 }

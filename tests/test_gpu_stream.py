@@ -347,7 +347,7 @@ def test_ragged_graded_beams_alone_and_batched(snd, orc):
     ragged against the plan's, history fill included, levels within the byte sums' bound and past it: both
     equal the oracle on the whole block, bit for bit."""
     beams = [(250, 4, 120, 1500, 3, 255), (97, 3, 300, 2100, 7, 255), (250, 4, 64, 1500, 40, 200),
-             (500, 8, 90, 1009, 4, 90), (64, 4, 100, 1500, 4, 255)]  # the last one regular
+             (500, 8, 90, 1009, 4, 90), (64, 4, 100, 1500, 4, 255), (256, 4, 46, 1500, 4, 255)]  # two regular ones
     plans, srcs, wants = [], [], []
     for i, (nchan, B, ndm, chunk, top, cap) in enumerate(beams):
         f, dms = synth.channel_freqs(nchan), np.linspace(0.0, 60.0, ndm)
