@@ -62,10 +62,11 @@ struct LinBase {
     }
 };
 
+// V: blocks of a tile (four, or two in short tiles).
+template <int V>
 struct LinF32 : LinBase {
     using TI = float;
-    static constexpr int R = lin_rows(SND_DT_F32), kRows = R, kStep = lin_tile(SND_DT_F32);
-    static constexpr int V = kStep / kLinBlock;
+    static constexpr int R = lin_rows(SND_DT_F32), kRows = R, kStep = V * kLinBlock;
     static constexpr int kState = R * V * 4;
     static_assert(kLinBlock == 4 * 63 && R % 2 == 0, "the last quad of a block only feeds its neighbour; rows in twos");
 
@@ -346,7 +347,9 @@ int launch_group_lin(int src_dt, const GroupArgs &a, int64_t n_out, int lds, voi
                      int64_t nblocks)
 {
     switch (src_dt) {
-    case SND_DT_F32: return launch_lin<LinF32>(a, n_out, lds, stream, m, nblocks);
+    case SND_DT_F32:
+        if (a.lin_kernel == 3) return launch_lin<LinF32<kLinShortTile / kLinBlock>>(a, n_out, lds, stream, m, nblocks);
+        return launch_lin<LinF32<lin_tile(SND_DT_F32) / kLinBlock>>(a, n_out, lds, stream, m, nblocks);
     case SND_DT_BF16: return launch_lin<Lin16<false>>(a, n_out, lds, stream, m, nblocks);
     case SND_DT_F16: return launch_lin<Lin16<true>>(a, n_out, lds, stream, m, nblocks);
     default: return (int)hipErrorInvalidValue;

@@ -183,12 +183,14 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     if (bits && !f1) return false;  // bit rows: specialised kernel only
     // samples a window holds beyond its span (its tile, plus one unit for the linear kernel on
     // 16-bit rows), and the tile step in time
-    const int tile = lin    ? lin_cover(S.src_dtype)
+    const bool lin_short = lin && S.src_dtype == SND_DT_F32 && rows <= kGroupRows * lin_rows(S.src_dtype) &&
+                           (p.n_out + lin_tile(S.src_dtype) - 1) / lin_tile(S.src_dtype) < kLinMinBlocks;
+    const int tile = lin    ? (lin_short ? kLinShortTile + 4 : lin_cover(S.src_dtype))
                      : pack ? (pack_rows(f1, S.depth) == 2 ? kPackReach : pack_tile(f1, S.depth) + 16)
                      : bits ? kGroupTileBits
                      : f1   ? kGroupTileFast
                             : kGroupTile;
-    const int tile_step = lin ? lin_tile(S.src_dtype) : pack ? pack_tile(f1, S.depth) : tile;
+    const int tile_step = lin ? (lin_short ? kLinShortTile : lin_tile(S.src_dtype)) : pack ? pack_tile(f1, S.depth) : tile;
     const int rpw = lin ? lin_rows(S.src_dtype) : pack ? pack_rows(f1, S.depth) : f1 ? kFastRows : 1;  // rows per wave
     const int max_entries = lin ? lin_max_batch_entries(S.src_dtype) : kPackMaxBatchEntries;  // table kernels
     const int n_words = lin ? kLinWords : kPackWords;
@@ -481,6 +483,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     S.group_tile = tile_step;
     S.group_rpw = rpw;
     S.group_lin = lin;
+    S.lin_short = lin_short;
     S.group_pack = pack;
     S.wide_level = wide_level;
     S.wide_inputs = wide_inputs;

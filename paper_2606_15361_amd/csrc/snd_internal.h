@@ -76,6 +76,7 @@ struct Stage {
     // row's inputs that start a dword (4 bits per row), and last n.  The packed kernel keeps its
     // tables (kPackWords and kPackSmemWords per batch and wave) in the same two vectors.
     bool group_lin = false;
+    bool lin_short = false;  // tiles of kLinShortTile
     bool group_pack = false;
     // packed kernel, two-row shapes: the super nodes' level and largest number of inputs, and that of
     // the nodes one level below
@@ -125,6 +126,11 @@ constexpr int kGroupTileBits = 2048;  // bit rows: 32 samples (one word) per lan
 // that starts in the upper half of a dword reads one dword past the tile, so those windows stage one
 // 16-byte unit more.
 constexpr int kLinBlock = 4 * 63;
+// f32 rows of one group take tiles of two blocks where four would give fewer workgroups than half the CUs
+// (final stage of 1024 channels, 24 DMs x 30,014 samples: 391 us in tiles of four, 243 of two; 64 x 2514
+// 369 and 268; 300 channels, 16 x 9017: 122 and 81).
+constexpr int kLinShortTile = 2 * kLinBlock;
+constexpr int64_t kLinMinBlocks = 128;
 constexpr int lin_rows(int) { return 4; }
 constexpr int lin_tile(int src_dtype) { return src_dtype == SND_DT_F32 ? 4 * kLinBlock : 1024; }
 inline int lin_cover(int src_dtype) { return src_dtype == SND_DT_F32 ? lin_tile(src_dtype) + 4 : lin_tile(src_dtype) + 8; }
@@ -327,7 +333,7 @@ struct GroupArgs {
     const int32_t *node_closes;  // specialised kernel only
     const uint32_t *lin_smem;    // linear kernel only
     const uint32_t *lin;
-    int32_t lin_kernel;          // 1: linear kernel, 2: packed kernel
+    int32_t lin_kernel;          // 1: linear kernel, 2: packed kernel, 3: linear kernel, short tiles
     int32_t xcd_chunk;           // DM groups of one time tile dealt to each XCD in turn
     int32_t ngroups;
     int32_t n_entries;
@@ -396,11 +402,11 @@ int launch_ring_put_bits(const uint32_t *chunk, int64_t chunk_words, uint32_t *r
 
 // Compile-time shape of the kernel instance that runs stage S: the depth class, or, for the
 // specialised row-group kernel, 1000 * (inputs per level-1 node) + depth; -1 for the linear
-// kernel; minus the specialised shape for the packed kernel (irregular nodes: its depth and the
+// kernel, -2 with short tiles; minus the specialised shape for the packed kernel (irregular nodes: its depth and the
 // levels above its super nodes).
 inline int stage_shape(const Stage &S)
 {
-    if (S.kernel == kKernelGroupLds && S.group_lin) return -1;
+    if (S.kernel == kKernelGroupLds && S.group_lin) return S.lin_short ? -2 : -1;
     if (S.kernel == kKernelGroupLds && S.group_pack)
         return -(S.group_f1 ? 1000 * S.group_f1 + S.depth : 16000 + 10 * (S.depth - S.wide_level) + S.depth);
     if (S.kernel == kKernelGroupLds && S.group_f1 > 0) return 1000 * S.group_f1 + S.depth;

@@ -666,3 +666,31 @@ def test_graded_ragged_packed_grid(snd, orc, nchan, B, top, cap):
         ws.fill_(255)
         y = to_np(p.execute(xt, workspace=ws))
         assert np.array_equal(y[:, :want.shape[1]], want[::step].astype(y.dtype))
+
+
+@pytest.mark.parametrize("n_out", [1, 503, 504, 505, 1008, 1009, 2600])
+def test_float_rows_of_few_dms_in_short_tiles(snd, orc, n_out):
+    """Up to 64 DMs of f32 rows take tiles of 504 samples: the same bits as the 1008-sample tiles that one
+    DM more brings, on output rows that start on any element, and the oracle's sums of integer samples
+    exactly."""
+    nchan = 96
+    f = synth.channel_freqs(nchan)
+    dms = np.sort(synth.make_rng(n_out).uniform(0.0, 3.0, 65))
+    d = orc.delays(f, dms, 0.138e-3)
+    nsamp = int(d.max()) + n_out
+    rng = synth.make_rng(n_out + 1)
+    for x in (rng.standard_normal((nchan, nsamp)).astype(np.float32), rng.integers(-9, 10, (nchan, nsamp)).astype(np.float32)):
+        xt = torch.from_numpy(x).cuda()
+        p = snd.Plan(f, dms, 0.138e-3, nsamp)
+        assert p.info["stage_kernel"] == ["anchored", "group_lin"] and p.n_out == n_out
+        long = to_np(p.execute(xt))
+        for drop in (1, 40, 64):  # leading DMs left out: the last one, of the largest delay, stays
+            q = snd.Plan(f, dms[drop:], 0.138e-3, nsamp)
+            assert q.info["stage_kernel"] == ["anchored", "group_lin"] and q.n_out == n_out
+            out = torch.full((q.ndm, n_out + 5), -3.0, device="cuda")
+            q.execute(xt, out=out[:, 3:3 + n_out])
+            y = out.cpu().numpy()
+            assert np.array_equal(y[:, 3:3 + n_out], long[drop:])
+            assert np.all(y[:, :3] == -3.0) and np.all(y[:, 3 + n_out:] == -3.0)
+    want, _ = orc.snd_dedup(x, f, d, mode="float", cluster=4, branching=4)
+    assert np.array_equal(long, want.astype(np.float32))
