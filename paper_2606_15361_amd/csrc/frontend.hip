@@ -262,26 +262,27 @@ __device__ inline void block_sum2(double &a, double &b, double (*sh)[T / 64])
 
 // Sigma-clip statistics of one channel per workgroup: a first FP64 pass about the channel's
 // first sample gives mu0 and sigma0, a second pass the same statistics of the clipped values
-// (about the clip range's centre, mu0).  Two workgroups of 16 waves fill a CU, four 16-byte loads
+// (about the clip range's centre, mu0).  Two workgroups of T = 1024 threads fill a CU, four 16-byte loads
 // per lane in flight (256 threads with one 4-byte load each took 0.53 ms for 1024 x 131,072,
-// this 0.18).
-constexpr int kStatThreads = 1024;
-template <typename F>
+// this 0.18).  Shorter rows take T = 256 (up to 16,384 samples) or one wave (up to 1024), since all of a
+// large workgroup's threads take part in its sums: 4096 x 1000 samples 64 us by 1024, 12 by 256, 8 by 64;
+// 4096 x 8200 85 by 1024, 39 by 256.
+template <int T, typename F>
 __device__ inline void stat_fold(global_ptr<const float> row, int64_t n, F &&f)
 {
     const int tid = threadIdx.x;
     const int64_t nv = n / 4;
     int64_t i = tid;
-    for (; i + 3 * kStatThreads < nv; i += 4 * kStatThreads) {
+    for (; i + 3 * T < nv; i += 4 * T) {
         f32x4u v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = load4(row + 4 * (i + u * kStatThreads));
+        for (int u = 0; u < 4; ++u) v[u] = load4(row + 4 * (i + u * T));
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) f(v[u][j]);
     }
-    for (; i < nv; i += kStatThreads) {
+    for (; i < nv; i += T) {
         const f32x4u v = load4(row + 4 * i);
 #pragma unroll
         for (int j = 0; j < 4; ++j) f(v[j]);
@@ -289,20 +290,21 @@ __device__ inline void stat_fold(global_ptr<const float> row, int64_t n, F &&f)
     if (4 * nv + tid < n) f(row[4 * nv + tid]);
 }
 
-__global__ __launch_bounds__(kStatThreads) void k_chanstats(const float *p, int64_t pp, int64_t n, double clip,
+template <int T>
+__global__ __launch_bounds__(T) void k_chanstats(const float *p, int64_t pp, int64_t n, double clip,
                                                             double *stats)
 {
-    __shared__ double sh[2][kStatThreads / 64];
+    __shared__ double sh[2][T / 64];
     const int c = blockIdx.x;
     const auto row = as_global(p + (int64_t)c * pp);
     const double shift = (double)row[0];
     double a = 0.0, b = 0.0;
-    stat_fold(row, n, [&](float x) {
+    stat_fold<T>(row, n, [&](float x) {
         const double d = (double)x - shift;
         a += d;
         b += d * d;
     });
-    block_sum2<kStatThreads>(a, b, sh);
+    block_sum2<T>(a, b, sh);
     const double dn = (double)n;
     const double m1 = a / dn;
     const double mu0 = shift + m1;
@@ -311,14 +313,14 @@ __global__ __launch_bounds__(kStatThreads) void k_chanstats(const float *p, int6
     const double lo = mu0 - clip * s0, hi = mu0 + clip * s0;
     a = 0.0;
     b = 0.0;
-    stat_fold(row, n, [&](float x) {
+    stat_fold<T>(row, n, [&](float x) {
         double v = (double)x;
         v = v < lo ? lo : (v > hi ? hi : v);
         const double d = v - mu0;
         a += d;
         b += d * d;
     });
-    block_sum2<kStatThreads>(a, b, sh);
+    block_sum2<T>(a, b, sh);
     if (threadIdx.x == 0) {
         const double m = a / dn;
         const double v = b / dn - m * m;
@@ -612,8 +614,9 @@ int launch_scrunch(const float *z, int64_t zp, int nchan, int64_t nout, int s, f
 
 int launch_chanstats(const float *p, int64_t pp, int nchan, int64_t n, double clip, double *stats, void *stream)
 {
-    hipLaunchKernelGGL(k_chanstats, dim3((uint32_t)nchan), dim3(kStatThreads), 0, (hipStream_t)stream, p, pp, n, clip,
-                       stats);
+    const int threads = n <= 1024 ? 64 : n <= 16384 ? 256 : 1024;
+    hipLaunchKernelGGL(threads == 64 ? k_chanstats<64> : threads == 256 ? k_chanstats<256> : k_chanstats<1024>,
+                       dim3((uint32_t)nchan), dim3((uint32_t)threads), 0, (hipStream_t)stream, p, pp, n, clip, stats);
     return (int)hipGetLastError();
 }
 

@@ -189,3 +189,24 @@ def test_flagging_many_short_windows(snd, orc, nchan, n, window):
     y = zt.cpu().numpy()
     for b in np.flatnonzero(ok):
         assert np.array_equal(y[:, b * window:(b + 1) * window], want_z[:, b * window:(b + 1) * window])
+
+
+@pytest.mark.parametrize("n", [1, 3, 63, 257, 1023, 1024, 1025, 4099, 16384, 16385, 33001])
+def test_channel_stats_by_row_length(snd, orc, n):
+    """Clipped statistics of rows around each workgroup size, on rows that start on any element, with
+    bright samples that the clip moves, a constant and a NaN row: the oracle's to FP64 rounding."""
+    rng = synth.make_rng(n)
+    p = (rng.standard_normal((7, n + 1)) * 3.0 + 100.0).astype(np.float32)
+    p[2, n // 2] = 5000.0
+    p[3] = 17.25
+    p[6, n // 3 + 1] = np.nan
+    x = p[:, 1:]
+    block = torch.zeros((7, n + 2), device="cuda")
+    xt = block[:, 1:1 + n]
+    xt.copy_(torch.from_numpy(np.ascontiguousarray(x)))
+    got = snd.channel_stats(xt, clip=5.0).cpu().numpy()
+    want = orc.sigma_clip_stats(np.ascontiguousarray(x[:6]), 5.0)
+    # (the variance is E[d^2] - E[d]^2 about a sample of the row: rounding of its ten-fold squares)
+    assert np.allclose(got[:6, 0], want[:, 0], rtol=1e-12, atol=0)
+    assert np.allclose(got[:6, 1], want[:, 1], rtol=1e-9, atol=1e-9)
+    assert got[3, 1] == 0.0 and np.isnan(got[6, 0])
