@@ -23,7 +23,7 @@ __device__ inline f32x4u load4(global_ptr<const float> p) { return *reinterpret_
 
 constexpr int kRow = 4096;  // samples of a row per workgroup: 256 threads, four 16-byte loads each
 
-// A 256-thread workgroup's kRow samples of a row from t0 (n: the row's samples): f(t, x) for every
+// A workgroup's kRow samples of a row from t0 (n: the row's samples; row_threads threads): f(t, x) for every
 // whole group of four, one(t, x) for the samples of the last, partial one.
 template <typename F, typename G>
 __device__ inline void row_quads(const float *row, int64_t t0, int64_t n, F &&f, G &&one)
@@ -74,26 +74,29 @@ __global__ __launch_bounds__(256) void k_encode_cm(const float *z, int64_t zp, i
         [&](int64_t t, float x) { dst[t] = (uint8_t)level(th, x); });
 }
 
-// Time-major input, transposed through LDS: a tile of 64 channels x 256 samples.  A lane reads one
-// channel of 64 consecutive samples (a wave reads whole 256-byte lines), packs four levels per dword
-// and writes them to its channel's LDS row; the rows leave as 256-byte stores (64 x 64 tiles of bytes
-// took 0.26 ms for 1024 x 131,072 samples, this 0.17).
-constexpr int kTmT = 256;            // samples per tile
-constexpr int kTmPitch = kTmT / 4 + 1;  // dwords per LDS row: odd, so that a column of lanes spreads over the banks
+// Time-major input, transposed through LDS: a tile of 64 channels x T samples.  A lane reads one
+// channel of T / 4 consecutive samples (a wave reads whole 256-byte lines), packs four levels per dword
+// and writes them to its channel's LDS row; the rows leave as runs of T bytes (64 x 64 tiles of bytes
+// took 0.26 ms for 1024 x 131,072 samples, T = 256 takes 0.17).  Blocks of fewer than kTmBlocks such tiles
+// take T = 64, since a wave's loads come in rounds of sixteen (four thresholds: 64 channels x 4000 samples
+// 14.6 us by 256, 9.1 by 64; 1024 x 8192 16.0 and 10.9).
+constexpr int64_t kTmBlocks = 1024, kTmBitBlocks = 512;
 
+template <int T>
 __global__ __launch_bounds__(256) void k_encode_tm(const float *z, int64_t zp, int nchan, int64_t nsamp, Thresholds th,
                                                    uint8_t *out, int64_t op)
 {
-    __shared__ uint32_t tile[64 * kTmPitch];
-    const int64_t tb = (int64_t)blockIdx.x * kTmT;
+    constexpr int W = T / 4, pitch = W + 1;  // dwords of an LDS row; odd pitch: a column of lanes spreads over the banks
+    __shared__ uint32_t tile[64 * pitch];
+    const int64_t tb = (int64_t)blockIdx.x * T;
     const int cb = blockIdx.y * 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = cb + lane;
     const auto src = as_global(z) + c;
-    const bool inside = tb + kTmT <= nsamp && cb + 64 <= nchan;  // uniform
+    const bool inside = tb + T <= nsamp && cb + 64 <= nchan;  // uniform
 #pragma unroll 1
-    for (int g = 0; g < 4; ++g) {  // 16 samples of the wave's 64 at a time
-        const int64_t t = tb + 64 * wave + 16 * g;
+    for (int g = 0; g < W / 16; ++g) {  // 16 samples of the wave's T / 4 at a time
+        const int64_t t = tb + W * wave + 16 * g;
         float x[16];
         if (inside) {
 #pragma unroll
@@ -104,16 +107,18 @@ __global__ __launch_bounds__(256) void k_encode_tm(const float *z, int64_t zp, i
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            tile[lane * kTmPitch + 16 * wave + 4 * g + q] = level(th, x[4 * q]) | level(th, x[4 * q + 1]) << 8 |
-                                                            level(th, x[4 * q + 2]) << 16 | level(th, x[4 * q + 3]) << 24;
+            tile[lane * pitch + W / 4 * wave + 4 * g + q] =
+                level(th, x[4 * q]) | level(th, x[4 * q + 1]) << 8 | level(th, x[4 * q + 2]) << 16 |
+                level(th, x[4 * q + 3]) << 24;
     }
     __syncthreads();
-    const int64_t t = tb + 4 * lane;
+    const int wl = lane & (W - 1);
+    const int64_t t = tb + 4 * wl;
 #pragma unroll 4
-    for (int i = 0; i < 16; ++i) {
-        const int r = 16 * wave + i;  // channel within the tile
+    for (int i = 0; i < 16; i += 64 / W) {
+        const int r = 16 * wave + i + lane / W;  // channel within the tile
         if (cb + r >= nchan) break;
-        const uint32_t w = tile[r * kTmPitch + lane];
+        const uint32_t w = tile[r * pitch + wl];
         const auto dst = as_global(out + (int64_t)(cb + r) * op + t);
         if (t + 4 <= nsamp) *reinterpret_cast<global_ptr<u32u>>(dst) = w;
         else
@@ -123,7 +128,7 @@ __global__ __launch_bounds__(256) void k_encode_tm(const float *z, int64_t zp, i
 
 // Bits: a wave tests 1024 consecutive samples of a channel, 64 per ballot (sixteen loads in flight),
 // and writes their 32 words as one 128-byte store (one ballot and an 8-byte store per wave took
-// 0.27 ms for 1024 x 131,072 samples, this 0.10).
+// 0.27 ms for 1024 x 131,072 samples, this 0.10).  Rows short of kRow take no more waves than they fill.
 __global__ __launch_bounds__(256) void k_encode_bits_cm(const float *z, int64_t zp, int64_t nsamp, float th,
                                                         uint32_t *out, int64_t ow)
 {
@@ -150,37 +155,41 @@ __global__ __launch_bounds__(256) void k_encode_bits_cm(const float *z, int64_t 
 }
 
 // Bits from time-major input: a lane builds the words of one channel from the samples it reads (a
-// wave reads whole 256-byte lines), 32 samples each; the words of 64 channels x 1024 samples leave
-// through LDS as 128-byte runs of each row.
+// wave reads whole 256-byte lines), 32 samples each; the words of 64 channels x 128 K samples leave
+// through LDS as runs of 4 K words of each row.  Blocks of fewer than kTmBitBlocks tiles of K = 8 take
+// K = 2 (3 channels x 100,000 samples: 29 us by 8, with a branch for the last channels, 7.9).
+template <int K>
 __global__ __launch_bounds__(256) void k_encode_bits_tm(const float *z, int64_t zp, int nchan, int64_t nsamp,
                                                         float th, uint32_t *out, int64_t ow)
 {
-    __shared__ uint32_t tile[64 * 33];
-    const int64_t tb = (int64_t)blockIdx.x * 1024;
+    constexpr int W = 4 * K;  // words of an LDS row
+    __shared__ uint32_t tile[64 * (W + 1)];
+    const int64_t tb = (int64_t)blockIdx.x * (32 * W);
     const int cb = blockIdx.y * 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = cb + lane;
-    const auto src = as_global(z) + c;
+    // lanes past the last channel read the last one's samples: their words are not stored
+    const auto src = as_global(z) + (cb + lane < nchan ? cb + lane : nchan - 1);
 #pragma unroll 1
-    for (int k = 0; k < 8; ++k) {  // the wave's words 8 wave + k
-        const int64_t t = tb + 256 * wave + 32 * k;
-        uint32_t w = 0;
-        if (t + 32 <= nsamp && cb + 64 <= nchan) {  // uniform
-            float x[32];
+    for (int k = 0; k < K; ++k) {  // the wave's words K wave + k
+        const int64_t t = tb + 32 * (K * wave + k);
+        float x[32];
+        if (t + 32 <= nsamp) {  // uniform
 #pragma unroll
             for (int i = 0; i < 32; ++i) x[i] = src[(t + i) * zp];
+        } else {
 #pragma unroll
-            for (int i = 0; i < 32; ++i) w |= (uint32_t)(x[i] > th) << i;
-        } else if (c < nchan) {
-            for (int i = 0; i < 32 && t + i < nsamp; ++i) w |= (uint32_t)(src[(t + i) * zp] > th) << i;
+            for (int i = 0; i < 32; ++i) x[i] = t + i < nsamp ? src[(t + i) * zp] : -__builtin_inff();
         }
-        tile[lane * 33 + 8 * wave + k] = w;
+        uint32_t w = 0;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) w |= (uint32_t)(x[i] > th && t + i < nsamp) << i;
+        tile[lane * (W + 1) + K * wave + k] = w;
     }
     __syncthreads();
-    const int wl = lane & 31;
+    const int wl = lane & (W - 1);
     const int64_t wi = (tb >> 5) + wl;
-    for (int r = 2 * wave + (lane >> 5); r < 64; r += 8)
-        if (cb + r < nchan && 32 * wi < nsamp) as_global(out + (int64_t)(cb + r) * ow)[wi] = tile[r * 33 + wl];
+    for (int r = 64 / W * wave + lane / W; r < 64; r += 256 / W)
+        if (cb + r < nchan && 32 * wi < nsamp) as_global(out + (int64_t)(cb + r) * ow)[wi] = tile[r * (W + 1) + wl];
 }
 
 // Time scrunch: output t is the sum of s consecutive samples of one channel in order (FP32, no
@@ -562,6 +571,8 @@ __global__ __launch_bounds__(256) void k_cast(const float *src, int64_t sp, int6
 }
 
 uint32_t blocks(int64_t n, int64_t per) { return (uint32_t)((n + per - 1) / per); }
+// threads of a row_quads workgroup: rows of up to 512 samples have one quad for half of 256 or fewer
+uint32_t row_threads(int64_t n) { return n > 512 ? 256 : n > 256 ? 128 : 64; }
 
 }  // namespace
 
@@ -572,12 +583,13 @@ int launch_encode(const float *z, int64_t zp, int time_major, int nchan, int64_t
     th.n = nthr;
     for (int i = 0; i < nthr; ++i) th.v[i] = thr[i];
     hipStream_t st = (hipStream_t)stream;
+    const bool few = (int64_t)blocks(nsamp, 256) * blocks(nchan, 64) < kTmBlocks;
     if (time_major)
-        hipLaunchKernelGGL(k_encode_tm, dim3(blocks(nsamp, kTmT), blocks(nchan, 64)), dim3(256), 0, st, z, zp, nchan,
-                           nsamp, th, out, op);
+        hipLaunchKernelGGL(few ? k_encode_tm<64> : k_encode_tm<256>, dim3(blocks(nsamp, few ? 64 : 256), blocks(nchan, 64)),
+                           dim3(256), 0, st, z, zp, nchan, nsamp, th, out, op);
     else
-        hipLaunchKernelGGL(k_encode_cm, dim3(blocks(nsamp, kRow), (uint32_t)nchan), dim3(256), 0, st, z, zp, nsamp, th,
-                           out, op);
+        hipLaunchKernelGGL(k_encode_cm, dim3(blocks(nsamp, kRow), (uint32_t)nchan), dim3(row_threads(nsamp)), 0, st, z,
+                           zp, nsamp, th, out, op);
     return (int)hipGetLastError();
 }
 
@@ -585,12 +597,14 @@ int launch_encode_bits(const float *z, int64_t zp, int time_major, int nchan, in
                        int64_t ow, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
+    const bool few = (int64_t)blocks(nsamp, 1024) * blocks(nchan, 64) < kTmBitBlocks;
     if (time_major)
-        hipLaunchKernelGGL(k_encode_bits_tm, dim3(blocks(nsamp, 1024), blocks(nchan, 64)), dim3(256), 0, st, z, zp,
-                           nchan, nsamp, thr, out, ow);
-    else
-        hipLaunchKernelGGL(k_encode_bits_cm, dim3(blocks(nsamp, kRow), (uint32_t)nchan), dim3(256), 0, st, z, zp, nsamp,
+        hipLaunchKernelGGL(few ? k_encode_bits_tm<2> : k_encode_bits_tm<8>,
+                           dim3(blocks(nsamp, few ? 256 : 1024), blocks(nchan, 64)), dim3(256), 0, st, z, zp, nchan, nsamp,
                            thr, out, ow);
+    else
+        hipLaunchKernelGGL(k_encode_bits_cm, dim3(blocks(nsamp, kRow), (uint32_t)nchan),
+                           dim3(64 * blocks(nsamp < kRow ? nsamp : kRow, 1024)), 0, st, z, zp, nsamp, thr, out, ow);
     return (int)hipGetLastError();
 }
 
@@ -623,8 +637,8 @@ int launch_chanstats(const float *p, int64_t pp, int nchan, int64_t n, double cl
 int launch_normalize(const float *p, int64_t pp, int nchan, int64_t n, const double *stats, float *z, int64_t zp,
                      void *stream)
 {
-    hipLaunchKernelGGL(k_normalize, dim3(blocks(n, kRow), (uint32_t)nchan), dim3(256), 0, (hipStream_t)stream, p, pp, n,
-                       stats, z, zp);
+    hipLaunchKernelGGL(k_normalize, dim3(blocks(n, kRow), (uint32_t)nchan), dim3(row_threads(n)), 0, (hipStream_t)stream,
+                       p, pp, n, stats, z, zp);
     return (int)hipGetLastError();
 }
 
@@ -653,9 +667,9 @@ int launch_flag_channels(float *z, int64_t zp, int nchan, int64_t n, int64_t w, 
 int launch_cast(const float *src, int64_t sp, int64_t rows, int64_t cols, void *dst, int64_t dp, int dst_dt, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid(blocks(cols, kRow), (uint32_t)rows);
-    if (dst_dt == SND_DT_BF16) hipLaunchKernelGGL(k_cast<bf16_t>, grid, dim3(256), 0, st, src, sp, cols, (bf16_t *)dst, dp);
-    else if (dst_dt == SND_DT_F16) hipLaunchKernelGGL(k_cast<f16_t>, grid, dim3(256), 0, st, src, sp, cols, (f16_t *)dst, dp);
+    const dim3 grid(blocks(cols, kRow), (uint32_t)rows), threads(row_threads(cols));
+    if (dst_dt == SND_DT_BF16) hipLaunchKernelGGL(k_cast<bf16_t>, grid, threads, 0, st, src, sp, cols, (bf16_t *)dst, dp);
+    else if (dst_dt == SND_DT_F16) hipLaunchKernelGGL(k_cast<f16_t>, grid, threads, 0, st, src, sp, cols, (f16_t *)dst, dp);
     else return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
 }

@@ -210,3 +210,26 @@ def test_channel_stats_by_row_length(snd, orc, n):
     assert np.allclose(got[:6, 0], want[:, 0], rtol=1e-12, atol=0)
     assert np.allclose(got[:6, 1], want[:, 1], rtol=1e-9, atol=1e-9)
     assert got[3, 1] == 0.0 and np.isnan(got[6, 0])
+
+
+@pytest.mark.parametrize("nchan,n", [(1000, 32805), (130, 90001), (70, 5000), (2, 129), (64, 256), (129, 1023)])
+def test_time_major_tiles(snd, orc, nchan, n):
+    """Both tile lengths of the time-major encoders (the longer ones in blocks that fill the chip), with
+    ragged ends in channels and time, infinities and NaNs: the oracle's levels and bits, the channel-major
+    encoders' too, and nothing written past a row."""
+    z = synth.make_rng(nchan + n).standard_normal((nchan, n)).astype(np.float32)
+    z[0, :: 7], z[-1, 1:: 11], z[nchan // 2, n - 1] = np.inf, np.nan, -np.inf
+    th = [-0.5, 0.25, 1.0]
+    want, want1 = orc.encode(z, th), orc.encode(z, [0.25])
+    zt = torch.from_numpy(z).cuda()
+    for tm in (True, False):
+        src = zt.t().contiguous() if tm else zt
+        guard = torch.full((nchan, n + 7), 77, dtype=torch.uint8, device="cuda")
+        snd.encode(src, th, time_major=tm, out=guard[:, 3:3 + n])
+        g = guard.cpu().numpy()
+        assert np.array_equal(g[:, 3:3 + n], want) and np.all(g[:, :3] == 77) and np.all(g[:, 3 + n:] == 77)
+        words = torch.full((nchan, (n + 31) // 32 + 2), -1, dtype=torch.int32, device="cuda")
+        snd.encode_bits(src, 0.25, time_major=tm, out=words)
+        bits = np.unpackbits(words.cpu().numpy().view(np.uint8), axis=1, bitorder="little")
+        pad = (n + 31) // 32 * 32
+        assert np.array_equal(bits[:, :n], want1) and np.all(bits[:, n:pad] == 0) and np.all(bits[:, pad:] == 1)
