@@ -1,4 +1,4 @@
-// FDMT merges for gfx950 (Methods, "Classical dedispersion algorithms"), K iterations per pass.
+// FDMT merges for gfx950 (Methods, "Classical dedispersion algorithms"), K = 2 .. 5 iterations per pass.
 //
 // One iteration writes every delay row of every sub-band and the next one reads them all, about 2 n
 // samples of traffic per row and iteration, which is all the time there is (a pass over one iteration
@@ -8,8 +8,9 @@
 // shifted by less than kFdmtRun samples along the group.  A workgroup keeps those rows as 256-sample
 // slots, reads the pass's source rows once for the iteration next to them, and forms the others slot from
 // slot (the same FP32 sums as K single passes, bit for bit).  The sources of the next tile are on
-// their way while a tile is formed; two workgroups share a CU.
-// @MEASURED@
+// their way while a tile is formed; two workgroups share a CU.  1024 channels x 65,536 samples to DM 1000,
+// ten iterations: in ten passes of one 16.0 ms, in four of up to three through registers 7.8, in two of
+// five through LDS 3.6.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -43,7 +44,7 @@ constexpr int ops_at(int k) { return (slots_at(k) + kWaves - 1) / kWaves; }
 // a shifted row may run a quad and the largest shift past its slot
 constexpr int lds_bytes(int k)
 {
-    return k < 2 ? 1024 : (slots_at(k - 1) + (k > 2 ? slots_at(k - 2) : 0)) * kSlotBytes + 4 * kFdmtRun + 16;
+    return (slots_at(k - 1) + (k > 2 ? slots_at(k - 2) : 0)) * kSlotBytes + 4 * kFdmtRun + 16;
 }
 static_assert(lds_bytes(kFdmtMaxIters) <= 81920, "two workgroups on a CU");
 
@@ -198,34 +199,45 @@ __global__ __launch_bounds__(64 * kWaves, 8) void k_fdmt(const float *src, int64
     };
     if (tile0 < tile1) load(tile0);
     for (int64_t tile = tile0; tile < tile1; ++tile) {
-        if constexpr (K == 1) {
-            f32x4 s[M];
 #pragma unroll
-            for (int m = 0; m < M; ++m) s[m] = u[m] + l[m];
-            if (tile + 1 < tile1) load(tile + 1);
+        for (int m = 0; m < M; ++m)
+            if (m < cnt[K - 1])
+                *reinterpret_cast<f32x4 *>(smem + (wave + kWaves * m) * kSlotBytes + 16 * lane) = u[m] + l[m];
+        lds_barrier();
+        if (tile + 1 < tile1) load(tile + 1);
 #pragma unroll
-            for (int m = 0; m < M; ++m)
-                if (m < cnt[0]) store(m, tile, s[m]);
-        } else {
+        for (int k = K - 2; k >= 0; --k) {
+            unsigned char *out = smem + ((K - 1 - k) % 2 ? kOther : 0);
 #pragma unroll
-            for (int m = 0; m < M; ++m)
-                if (m < cnt[K - 1])
-                    *reinterpret_cast<f32x4 *>(smem + (wave + kWaves * m) * kSlotBytes + 16 * lane) = u[m] + l[m];
-            lds_barrier();
-            if (tile + 1 < tile1) load(tile + 1);
-#pragma unroll
-            for (int k = K - 2; k >= 0; --k) {
-                unsigned char *out = smem + ((K - 1 - k) % 2 ? kOther : 0);
-#pragma unroll
-                for (int m = 0; m < ops_at(k); ++m) {
-                    if (m >= cnt[k]) break;
-                    const f32x4 s = sum_rows(smem, at[k][m][0], at[k][m][1], lane);
-                    if (k == 0) store(m, tile, s);
-                    else *reinterpret_cast<f32x4 *>(out + (wave + kWaves * m) * kSlotBytes + 16 * lane) = s;
-                }
-                // (level 0 reads the buffer that the next tile's level K - 1 writes where K is even)
-                if (k > 0 || K % 2 == 0) lds_barrier();
+            for (int m = 0; m < ops_at(k); ++m) {
+                if (m >= cnt[k]) break;
+                const f32x4 s = sum_rows(smem, at[k][m][0], at[k][m][1], lane);
+                if (k == 0) store(m, tile, s);
+                else *reinterpret_cast<f32x4 *>(out + (wave + kWaves * m) * kSlotBytes + 16 * lane) = s;
             }
+            // (level 0 reads the buffer that the next tile's level K - 1 writes where K is even)
+            if (k > 0 || K % 2 == 0) lds_barrier();
+        }
+    }
+}
+
+// One merge alone (two channels): output row r = source row U (tab[4r]) plus source row L (tab[4r + 1]) read
+// tab[4r + 2] samples later, zero past n.  Nothing to keep in LDS; a workgroup covers 2048 samples of a
+// strided set of rows, and the table words are uniform (7089 rows of 100,000 samples: 0.51 ms, by tiles
+// of the pass above 0.61).
+__global__ __launch_bounds__(256) void k_fdmt_merge(const float *src, int64_t sp, float *dst, int64_t dp,
+                                                    const int32_t *tab, int64_t rows, int64_t n)
+{
+    const int64_t t0 = (int64_t)blockIdx.x * 2048 + threadIdx.x;
+    for (int64_t r = blockIdx.y; r < rows; r += gridDim.y) {
+        const int64_t ru = tab[4 * r], rl = tab[4 * r + 1], du = tab[4 * r + 2];
+        const float *u = src + ru * sp;
+        const float *l = src + rl * sp + du;
+        float *o = dst + r * dp;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t t = t0 + 256 * j;
+            if (t < n) o[t] = u[t] + (t + du < n ? l[t] : 0.0f);
         }
     }
 }
@@ -261,7 +273,10 @@ int launch_fdmt_pass(int k, const float *src, int64_t sp, float *dst, int64_t dp
     if (rows < 1) return 0;
     hipStream_t st = (hipStream_t)stream;
     switch (k) {
-    case 1: return launch_pass<1>(src, sp, dst, dp, tabs, rows, ngroups, n, st);
+    case 1:
+        hipLaunchKernelGGL(k_fdmt_merge, dim3((uint32_t)((n + 2047) / 2048), (uint32_t)(rows < 4096 ? rows : 4096)),
+                           dim3(256), 0, st, src, sp, dst, dp, tabs[0], rows, n);
+        return (int)hipGetLastError();
     case 2: return launch_pass<2>(src, sp, dst, dp, tabs, rows, ngroups, n, st);
     case 3: return launch_pass<3>(src, sp, dst, dp, tabs, rows, ngroups, n, st);
     case 4: return launch_pass<4>(src, sp, dst, dp, tabs, rows, ngroups, n, st);
