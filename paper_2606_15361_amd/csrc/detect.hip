@@ -57,9 +57,10 @@ template <typename T> int snr_tile(int wmax)
                                                   : (kThreads * kFloatSlabs - (wmax - 1)) / 64 * 64;
 }
 static_assert(kThreads * kFloatSlabs - kFloatNarrow - 63 > kThreads * (kFloatSlabs - 1), "only the last slab is partial");
-// Prefix entry j of a float tile sits at j + j / 8: a thread writes runs of consecutive entries, and
-// the gap of one entry in eight spreads the lanes of a wave over the LDS banks.
-template <typename P> __device__ inline int pre_at(int j) { return std::is_same<P, double>::value ? j + (j >> 3) : j; }
+// Prefix entry j of a float tile of the cell list sits at j + j / 8: a thread writes runs of consecutive
+// entries, and the gap of one entry in eight spreads the lanes of a wave over the LDS banks.  (The whole
+// plane's tiles have none: every cell reads every width there, and the gaps cost more than they save.)
+template <bool GAPS> __device__ inline int pre_at(int j) { return GAPS ? j + (j >> 3) : j; }
 
 // Row sums with 16-byte loads: a scalar head up to the first 16-byte boundary of the row, then
 // 16-byte vectors (four in flight per thread), then a scalar tail.  f(x, j) folds one sample;
@@ -582,16 +583,18 @@ __global__ __launch_bounds__(kThreads) void k_snr_pairs(const uint8_t *plane, in
         snr_pairs_tile<true>(rowk + t0, k, t0, avail, nwk, stats, a, pair_dyn, sh);
 }
 
-// PER: staged samples per thread.  BATCH: rows of several planes (SnrArgs::beams).  LDS reads and
+// PER: staged samples per thread.  BATCH: rows of several planes (SnrArgs::beams).  PLANE: the whole S/N
+// plane instead of the cell list.  LDS reads and
 // the FP64 bound tests bound the float form; with the widths as a run-time outer loop over
 // straight-line slabs (against a run-time loop with end tests inside each cell) a 4096 x 102,748
 // plane takes 1.12 ms with eleven widths up to 1024 (was 3.39), and 4 x 4096 rows of 8192 cells with
 // seven widths 0.26 ms (was 0.81).
-template <typename T, int PER, bool BATCH>
+template <typename T, int PER, bool BATCH, bool PLANE>
 __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch, int64_t n_, const double *stats,
                                                   SnrArgs a)
 {
     using P = typename PrefixType<T>::type;
+    constexpr bool G = std::is_same<P, double>::value && !PLANE;
     constexpr int kSlabs = snr_slabs<T>();  // cells per thread
     static_assert(kSlabs <= 32, "one flag bit per slab");
     extern __shared__ __align__(16) unsigned char snr_dyn[];  // prefix sums: tile + widest width + 1
@@ -621,9 +624,10 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
     const int avail = (int)(n - t0 < tile + kMaxWidth ? n - t0 : tile + kMaxWidth);
     // elements t0 .. t0 + L - 1 are needed (and exist)
     const int L = avail < tile + wmax - 1 ? avail : tile + wmax - 1;
-    // float tiles on a 16-byte boundary are read as 16-byte vectors
+    // float tiles are read as 16-byte vectors, which may start on any element (1024 unaligned rows x 40,000
+    // samples, one boxcar of 16: 129 us sample by sample, 96 so)
     static_assert(PER % 4 == 0, "vector chunks");
-    const bool vec4 = !IsInt<T>::value && sizeof(T) == 4 && ((uintptr_t)row & 15u) == 0;
+    const bool vec4 = !IsInt<T>::value && sizeof(T) == 4 && ((uintptr_t)row & 3u) == 0;
     // every thread takes PER elements, those past L read as zero (integer tiles: the staged bytes
     // fit the prefix array for any L), and only prefix entries up to L are written
     const int beg = tid * PER;
@@ -655,14 +659,13 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
             run += v[i];
         }
     } else if (vec4) {
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        const auto g4 = as_global(reinterpret_cast<const f32x4 *>(row));
+        typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
         const auto grow = as_global(row);
 #pragma unroll
         for (int i = 0; i < PER; i += 4) {
             const int j = beg + i;
             if (j + 3 < L) {
-                const f32x4 q = g4[j >> 2];
+                const f32x4u q = *reinterpret_cast<global_ptr<const f32x4u>>(grow + j);
                 v[i] = (P)q.x;
                 v[i + 1] = (P)q.y;
                 v[i + 2] = (P)q.z;
@@ -688,13 +691,22 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
     __syncthreads();
     P acc = inc - run;
     for (int w = 0; w < wv; ++w) acc += wtot[w];
-    // entries 0 .. L: each thread writes the prefix before each of its samples, the thread that
-    // holds sample L - 1 also the one after it
+    if constexpr (G) {
+        // entries 0 .. L: each thread writes the prefix before each of its samples, the thread that
+        // holds sample L - 1 also the one after it
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        if (beg + i < L) pre[pre_at<P>(beg + i)] = acc;
-        acc += v[i];
-        if (beg + i == L - 1) pre[pre_at<P>(L)] = acc;
+        for (int i = 0; i < PER; ++i) {
+            if (beg + i < L) pre[pre_at<G>(beg + i)] = acc;
+            acc += v[i];
+            if (beg + i == L - 1) pre[pre_at<G>(L)] = acc;
+        }
+    } else {
+        if (tid == 0) pre[0] = (P)0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            acc += v[i];
+            if (beg + i < L) pre[beg + i + 1] = acc;  // entries 1 .. L
+        }
     }
     const double mu = stats[2 * k], sg = stats[2 * k + 1];
     // per-row constants of S/N(t, W) = (S_W(t) - mu W) / (sigma sqrt W)
@@ -710,7 +722,7 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
             if (i + W > avail) break;
             double val = 0.0;
             if (sg > 0.0) {
-                const double s = (double)(pre[pre_at<P>(i + W)] - pre[pre_at<P>(i)]);
+                const double s = (double)(pre[pre_at<G>(i + W)] - pre[pre_at<G>(i)]);
                 val = __dsub_rn(s, muw[w]) / den[w];
             }
             if (bi < 0 || val > best) {
@@ -719,10 +731,11 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
             }
         }
     };
-    if (a.snr) {  // the whole S/N plane
-        for (int i = tid; i < tile; i += kThreads) {
+    if constexpr (PLANE) {
+        for (int j = 0; j < kSlabs; ++j) {
+            const int i = tid + kThreads * j;
             const int64_t t = t0 + i;
-            if (t >= n) break;
+            if (i >= tile || t >= n) break;
             double best;
             int bi;
             exact(i, best, bi);
@@ -742,16 +755,16 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
 #pragma unroll
     for (int j = 0; j < kSlabs; ++j) {
         mk[j] = 0;
-        p0[j] = j < slabs ? pre[pre_at<P>(tid + kThreads * j)] : (P)0;
+        p0[j] = j < slabs ? pre[pre_at<G>(tid + kThreads * j)] : (P)0;
     }
     if (tile - 1 + wmax <= avail) {  // uniform: every width fits every cell
         for (int w = 0; w < nwk; ++w) {
             const P thr = sthr[w];
-            const P *p = pre + pre_at<P>(tid + sw[w]);
+            const P *p = pre + pre_at<G>(tid + sw[w]);
             P s[kSlabs];
             // entry i + W + 256 j: 256 entries on, 32 gaps more in a float tile
 #pragma unroll
-            for (int j = 0; j < kSlabs; ++j) s[j] = p[pre_at<P>(kThreads * j)];
+            for (int j = 0; j < kSlabs; ++j) s[j] = p[pre_at<G>(kThreads * j)];
 #pragma unroll
             for (int j = 0; j < kSlabs; ++j) mk[j] |= __ballot((P)(s[j] - p0[j]) >= thr);
         }
@@ -761,11 +774,11 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
             const int W = __builtin_amdgcn_readfirstlane(sw[w]);
             const int lim = avail - W < last ? avail - W : last;  // last cell of the tile that the width fits
             const P thr = sthr[w];
-            const P *p = pre + pre_at<P>(tid + W);
+            const P *p = pre + pre_at<G>(tid + W);
 #pragma unroll
             for (int j = 0; j < kSlabs; ++j) {
                 if (kThreads * j > lim) break;  // uniform
-                uint64_t hit = __ballot((P)(p[pre_at<P>(kThreads * j)] - p0[j]) >= thr);
+                uint64_t hit = __ballot((P)(p[pre_at<G>(kThreads * j)] - p0[j]) >= thr);
                 if (kThreads * j + kThreads - 1 > lim) hit &= __ballot(tid + kThreads * j <= lim);  // uniform
                 mk[j] |= hit;
             }
@@ -979,17 +992,16 @@ int launch_snr(int rows, const T *p, int64_t pitch, int64_t n, double *stats, co
             return (int)hipGetLastError();
         }
     }
-    // the prefix array holds the tile's slabs (which are read whole) plus the widest boxcar; integer tiles are first staged in its storage (at most kThreads * per
-    // samples of sizeof(T) <= 2 bytes each)
+    // the prefix array holds the tile's slabs (which are read whole) plus the widest boxcar; integer tiles
+    // are first staged in its storage (at most kThreads * per samples of sizeof(T) <= 2 bytes each)
     int64_t bytes = ((int64_t)snr_slabs<T>() * kThreads + wmax + 1) * (int64_t)sizeof(P);
     if (IsInt<T>::value) bytes = std::max<int64_t>(bytes, (int64_t)kThreads * snr_per<T>(false) * 2);
-    else bytes += bytes / 8 + (int64_t)sizeof(P);
-    if (wide)
-        hipLaunchKernelGGL((k_snr<T, snr_per<T>(true), BATCH>), grid, dim3(kThreads), (size_t)bytes, st, p, pitch, n,
-                           stats, a);
-    else
-        hipLaunchKernelGGL((k_snr<T, snr_per<T>(false), BATCH>), grid, dim3(kThreads), (size_t)bytes, st, p, pitch, n,
-                           stats, a);
+    else if (!a.snr) bytes += bytes / 8 + (int64_t)sizeof(P);
+    constexpr int narrow = snr_per<T>(false), broad = snr_per<T>(true);
+    auto kernel = wide ? k_snr<T, broad, BATCH, false> : k_snr<T, narrow, BATCH, false>;
+    if constexpr (!BATCH)
+        if (a.snr) kernel = wide ? k_snr<T, broad, false, true> : k_snr<T, narrow, false, true>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), (size_t)bytes, st, p, pitch, n, stats, a);
     return (int)hipGetLastError();
 }
 

@@ -490,3 +490,44 @@ def test_batched_detection_equals_per_beam(snd, orc, scaled):
         assert bd.npixels[i] == d.npixels, i
         total += len(want)
     assert total > 0
+
+
+@pytest.mark.parametrize("dtype", ["u8", "u16", "float"])
+@pytest.mark.parametrize("n", [5, 1984, 2049, 4097, 9000])
+def test_rows_on_any_element(snd, orc, dtype, n):
+    """Rows that start on any element, padding of large values on both sides: the S/N plane and its width
+    indices at every cell, and the oracle's cells, for narrow and wide lists; float rows that hold a NaN or an
+    infinity have neither."""
+    rng = synth.make_rng(n + len(dtype))
+    ndm = 5
+    if dtype == "float":
+        plane = rng.standard_normal((ndm, n)).astype(np.float32)
+    else:
+        plane = rng.integers(0, 4, (ndm, n)).astype(np.uint8 if dtype == "u8" else np.uint16)
+    hi = {"u8": 255, "u16": 900, "float": 1e6}[dtype]
+    plane[1, n // 2: n // 2 + 20] += plane.dtype.type(9)
+    plane[2, -3:] += plane.dtype.type(9)
+    mode, cap = ("float", 255) if dtype == "float" else ("graded", 255 if dtype == "u8" else 900)
+    p = snd.Plan(synth.channel_freqs(4), np.zeros(ndm), 0.138e-3, n, mode=mode, branching=2, cap=cap)
+    for off in (1, 2, 3):
+        full = np.full((ndm, n + 8 + n % 2), hi).astype(plane.dtype)
+        full[:, off:off + n] = plane
+        dev = torch.from_numpy(full).cuda()[:, off:off + n]
+        for widths in ([1, 3, 4, 60], [2, 200, 1000], [1]):
+            o_snr, o_widx, _, _ = orc.matched_filter(plane.astype(np.float64), widths, integer_plane=dtype != "float")
+            det = snd.Detector(p, widths, threshold=4.0, closing_radius=0, n_min=1)
+            snr, widx = det.snr_plane(dev)
+            # float prefix sums agree to FP64 rounding, which the plane's float32 may round either way
+            assert np.allclose(snr.cpu().numpy(), o_snr, rtol=2e-7, atol=1e-12 if dtype == "float" else 0)
+            assert np.array_equal(widx.cpu().numpy(), o_widx)
+            got = det.run(dev)
+            want = orc.candidates(o_snr, o_widx, 4.0, radius=0, n_min=1)
+            assert det.npixels == int((o_snr >= 4.0).sum())
+            assert [(g["k"], g["t"], g["widx"], g["npix"]) for g in got] == \
+                [(w["k"], w["t"], w["widx"], w["npix"]) for w in want]
+        if dtype == "float":
+            bad = dev.clone()
+            bad[1, n // 3], bad[2, n - 1] = float("nan"), float("inf")
+            det = snd.Detector(p, [1, 3, 4, 60], threshold=1.0, closing_radius=0, n_min=1)
+            assert not any(c["k"] in (1, 2) for c in det.run(bad))
+            assert not det.snr_plane(bad)[0][1:3].any()
