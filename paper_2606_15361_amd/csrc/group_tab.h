@@ -54,6 +54,10 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
     // the tile's first sample of the plane's first row (t0 is a multiple of a 16-byte unit's samples);
     // chunk sources add their unit index
     const unsigned char *tile_src = srcb + ((int64_t)t0 * ES - 16 * kChunkBias);
+    // the lane's offset words of the next batch
+    constexpr bool kCompact = lin_compact(WPL == 4, R);
+    constexpr int kPerInput = lin_input_words(WPL == 4, R);
+    auto next = as_global(s.lin + (kCompact ? ((int64_t)g * kGroupRows + wave) * s.n_entries * kPerInput : 0)) + WPL * lane;
     // Copies of batch bb into buffer j: this wave's chunks of its windows (scalar words blk), or
     // its windows one by one in the last tile; and the lane's offset words of the batch into w.
     auto issue = [&](int bb, const uint32_t (&blk)[NSM], int j, uint32_t (&w)[WPL]) {
@@ -72,11 +76,18 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
             issue_batch<TI, true>(batches, instrs, bb, wave, lane, srcb, pitch_bytes, t0, vt,
                             reinterpret_cast<TI *>(buf_base));
         }
-        const auto wp = as_global(s.lin + ((int64_t)bb * kGroupRows + wave) * NW + WPL * lane);
         typedef uint32_t words_t __attribute__((ext_vector_type(WPL)));
-        const words_t t = *reinterpret_cast<global_ptr<const words_t>>(wp);
+        auto take = [&](global_ptr<const uint32_t> wp) {
+            const words_t t = *reinterpret_cast<global_ptr<const words_t>>(wp);
 #pragma unroll
-        for (int i = 0; i < WPL; ++i) w[i] = t[i];
+            for (int i = 0; i < WPL; ++i) w[i] = t[i];
+        };
+        if constexpr (kCompact) {
+            take(next);
+            next += (int)blk[NSM - 1] * kPerInput;
+        } else {
+            take(as_global(s.lin + ((int64_t)bb * kGroupRows + wave) * NW + WPL * lane));
+        }
     };
     auto load_blk = [&](int bb, uint32_t (&blk)[NSM]) {
         const_ptr<uint32_t> p = smem_tab + ((int64_t)bb * kGroupRows + wave) * NSM;

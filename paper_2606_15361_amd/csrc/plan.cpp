@@ -273,9 +273,8 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
                 const Entry &en = S.ent[S.row_ptr[r] + e];
                 rd.push_back({en.rowc & kRowMask, en.off, w});
             }
-            std::sort(rd.begin(), rd.end(), [](const Rd &a, const Rd &b) {
-                return a.row != b.row ? a.row < b.row : a.off < b.off;
-            });
+            auto before = [](const Rd &a, const Rd &b) { return a.row != b.row ? a.row < b.row : a.off < b.off; };
+            if (!std::is_sorted(rd.begin(), rd.end(), before)) std::sort(rd.begin(), rd.end(), before);
             srcs.clear();
             for (const Rd &x : rd) {
                 if (srcs.empty() || srcs.back().row != x.row || x.off - srcs.back().lo > kGroupMaxSpan)
@@ -514,6 +513,29 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     S.lin = std::move(lin_tab);
     S.lin_smem = std::move(lin_smem);
     return true;
+}
+
+// Offset words of a table stage in the device image, and the copy of them.
+int64_t lin_image_words(const Stage &S)
+{
+    if (!lin_compact(S.group_pack, S.group_rpw)) return (int64_t)S.lin.size();
+    return S.ngroups * kGroupRows * (int64_t)S.n_entries * lin_input_words(S.group_pack, S.group_rpw);
+}
+void put_lin(const Stage &S, uint32_t *dst)
+{
+    if (!lin_compact(S.group_pack, S.group_rpw)) {
+        std::memcpy(dst, S.lin.data(), S.lin.size() * 4);
+        return;
+    }
+    const size_t full = S.group_pack ? kPackWords : kLinWords;
+    const size_t per = (size_t)lin_input_words(S.group_pack, S.group_rpw);
+    for (size_t g = 0; g + 1 < S.batch_ptr.size(); ++g)
+        for (size_t w = 0; w < (size_t)kGroupRows; ++w)
+            for (size_t b = (size_t)S.batch_ptr[g]; b < (size_t)S.batch_ptr[g + 1]; ++b) {
+                const size_t words = (size_t)(S.batches[4 * b + 1] - S.batches[4 * b]) * per;
+                std::memcpy(dst, &S.lin[(b * kGroupRows + w) * full], words * 4);
+                dst += words;
+            }
 }
 
 // First stage anchored on the input: one workgroup per (node, window of reference samples)
@@ -959,16 +981,18 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
     };
     for (Stage *T : in_table) {
         Stage &S = *T;
-        S.off_row_ptr = reserve((int64_t)S.row_ptr.size() * 4);
-        S.off_row_len = reserve((int64_t)S.row_len.size() * 4);
-        S.off_ent = reserve((int64_t)S.ent.size() * 8);
+        if (S.kernel != kKernelGroupLds) {  // (the row-group kernels have tables of their own)
+            S.off_row_ptr = reserve((int64_t)S.row_ptr.size() * 4);
+            S.off_row_len = reserve((int64_t)S.row_len.size() * 4);
+            S.off_ent = reserve((int64_t)S.ent.size() * 8);
+        }
         S.off_grp_rows = reserve((int64_t)S.grp_rows.size() * 4);
         S.off_batch_ptr = reserve((int64_t)S.batch_ptr.size() * 4);
         S.off_batches = reserve((int64_t)S.batches.size() * 4);
         S.off_instrs = reserve((int64_t)S.instrs.size() * 4);
         S.off_ldsb = reserve((int64_t)S.ldsb.size() * 4);
         S.off_node_closes = reserve((int64_t)S.node_closes.size() * 4);
-        S.off_lin = reserve((int64_t)S.lin.size() * 4);
+        S.off_lin = reserve(S.lin.empty() ? 0 : 4 * (lin_image_words(S) + kPackWords));
         S.off_lin_smem = reserve((int64_t)S.lin_smem.size() * 4);
         S.off_nodes = reserve((int64_t)S.nodes.size() * 4);
         S.off_tiles = reserve((int64_t)S.tiles.size() * 4);
@@ -981,16 +1005,18 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
     };
     for (Stage *T : in_table) {
         Stage &S = *T;
-        put(S.off_row_ptr, S.row_ptr.data(), S.row_ptr.size() * 4);
-        put(S.off_row_len, S.row_len.data(), S.row_len.size() * 4);
-        put(S.off_ent, S.ent.data(), S.ent.size() * 8);
+        if (S.kernel != kKernelGroupLds) {
+            put(S.off_row_ptr, S.row_ptr.data(), S.row_ptr.size() * 4);
+            put(S.off_row_len, S.row_len.data(), S.row_len.size() * 4);
+            put(S.off_ent, S.ent.data(), S.ent.size() * 8);
+        }
         put(S.off_grp_rows, S.grp_rows.data(), S.grp_rows.size() * 4);
         put(S.off_batch_ptr, S.batch_ptr.data(), S.batch_ptr.size() * 4);
         put(S.off_batches, S.batches.data(), S.batches.size() * 4);
         put(S.off_instrs, S.instrs.data(), S.instrs.size() * 4);
         put(S.off_ldsb, S.ldsb.data(), S.ldsb.size() * 4);
         put(S.off_node_closes, S.node_closes.data(), S.node_closes.size() * 4);
-        put(S.off_lin, S.lin.data(), S.lin.size() * 4);
+        if (!S.lin.empty()) put_lin(S, reinterpret_cast<uint32_t *>(&p.table[(size_t)S.off_lin]));
         put(S.off_lin_smem, S.lin_smem.data(), S.lin_smem.size() * 4);
         put(S.off_nodes, S.nodes.data(), S.nodes.size() * 4);
         put(S.off_tiles, S.tiles.data(), S.tiles.size() * 4);

@@ -71,8 +71,8 @@ struct Stage {
     // q * n .. q * n + n - 1 are the LDS byte offsets of the first samples of the n inputs of the
     // wave's row q (16-bit rows: those that start a dword first, each part in plan order); and
     // kLinSmemWords words read as scalars: the number of copy chunks of the wave, then for its
-    // chunks (global -> LDS copies of up to 64 16-byte units) the source unit index from the
-    // plane start, the LDS byte offset and the unit count, then (16-bit rows) the count of each
+    // chunks (global -> LDS copies of up to 64 16-byte units, see kLinMaxChunks) three words each,
+    // then (16-bit rows) the count of each
     // row's inputs that start a dword (4 bits per row), and last n.  The packed kernel keeps its
     // tables (kPackWords and kPackSmemWords per batch and wave) in the same two vectors.
     bool group_lin = false;
@@ -137,7 +137,7 @@ inline int lin_cover(int src_dtype) { return src_dtype == SND_DT_F32 ? lin_tile(
 // inputs per row and batch: the wave's offset words fit 64 lanes, and the 16-bit kernels pack
 // each row's count of inputs of one dword phase in 4 bits
 constexpr int lin_max_batch_entries(int src_dtype) { return 64 / lin_rows(src_dtype) < 15 ? 64 / lin_rows(src_dtype) : 15; }
-constexpr int kLinWords = 64;                  // offset words per (batch, wave)
+constexpr int kLinWords = 64;                  // offset words per (batch, wave), at most
 // Copy chunks of a wave and batch: up to 64 consecutive 16-byte units of the LDS buffer each, from one
 // window or the end of one and the start of the next (windows are laid out one after the other, and a
 // window's last chunk alone would leave most lanes idle: u8 windows of 65 or 66 units took two chunks
@@ -187,9 +187,16 @@ constexpr int kPackRoom = 59 * 1024;
 constexpr int64_t kPackMinBlocks = 128;
 constexpr int kPackRowsMax = 4;
 constexpr int kPackMaxBatchEntries = 64;
-constexpr int kPackWords = 256;                // offset words per (batch, wave)
+constexpr int kPackWords = 256;                // offset words per (batch, wave), at most
 constexpr int kPackCloses = 22, kPackParts = kPackCloses + kPackMaxBatchEntries / 8;  // first words
 constexpr int kPackSmemWords = kPackParts + kPackMaxParts / 2 + 2;
+// The device image holds the offset words without the unused ones, group by group and in each wave by
+// wave: lin_input_words per input of the row, batch after batch.  A wave's lanes may read up to kPackWords
+// words on from a batch's first.  (1024 channels x 4096 DMs: 49 MB of tables graded and 44 in f32 with them,
+// 20 and 21.)  Four-row packed shapes keep them, kPackWords a batch and wave: their scalar registers are
+// full, and a running address cost the kernel 10 % (1024 channels by eights x 1000 DMs, 0.48 -> 0.53 ms).
+constexpr bool lin_compact(bool pack, int rows) { return !(pack && rows == 4); }
+constexpr int lin_input_words(bool pack, int rows) { return pack ? 4 : rows; }
 constexpr int kPackLdsBytes = 163840 / 2;
 inline bool group_fast_types(int mode, int src_dt, int dst_dt)
 {

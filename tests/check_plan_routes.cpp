@@ -96,5 +96,9 @@ int main()
     EXPECT(P.stages[1].group_pack && P.alone.empty(), G, U8, 256, 4, 600, 0.0, 780.0, 9000);
     EXPECT(P.stages[1].group_pack && P.alone.size() == 1 && P.alone[0].group_f1 == 4, G, U8, 256, 4, 600, 0.0, 780.0,
            2640, true);
+    // device tables: a row-group stage's entry lists stay on the host, and offset words leave without padding
+    EXPECT(P.stages[1].off_ent == 0 && P.table.size() < 6000000, G, U8, 1000, 4, 1000, 0.0, 500.0, 30000);
+    EXPECT(P.stages[1].off_ent == 0 && P.table.size() < 2000000, F, F32, 1024, 4, 300, 0.0, 150.0, 30000);
+    EXPECT(P.direct[0].off_ent == 0 && P.table.size() < 1500000, F, F32, 64, 4, 600, 2.0, 800.0, 30000);
     return bad;
 }
