@@ -242,3 +242,36 @@ def test_autotune_times_candidates_with_identical_results(snd):
     assert res[best]["ms"] == min(r["ms"] for r in res)
     assert res[1]["workspace_bytes"] == 0 and res[2]["workspace_bytes"] < res[0]["workspace_bytes"]
     assert torch.equal(out, want)  # the last candidate (levels 0 and 2, chunks of 1500) wrote the same rows
+
+
+def test_batch_ragged_graded_beams(snd, orc):
+    """Graded beams over irregular trees in shared grids: packed ones by their own leaf maximum (within the
+    byte sums' bound and past it), one whose grid is too small for the packed kernel, and a regular one, whole
+    and partial runs, every workspace filled with 0xFF.  Bit-exact against the oracle and one execute per beam."""
+    cases = [(250, 4, 470, 9400, 15, 255, None), (250, 4, 470, 9500, 40, 200, 5000), (97, 3, 500, 9100, 29, 255, None),
+             (250, 4, 60, 1500, 15, 255, None), (256, 4, 200, 2300, 15, 255, 1111), (500, 8, 480, 9300, 31, 90, 9299)]
+    plans, xs, wants, n_run = [], [], [], []
+    for i, (nchan, B, ndm, n_out, top, cap, nr) in enumerate(cases):
+        f, dms = synth.channel_freqs(nchan), np.linspace(0.0, 20.0, ndm)
+        d = orc.delays(f, dms, 0.138e-3)
+        nsamp = int(d.max()) + n_out
+        x = synth.random_levels(synth.make_rng(700 + i), nchan, nsamp, 3)
+        q, r = divmod(top, 4)
+        for c in range(min(nchan // 4 * 4, 64)):
+            x[c, 50:nsamp - 50] = q + (1 if c % 4 < r else 0)
+        plans.append(snd.Plan(f, dms, 0.138e-3, nsamp, mode="graded", branching=B, cap=cap))
+        xs.append(torch.from_numpy(np.ascontiguousarray(x)).cuda())
+        wants.append(orc.snd_dedup(x, f, d, mode="graded", cluster=4, branching=B, cap=cap)[0])
+        n_run.append(n_out if nr is None else nr)
+    batch = snd.Batch(plans)
+    for w in batch.workspaces:
+        w.fill_(255)
+    outs = [p.empty_output("cuda") for p in plans]
+    for o in outs:
+        o.zero_()
+    batch.execute(xs, outs, n_run=n_run)
+    torch.cuda.synchronize()
+    for i, (p, x, o, want, nr) in enumerate(zip(plans, xs, outs, wants, n_run)):
+        y = to_np(o)[:, :nr]
+        assert np.array_equal(y, want[:, :nr].astype(y.dtype)), i
+        assert np.array_equal(y, to_np(p.execute(x))[:, :nr]), i

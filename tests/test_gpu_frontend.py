@@ -233,3 +233,27 @@ def test_time_major_tiles(snd, orc, nchan, n):
         bits = np.unpackbits(words.cpu().numpy().view(np.uint8), axis=1, bitorder="little")
         pad = (n + 31) // 32 * 32
         assert np.array_equal(bits[:, :n], want1) and np.all(bits[:, n:pad] == 0) and np.all(bits[:, pad:] == 1)
+
+
+@pytest.mark.parametrize("n", [97, 4096, 5003])
+def test_non_finite_samples(snd, orc, n):
+    """NaNs and infinities through the casts, the scrunch, the normalisation and zero-DM subtraction (a NaN
+    never exceeds gamma, an infinite sum does): the oracle's values, NaNs where it has them."""
+    rng = synth.make_rng(n)
+    z = rng.standard_normal((9, n)).astype(np.float32)
+    z[0, n // 2], z[1, 3], z[2, n - 1], z[8, :: 5] = np.nan, np.inf, -np.inf, np.nan
+    zt = torch.from_numpy(z).cuda()
+    for dt, tt in (("bf16", torch.bfloat16), ("f16", torch.float16)):
+        got, want = snd.cast(zt, dt).cpu().float().numpy(), torch.from_numpy(z).to(tt).float().numpy()
+        assert np.array_equal(got, want, equal_nan=True)
+    st = np.stack([np.linspace(-1.0, 1.0, 9), np.linspace(0.5, 2.0, 9)], axis=1)
+    with np.errstate(invalid="ignore"):
+        for s in (1, 2, 4, 5, 8, 16):
+            assert np.array_equal(snd.scrunch(zt, s).cpu().numpy(), orc.scrunch(z, s), equal_nan=True)
+        assert np.array_equal(snd.normalize(zt, torch.from_numpy(st).cuda()).cpu().numpy(), orc.normalize(z, st),
+                              equal_nan=True)
+        y = zt.clone()
+        cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+        snd.zero_dm(y, 1.5, count=cnt)
+        want, hits = orc.zero_dm(z, 1.5)
+    assert np.array_equal(y.cpu().numpy(), want, equal_nan=True) and int(cnt.item()) == hits

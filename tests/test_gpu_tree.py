@@ -694,3 +694,55 @@ def test_float_rows_of_few_dms_in_short_tiles(snd, orc, n_out):
             assert np.all(y[:, :3] == -3.0) and np.all(y[:, 3 + n_out:] == -3.0)
     want, _ = orc.snd_dedup(x, f, d, mode="float", cluster=4, branching=4)
     assert np.array_equal(long, want.astype(np.float32))
+
+
+@pytest.mark.parametrize("mode,nchan,B,ndm,top,n_out,direct", [
+    ("float", 64, 4, 600, 400.0, 2200, True), ("float", 64, 4, 600, 800.0, 2049, True),
+    ("float", 64, 8, 700, 800.0, 1537, True), ("float", 100, 4, 600, 800.0, 2050, True),
+    ("float", 37, 2, 600, 800.0, 2049, True), ("float", 16, 4, 1000, 800.0, 1100, True),
+    ("float", 7, 3, 1300, 400.0, 1025, True), ("float", 100, 2, 600, 800.0, 2100, True),
+    ("float", 128, 2, 400, 800.0, 3073, True), ("graded", 64, 4, 600, 400.0, 2200, True),
+    ("graded", 64, 2, 650, 800.0, 2047, True), ("graded", 64, 8, 1000, 800.0, 1030, True),
+    ("graded", 128, 4, 600, 800.0, 6001, True), ("graded", 16, 2, 1100, 400.0, 1024, True),
+    ("graded", 128, 2, 600, 800.0, 2000, False), ("graded", 100, 2, 600, 800.0, 2000, False),
+    ("float", 128, 3, 400, 800.0, 3000, False), ("float", 64, 2, 600, 800.0, 2000, False),
+])
+def test_sparse_dms_every_form_of_the_one_stage_schedule(snd, orc, mode, nchan, B, ndm, top, n_out, direct):
+    """DM grids in equal ratios, large enough for the one-stage schedule: regular and ragged trees, the
+    specialised and the general row-group kernel, whole and partial groups and tiles; and the shapes that
+    stay on the leaf plane.  A plain execution that takes the tree from the input leaves the workspace's
+    0xFF fill as it is; the same call on rows off 16 bytes and the stages in order give the same bits, the
+    generic kernels the same sums, and the oracle's sums at 500 cells (exactly, graded)."""
+    f = synth.channel_freqs(nchan)
+    dms = np.geomspace(2.0, top, ndm)
+    d = orc.delays(f, dms, 0.138e-3)
+    nsamp = int(d.max()) + n_out
+    rng = synth.make_rng(nchan * 31 + ndm + B)
+    x = rng.standard_normal((nchan, nsamp)).astype(np.float32) if mode == "float" else \
+        rng.integers(0, 90, (nchan, nsamp), dtype=np.uint8)
+    kw = dict(mode=mode, branching=B, cap=200)
+    p = snd.Plan(f, dms, 0.138e-3, nsamp, **kw)
+    _say(f"one-stage schedule mode={mode} nchan={nchan} B={B} ndm={ndm} n_out={n_out} {p.info['stage_kernel']}")
+    pitch = (nsamp + 31) // 16 * 16
+    ws = p.workspace(torch.device("cuda"))
+    ys = []
+    for first, row in ((0, pitch), (1, pitch), (0, pitch + 1)):
+        block = torch.zeros(nchan * row + 16, dtype=torch.from_numpy(x).dtype, device="cuda")
+        view = block[first:first + nchan * row].view(nchan, row)[:, :nsamp]
+        view.copy_(torch.from_numpy(x))
+        ws.fill_(255)
+        ys.append(to_np(p.execute(view, workspace=ws)))
+        assert bool((ws == 255).all()) == (direct and first == 0 and row == pitch)
+    ys.append(gpu_run(p, x, stage_by_stage=True))
+    for y in ys[1:]:
+        assert np.array_equal(ys[0], y)
+    ks, ts = rng.integers(0, ndm, 500), rng.integers(0, p.n_out, 500)
+    ks[:2], ts[:2] = (0, ndm - 1), (0, p.n_out - 1)
+    want = orc.snd_points(x, f, d, ks, ts, cluster=4, **kw)
+    if mode == "graded":
+        assert np.array_equal(ys[0][ks, ts], want.astype(ys[0].dtype))
+    else:
+        assert rel_rms(ys[0][ks, ts], want) <= FP32_TOL
+    pg = snd.Plan(f, dms, 0.138e-3, nsamp, generic_kernels=True, **kw)
+    y = gpu_run(pg, x)
+    assert np.array_equal(y, ys[0]) if mode == "graded" else rel_rms(y, ys[0]) <= FP32_TOL
