@@ -531,3 +531,33 @@ def test_rows_on_any_element(snd, orc, dtype, n):
             det = snd.Detector(p, [1, 3, 4, 60], threshold=1.0, closing_radius=0, n_min=1)
             assert not any(c["k"] in (1, 2) for c in det.run(bad))
             assert not det.snr_plane(bad)[0][1:3].any()
+
+
+@pytest.mark.parametrize("widths", [[1], [1, 2, 4, 8, 16, 32, 64], [3, 150]])
+def test_float_row_ends_in_one_tile(snd, orc, widths):
+    """Float rows whose last tile is longer than the ones before it, by up to the list's halo: the plane and
+    the cells at every sample against the oracle, alone and in a batch of rows of all lengths."""
+    lens = [1, 1856, 1857, 1984, 1985, 2034, 2048, 2049, 3968, 4032, 4033, 6017]
+    plans, planes, wants = [], [], []
+    for i, n in enumerate(lens):
+        rng = synth.make_rng(1000 + n)
+        plane = rng.standard_normal((3, n)).astype(np.float32)
+        plane[1, -4:] += np.float32(9)
+        plane[2, n - n // 8: n - n // 8 + 4] += np.float32(9)
+        p = snd.Plan(synth.channel_freqs(4), np.zeros(3), 0.138e-3, n, mode="float", branching=2)
+        dev = torch.from_numpy(plane).cuda()
+        o_snr, o_widx, _, _ = orc.matched_filter(plane.astype(np.float64), widths, integer_plane=False)
+        det = snd.Detector(p, widths, threshold=2.0, closing_radius=0, n_min=1)
+        snr, widx = det.snr_plane(dev)
+        # float prefix sums agree to FP64 rounding, which the plane's float32 may round either way
+        assert np.allclose(snr.cpu().numpy(), o_snr, rtol=2e-7, atol=1e-12), n
+        assert np.array_equal(widx.cpu().numpy(), o_widx), n
+        want = [(w["k"], w["t"], w["widx"], w["npix"])
+                for w in orc.candidates(o_snr, o_widx, 2.0, radius=0, n_min=1)]
+        assert [(g["k"], g["t"], g["widx"], g["npix"]) for g in det.run(dev)] == want, n
+        assert det.npixels == int((o_snr >= 2.0).sum()), n
+        plans.append(p), planes.append(dev), wants.append(want)
+    bd = snd.BatchDetector(widths, threshold=2.0, closing_radius=0, n_min=1)
+    got = bd.collect(bd.launch(plans, planes))
+    for n, g, want in zip(lens, got, wants):
+        assert [(c["k"], c["t"], c["widx"], c["npix"]) for c in g] == want, n
