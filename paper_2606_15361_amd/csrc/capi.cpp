@@ -222,6 +222,7 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
         g.n_run = (int32_t)run.n_run;
         g.len_cut = len_cut;
         g.tile = S.anchor_tile;
+        g.spread = S.spread;
         if (bound && si == 0 && P.bound_off >= 0) g.bound_slots = reinterpret_cast<uint32_t *>(ws + P.bound_off);
         pr.shape = stage_shape(S);
         pr.nblocks = S.ntiles;

@@ -185,7 +185,9 @@ __device__ __forceinline__ void leaf_dwords(const unsigned char *lds, const uint
 // With that and the packed u8 sums the leaf stage went from 1.60 to 1.35 ms (u8, 1024 channels x
 // 4096 DMs x 131,072 samples; its stores alone need 0.9), 476 to 331 us (u8, 64 channels x 3000
 // DMs; row ends by the same dwords: 100 channels, 600 rows of 580 samples 38 us, one by one 40, now 36), and for eight beams of 8192 samples from 0.80 to 0.73 ms (u8) and 1.18 to 1.06 (bf16).
-template <int MODE, typename TI, typename TO, int MAXD>
+// REC: rows by records, in one-level stages.  Without, a row reads its words from the plan's row and entry
+// tables, which holds its stores back: the better form where those alone set the pace (see tables_pay).
+template <int MODE, typename TI, typename TO, int MAXD, bool REC>
 __global__ __launch_bounds__(64 * kAnchorWaves, MAXD == 1 ? 8 : 4) void k_anchored(AnchorArgs s0, Multi m)
 {
     using A = typename Acc<MODE>::type;
@@ -248,31 +250,37 @@ __global__ __launch_bounds__(64 * kAnchorWaves, MAXD == 1 ? 8 : 4) void k_anchor
     // one-level rows: everything a row needs in one record, the next row's on its way while one is
     // summed
     constexpr bool kLeaf = MAXD == 1 && !std::is_same<TO, bits_t>::value;
+    constexpr bool kRec = kLeaf && REC;
     typedef int32_t rec_t __attribute__((ext_vector_type(8)));
     const_ptr<rec_t> leaf = as_const(reinterpret_cast<const rec_t *>(s.leaf));
     rec_t next{};
-    if (kLeaf && r0 + wave < r1) next = leaf[r0 + wave];
+    if (kRec && r0 + wave < r1) next = leaf[r0 + wave];
     for (int r = r0 + wave; r < r1; r += kAnchorWaves) {
         const rec_t rec = next;
-        if (kLeaf && r + kAnchorWaves < r1) next = leaf[r + kAnchorWaves];
-        const int lo = kLeaf ? rec[0] : row_lo[r], len = (kLeaf ? rec[1] : row_len[r]) - s.len_cut;
-        const uint32_t eb = kLeaf ? (uint32_t)rec[6] : row_ptr[r], ee = kLeaf ? eb + (uint32_t)rec[7] : row_ptr[r + 1];
-        if constexpr (kLeaf) if (ee - eb == (uint32_t)EU && c1 - c0 <= 256) {
+        if (kRec && r + kAnchorWaves < r1) next = leaf[r + kAnchorWaves];
+        const int lo = kRec ? rec[0] : row_lo[r], len = (kRec ? rec[1] : row_len[r]) - s.len_cut;
+        const uint32_t eb = kRec ? (uint32_t)rec[6] : row_ptr[r], ee = kRec ? eb + (uint32_t)rec[7] : row_ptr[r + 1];
+        if constexpr (kLeaf) if (ee - eb == (uint32_t)EU && (!kRec || c1 - c0 <= 256)) {
             // rows of EU inputs (the leaf level of clusters of four channels; a record's channel
             // field has 8 bits): stores without per-sample tests inside the row
             // rows of 1- or 2-byte elements: lane i owns the PK consecutive samples PK i + j
             // + 64 PK w (j < PK) of a sub-tile, so that each store writes a whole dword
             constexpr int PK = sizeof(TO) < 4 ? 4 / (int)sizeof(TO) : 1;
             static_assert(V % PK == 0, "whole dwords per lane");
-            constexpr bool kPacked = MODE == SND_MODE_GRADED && sizeof(TI) == 1 && sizeof(TO) == 1;
+            constexpr bool kPacked = kRec && MODE == SND_MODE_GRADED && sizeof(TI) == 1 && sizeof(TO) == 1;
             const TI *p[EU];
-#pragma unroll
-            for (int u = 0; u < EU; ++u)
-                p[u] = lds + PK * lane + (int)((uint32_t)rec[2 + u] >> 24) * wst + (rec[2 + u] & (int)kRowMask);
             uint32_t at[EU];  // byte offset of each input's first sample at the window's start
 #pragma unroll
-            for (int u = 0; u < EU; ++u)
-                at[u] = (uint32_t)((int)((uint32_t)rec[2 + u] >> 24) * wst + (rec[2 + u] & (int)kRowMask)) * (uint32_t)sizeof(TI);
+            for (int u = 0; u < EU; ++u) {
+                if constexpr (kRec) {
+                    const int first = (int)((uint32_t)rec[2 + u] >> 24) * wst + (rec[2 + u] & (int)kRowMask);
+                    p[u] = lds + PK * lane + first;
+                    at[u] = (uint32_t)first * (uint32_t)sizeof(TI);
+                } else {
+                    p[u] = lds - lo + PK * lane + ((int)(ent[2 * (eb + u)] & kRowMask) - c0) * wst +
+                           (int32_t)ent[2 * (eb + u) + 1];
+                }
+            }
             // sample slot v of the lane: offset PK lane + off(v) in the sub-tile
             auto off = [](int v) { return (v % PK) + 64 * PK * (v / PK); };
             for (int sub = 0; sub < T; sub += ST) {
@@ -488,6 +496,22 @@ int launch_group_typed(const GroupArgs &a, int64_t n_out, int lds, hipStream_t s
     return (int)hipGetLastError();
 }
 
+// One-level rows of f32, f16 and u16 samples that spread their node's channels wide and are long: their
+// stores go to more of the plane at a time, the faster they are issued, and the memory takes them the slower
+// for it.  The lines, in samples of spread and of output, both sides measured over 64 to 1024 channels and
+// 5000 to 102,748 samples.  64 channels x 70,000 samples, 2500 DMs to 1500 (spread 1000, 48,747 out): f32 1027
+// us by records, 948 by tables, f16 642 and 581, u16 615 and 523.  Inside the lines: f32 at 64 channels
+// and 10,000 out 158 and 207, 1024 channels the same; f16 at 20,000 out 204 and 236; u16 of 1024 channels to
+// 800 (spread 33) and 100,000 out 752 and 830.  bf16 rows and the packed u8 ones are bound by their sums.
+template <typename TO>
+bool tables_pay(const AnchorArgs &a)
+{
+    if (std::is_same<TO, float>::value) return a.spread >= 300 && a.n_run >= 18000;
+    if (std::is_same<TO, f16_t>::value) return a.spread >= 400 && a.n_run >= 28000;
+    if (std::is_same<TO, uint16_t>::value) return a.spread >= 60 && a.n_run >= 28000;
+    return false;
+}
+
 template <int MODE, typename TI, typename TO>
 int launch_anchored_typed(const AnchorArgs &a, int64_t ntiles, int lds, hipStream_t st, const Multi &m)
 {
@@ -495,10 +519,17 @@ int launch_anchored_typed(const AnchorArgs &a, int64_t ntiles, int lds, hipStrea
     if (ntiles > 0x7fffffffLL || a.depth > 8) return (int)hipErrorInvalidValue;
     if (a.tile < kAnchorTile || a.tile % kAnchorTile) return (int)hipErrorInvalidValue;
     dim3 grid((uint32_t)ntiles), block(64 * kAnchorWaves);
-    if (a.depth <= 1) hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 1>), grid, block, lds, st, a, m);
-    else if (a.depth <= 2) hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 2>), grid, block, lds, st, a, m);
-    else if (a.depth <= 4) hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 4>), grid, block, lds, st, a, m);
-    else hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 8>), grid, block, lds, st, a, m);
+    constexpr bool kTables = std::is_same<TO, float>::value || std::is_same<TO, f16_t>::value ||
+                             std::is_same<TO, uint16_t>::value;
+    if constexpr (kTables)
+        if (a.depth <= 1 && m.n == 0 && tables_pay<TO>(a)) {
+            hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 1, false>), grid, block, lds, st, a, m);
+            return (int)hipGetLastError();
+        }
+    if (a.depth <= 1) hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 1, true>), grid, block, lds, st, a, m);
+    else if (a.depth <= 2) hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 2, false>), grid, block, lds, st, a, m);
+    else if (a.depth <= 4) hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 4, false>), grid, block, lds, st, a, m);
+    else hipLaunchKernelGGL((k_anchored<MODE, TI, TO, 8, false>), grid, block, lds, st, a, m);
     return (int)hipGetLastError();
 }
 

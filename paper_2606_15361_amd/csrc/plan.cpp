@@ -567,6 +567,7 @@ bool build_anchored(const PlanImpl &p, Stage &S)
         }
         if (bits && n.tlo % 64 != 0) return false;
         worst = std::max<int64_t>(worst, (int64_t)(n.c1 - n.c0) * n.rho_max);
+        S.spread = std::max(S.spread, n.rho_max);
         chan_max = std::max<int64_t>(chan_max, n.c1 - n.c0);
         ns.push_back(n);
     }

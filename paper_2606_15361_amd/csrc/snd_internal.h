@@ -96,6 +96,7 @@ struct Stage {
     // node << 24 | offset past row_lo; the first four), first entry, entries
     std::vector<int32_t> leaf;
     int32_t anchor_tile = 0;        // reference samples per workgroup window
+    int32_t spread = 0;             // largest delay difference between the inputs of a row
     int64_t off_nodes = 0, off_tiles = 0, off_row_lo = 0, off_leaf = 0;
     int64_t ntiles = 0;
 };
@@ -380,6 +381,7 @@ struct AnchorArgs {
     int32_t n_run;    // output samples of this run (<= n_out)
     int32_t len_cut;  // n_out - n_run: samples dropped from the end of every row
     int32_t tile;     // reference samples per workgroup window (a multiple of kAnchorTile)
+    int32_t spread;   // largest delay difference inside a row (see Stage)
     // graded u8 output: one word per workgroup receives the largest value it computed, and
     // the word after the last the largest of them all (k_bound_reduce); nullptr: not tracked
     uint32_t *bound_slots;

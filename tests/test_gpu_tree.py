@@ -746,3 +746,39 @@ def test_sparse_dms_every_form_of_the_one_stage_schedule(snd, orc, mode, nchan, 
     pg = snd.Plan(f, dms, 0.138e-3, nsamp, generic_kernels=True, **kw)
     y = gpu_run(pg, x)
     assert np.array_equal(y, ys[0]) if mode == "graded" else rel_rms(y, ys[0]) <= FP32_TOL
+
+
+@pytest.mark.parametrize("mode,nchan,dmax,around", [
+    ("f32", 64, 1500.0, 18000), ("f32", 30, 700.0, 18000), ("f16", 64, 1500.0, 28000), ("u16", 64, 1500.0, 28000),
+    ("u16", 512, 900.0, 28000)])
+def test_leaf_rows_by_records_and_by_tables(snd, orc, mode, nchan, dmax, around):
+    """Widely spread leaf rows on both sides of the length from which their words are read from the row and
+    entry tables, ragged and unaligned: whole numbers, whose sums are exact in each type, so the planes equal
+    the generic kernels' bit for bit, and the first samples those of the shorter block."""
+    f = synth.channel_freqs(nchan)
+    dms = np.linspace(0.0, dmax, 21)
+    dmaxd = int(orc.delays(f, dms, 0.138e-3).max())
+    rng = synth.make_rng(nchan + around)
+    n = dmaxd + around + 1
+    hi = 3 if mode == "f16" else 12
+    x = rng.integers(0, hi, (nchan, n + 7))
+    x = x.astype(np.uint8) if mode == "u16" else x.astype(np.float32)
+    xt = torch.from_numpy(x).cuda()
+    if mode == "f16":
+        xt = xt.half()
+    kw = dict(mode="graded", cap=700, node_dtype="u16") if mode == "u16" else \
+        dict(mode="float", in_dtype=mode, node_dtype=mode)
+    first = None
+    for n_out in (around - 1, around, around + 1):
+        nsamp = dmaxd + n_out
+        p = snd.Plan(f, dms, 0.138e-3, nsamp, **kw)
+        pg = snd.Plan(f, dms, 0.138e-3, nsamp, generic_kernels=True, **kw)
+        assert p.info["stage_kernel"][0] == "anchored" and p.n_out == n_out
+        for off in (0, 3):
+            _say(f"leaf rows mode={mode} nchan={nchan} n_out={n_out} off={off}")
+            view = xt[:, off:off + nsamp]
+            y = to_np(p.execute(view))
+            assert np.array_equal(y, to_np(pg.execute(view)))
+            if off == 0:
+                first = y if first is None else first
+                assert np.array_equal(y[:, :around - 1], first)
