@@ -509,14 +509,16 @@ int launch_pack(const GroupArgs &a, int64_t n_out, int lds, void *stream, const 
 }  // namespace
 
 // Every (inputs per level-1 node, depth) pair the plan builder admits for this kernel, and with
-// irregular nodes every (depth, levels above the super nodes).
+// irregular nodes every (depth, levels above the super nodes).  A tree of one level has no wide path: its
+// nodes are single level-1 nodes, which the byte sums serve as they are (16 channels, 300 DMs x 29,987
+// samples: 10.8 us by super nodes, 9.6).
 int launch_group_pack(const GroupArgs &a, int64_t n_out, int lds, void *stream, const Multi &m, int64_t nblocks)
 {
     const int u = a.depth - a.wide_level;
 #define SND_PACK(F, DD, UU) \
     if (a.f1 == F && a.depth == DD && (UU < 0 || u == UU)) \
         return launch_pack<F, DD, UU>(a, n_out, lds, stream, m, nblocks);
-    SND_PACK(4, 1, 0) SND_PACK(4, 2, 0) SND_PACK(4, 3, 1) SND_PACK(4, 4, 2) SND_PACK(4, 5, -1)
+    SND_PACK(4, 1, -1) SND_PACK(4, 2, 0) SND_PACK(4, 3, 1) SND_PACK(4, 4, 2) SND_PACK(4, 5, -1)
     SND_PACK(8, 1, -1) SND_PACK(8, 2, -1) SND_PACK(8, 3, -1) SND_PACK(8, 4, -1)
     SND_PACK(0, 1, 0)
     SND_PACK(0, 2, 0) SND_PACK(0, 2, 1)

@@ -782,3 +782,26 @@ def test_leaf_rows_by_records_and_by_tables(snd, orc, mode, nchan, dmax, around)
             if off == 0:
                 first = y if first is None else first
                 assert np.array_equal(y[:, :around - 1], first)
+
+
+@pytest.mark.parametrize("top,cap", [(63, 255), (64, 255), (40, 100)])
+def test_graded_packed_trees_of_one_level(snd, orc, top, cap):
+    """Sixteen channels in fours: one level of four leaves in the packed kernel, as bytes up to four times 63
+    and as 16-bit counts past it, under a cap that acts and one that does not, with a ragged last tile."""
+    f = synth.channel_freqs(16)
+    dms = np.linspace(0.0, 3.0, 300)
+    d = orc.delays(f, dms, 0.138e-3)
+    n_out = 16 * 1008 + 77
+    nsamp = int(d.max()) + n_out
+    rng = synth.make_rng(16 + top)
+    x = rng.integers(0, top // 4, (16, nsamp), dtype=np.uint8)
+    x[:, 500:900] = top // 4
+    x[::4, 500:900] += top % 4
+    p = snd.Plan(f, dms, 0.138e-3, nsamp, mode="graded", branching=4, cap=cap)
+    assert p.info["stage_kernel"] == ["anchored", "group_pack"]
+    xt = torch.from_numpy(x).cuda()
+    ws = p.workspace(xt.device)
+    ws.fill_(255)
+    y = to_np(p.execute(xt, workspace=ws))
+    want, _ = orc.snd_dedup(x, f, d, mode="graded", cluster=4, branching=4, cap=cap)
+    assert np.array_equal(y, want.astype(y.dtype))
