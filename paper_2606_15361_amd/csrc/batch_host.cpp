@@ -24,7 +24,7 @@ using ClassKey = std::tuple<int, int, int, int, int>;  // kind, mode, src dtype,
 
 ClassKey class_key(const PlanImpl &P, size_t si)
 {
-    const Stage &S = P.stages[si];
+    const Stage &S = si == kAloneStage ? P.alone[0] : P.stages[si];
     return ClassKey{S.kernel, P.desc.mode, S.src_dtype, S.dst_dtype, stage_shape(S)};
 }
 
@@ -41,8 +41,27 @@ int64_t class_bytes(int kind, int64_t n)
     return round_up(round_up((int64_t)args_size(kind) * n, 16) + 4 * (n + 1), 256);
 }
 
+// Jobs whose final stage takes the form for launches of their plan alone: those whose packed grid, all beams
+// of its class together, stays below the line of a single launch (kPackMinBlocks; pushes of 250 channels,
+// 120 DMs x 2000 samples, one beam 51 us on the packed kernel, 37 so, three 67 and 53).
+std::vector<char> alone_jobs(const std::vector<Job> &jobs)
+{
+    std::map<ClassKey, int64_t> blocks;
+    for (const Job &j : jobs) {
+        const Stage &S = j.P->stages.back();
+        if (S.group_pack && j.run.n_run > 0)
+            blocks[class_key(*j.P, j.P->stages.size() - 1)] +=
+                S.ngroups * ((j.run.n_run + S.group_tile - 1) / S.group_tile);
+    }
+    std::vector<char> alone;
+    for (const Job &j : jobs)
+        alone.push_back(!j.P->alone.empty() && blocks[class_key(*j.P, j.P->stages.size() - 1)] < kPackMinBlocks);
+    return alone;
+}
+
 }  // namespace
 
+// (enough for either form of the final stages that have two; grids as with the shared one)
 int64_t batch_record_bytes(const std::vector<const PlanImpl *> &plans, int *n_launches)
 {
     size_t waves = 0;
@@ -50,13 +69,16 @@ int64_t batch_record_bytes(const std::vector<const PlanImpl *> &plans, int *n_la
     int64_t bytes = 0;
     int nl = 0;
     for (size_t w = 0; w < waves; ++w) {
-        std::map<ClassKey, int64_t> cls;
-        for (const PlanImpl *P : plans)
+        std::map<ClassKey, int64_t> cls, alone;
+        for (const PlanImpl *P : plans) {
             if (w < P->stages.size()) cls[class_key(*P, w)] += 1;
+            if (w + 1 == P->stages.size() && !P->alone.empty()) alone[class_key(*P, kAloneStage)] += 1;
+        }
         for (const auto &kv : cls) {
             bytes += class_bytes(std::get<0>(kv.first), kv.second);
             ++nl;
         }
+        for (const auto &kv : alone) bytes += class_bytes(std::get<0>(kv.first), kv.second);
     }
     if (n_launches) *n_launches = nl;
     return bytes;
@@ -73,16 +95,20 @@ snd_status run_batch(const std::vector<Job> &jobs, void *d_records, int64_t reco
     }
     size_t waves = 0;
     for (const Job &j : jobs) waves = std::max(waves, j.P->stages.size());
+    const std::vector<char> alone = alone_jobs(jobs);
     uint8_t *rec = static_cast<uint8_t *>(d_records);
     std::vector<uint8_t> host;
     int nl = 0;
     for (size_t w = 0; w < waves; ++w) {
         std::map<ClassKey, std::vector<Prepared>> cls;
-        for (const Job &j : jobs) {
+        for (size_t i = 0; i < jobs.size(); ++i) {
+            const Job &j = jobs[i];
             if (w >= j.P->stages.size()) continue;
             if (j.run.n_run <= 0) continue;
-            cls[class_key(*j.P, w)].push_back(
-                prepare_stage(*j.P, w, j.run, j.in, j.in_pitch, j.out, j.out_pitch, j.ws, true));
+            const size_t si = alone[i] && w + 1 == j.P->stages.size() ? kAloneStage : w;
+            // (a final stage alone reads no bound)
+            cls[class_key(*j.P, si)].push_back(
+                prepare_stage(*j.P, si, j.run, j.in, j.in_pitch, j.out, j.out_pitch, j.ws, !alone[i]));
         }
         for (auto &kv : cls) {
             std::vector<Prepared> &v = kv.second;

@@ -179,8 +179,8 @@ constexpr int kPackReach = 1024 + 16;          // samples a two-row window holds
 // Irregular nodes, and regular ones whose windows nearly fill a buffer (more than kPackRoom bytes for one
 // node: a batch is then one node), take the packed kernel only in launches of at least this many
 // workgroups, about half the CUs: its groups are wider and its tiles longer than the other row-group
-// kernels', which leaves CUs idle on smaller grids.  (Streaming plans below that keep both: a push of
-// several beams shares one grid.)  Final stage of 1000 channels, against the general kernel: 100 DMs x 9042
+// kernels', which leaves CUs idle on smaller grids.  (Streaming plans below that keep both: the
+// beams of a batched push share one grid.)  Final stage of 1000 channels, against the general kernel: 100 DMs x 9042
 // samples (36 workgroups) 84 us, packed 185; 64 DMs x 30,014 (60) 99 and 155; 300 x 9042 (90) 142 and 150;
 // 100 x 30,042 (120) 188 and 186; 600 x 9042 (171) 233 and 138.  Of 256 channels, regular, DMs 1.3 apart,
 // against the specialised kernel: 600 x 2640 (57) 40 and 51; 200 x 30,047 (210) 76 and 52.

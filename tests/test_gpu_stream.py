@@ -342,8 +342,8 @@ def test_stream_bit_input_any_chunks(snd, orc):
 
 
 def test_ragged_graded_beams_alone_and_batched(snd, orc):
-    """Graded beams over irregular trees: a beam's push alone runs its small final stage on the general
-    kernel, a batched push on the packed one with each beam's own bound.  Chunks shorter than, equal to and
+    """Graded beams over irregular trees, whose pushes, alone or a few at a time, run their small final stages
+    on the general kernel.  Chunks shorter than, equal to and
     ragged against the plan's, history fill included, levels within the byte sums' bound and past it: both
     equal the oracle on the whole block, bit for bit."""
     beams = [(250, 4, 120, 1500, 3, 255), (97, 3, 300, 2100, 7, 255), (250, 4, 64, 1500, 40, 200),
@@ -380,3 +380,39 @@ def test_ragged_graded_beams_alone_and_batched(snd, orc):
             y = np.concatenate(rows[i], axis=1)
             assert y.shape[1] == 6000 - p.max_delay
             assert np.array_equal(y, wants[i][:, :y.shape[1]].astype(y.dtype)), (batched, i)
+
+
+def test_ragged_graded_beams_batched_in_large_grids(snd, orc):
+    """Batched pushes of many small graded beams: together their final stages fill a packed grid in full
+    chunks, with each beam's own bound (within the byte sums' and past it), and not in short ones, where each
+    takes the general kernel; either way as the oracle on the whole block, bit for bit."""
+    n, beams = 5000, [(97, 3, 300, 2100, top, 255) for top in (3, 7, 40, 3, 7)] + [(256, 4, 46, 1500, 4, 255)]
+    plans, srcs, wants = [], [], []
+    for i, (nchan, B, ndm, chunk, top, cap) in enumerate(beams):
+        f, dms = synth.channel_freqs(nchan), np.linspace(0.0, 60.0 + i, ndm)
+        plans.append(snd.Plan(f, dms, 0.138e-3, None, mode="graded", branching=B, cap=cap, chunk=chunk))
+        x = synth.random_levels(synth.make_rng(950 + i), nchan, n, top)
+        srcs.append(torch.from_numpy(np.ascontiguousarray(x)).cuda())
+        wants.append(orc.snd_dedup(x, f, orc.delays(f, dms, 0.138e-3), mode="graded", cluster=4, branching=B,
+                                   cap=cap)[0])
+    assert 4 * 10 * 3 < 128 <= 5 * 10 * 3  # packed workgroups of four and of five full chunks of the first kind
+    st = snd.Stream(1 << 34)
+    for i, p in enumerate(plans):
+        st.admit(i, p)
+    lens, rows, k = [2100, 1100, 900, 100, 1008], [[] for _ in beams], 0
+    rest = [0] * len(beams)
+    while min(rest) < n:
+        items = []
+        for i, p in enumerate(plans):
+            L = min(p.n_out, lens[k % len(lens)], n - rest[i])
+            if L > 0:
+                items.append((i, k, srcs[i][:, rest[i]:rest[i] + L], p.empty_output("cuda")))
+                rest[i] += L
+        k += 1
+        for (i, _, _, out), (_, m, status) in zip(items, st.push(items, batched=True)):
+            assert status == 0
+            rows[i].append(to_np(out[:, :m]))
+    for i, p in enumerate(plans):
+        y = np.concatenate(rows[i], axis=1)
+        assert y.shape[1] == n - p.max_delay
+        assert np.array_equal(y, wants[i][:, :y.shape[1]].astype(y.dtype)), i
