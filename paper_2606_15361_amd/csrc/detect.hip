@@ -613,12 +613,13 @@ __global__ __launch_bounds__(kThreads) void k_snr(const T *plane, int64_t pitch,
     // a row's last tile has no halo past it, so it may be as long as the slabs (1000 rows x 2034 samples,
     // the whole plane at seven widths: 40.0 us with a second tile of 50 samples, 26.7 in one)
     constexpr int kFull = kSlabs * kThreads;
-    const int64_t t0 = (int64_t)blockIdx.x * (IsInt<T>::value ? kFull : a.tile);
+    constexpr bool kWhole = IsInt<T>::value || PER == snr_per<T>(true);  // every tile is as long (see snr_tile)
+    const int64_t t0 = (int64_t)blockIdx.x * (kWhole ? kFull : a.tile);
     if constexpr (BATCH) {
         // past a shorter plane of the batch (uniform: before any barrier)
-        if (t0 >= n || (t0 > 0 && n - t0 + a.tile <= kFull)) return;
+        if (t0 >= n || (!kWhole && t0 > 0 && n - t0 + a.tile <= kFull)) return;
     }
-    const int tile = IsInt<T>::value || n - t0 <= kFull ? kFull : a.tile;  // (integer tiles are whole slabs)
+    const int tile = kWhole || n - t0 <= kFull ? kFull : a.tile;
     const T *row = rowk + t0;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // widths of this row: the first nwk of the list (all of them unless a DM-scaled set)
