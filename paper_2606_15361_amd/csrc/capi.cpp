@@ -2,6 +2,7 @@
 // schedule of one execute; all device arithmetic is in the HIP kernels.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -223,6 +224,7 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
         g.len_cut = len_cut;
         g.tile = S.anchor_tile;
         g.spread = S.spread;
+        g.node_rows = (int32_t)(S.rows * 6 / std::max<int64_t>(1, (int64_t)S.nodes.size()));  // (six words a node)
         if (bound && si == 0 && P.bound_off >= 0) g.bound_slots = reinterpret_cast<uint32_t *>(ws + P.bound_off);
         pr.shape = stage_shape(S);
         pr.nblocks = S.ntiles;

@@ -496,19 +496,21 @@ int launch_group_typed(const GroupArgs &a, int64_t n_out, int lds, hipStream_t s
     return (int)hipGetLastError();
 }
 
-// One-level rows of f32, f16 and u16 samples that spread their node's channels wide and are long: their
+// Many one-level rows of f32, f16 and u16 samples that spread their node's channels wide and are long: their
 // stores go to more of the plane at a time, the faster they are issued, and the memory takes them the slower
-// for it.  The lines, in samples of spread and of output, both sides measured over 64 to 1024 channels and
-// 5000 to 102,748 samples.  64 channels x 70,000 samples, 2500 DMs to 1500 (spread 1000, 48,747 out): f32 1027
-// us by records, 948 by tables, f16 642 and 581, u16 615 and 523.  Inside the lines: f32 at 64 channels
-// and 10,000 out 158 and 207, 1024 channels the same; f16 at 20,000 out 204 and 236; u16 of 1024 channels to
-// 800 (spread 33) and 100,000 out 752 and 830.  bf16 rows and the packed u8 ones are bound by their sums.
+// for it.  The lines, in samples of spread, samples of output and rows per node, both sides measured over 64 to
+// 1024 channels, 30 to 4096 DMs and 5000 to 102,748 samples.  64 channels x 70,000 samples, 2500 DMs to 1500
+// (spread 1000, 48,747 out): f32 1027 us by records, 948 by tables, f16 642 and 581, u16 615 and 523.  Inside
+// the lines: f32 at 64 channels and 10,000 out 158 and 207, 1024 channels the same, 128 channels x 81 rows 106
+// and 110 (120 rows 159 and 153); f16 at 20,000 out 204 and 236, 81 rows 33.4 and 34.6 (300 rows 118 and 110);
+// u16 of 1024 channels to 800 (spread 33) and 100,000 out 752 and 830, 512 channels x 100 rows 258 and 277
+// (400 rows 583 and 545).  bf16 rows and the packed u8 ones are bound by their sums.
 template <typename TO>
 bool tables_pay(const AnchorArgs &a)
 {
-    if (std::is_same<TO, float>::value) return a.spread >= 300 && a.n_run >= 18000;
-    if (std::is_same<TO, f16_t>::value) return a.spread >= 400 && a.n_run >= 28000;
-    if (std::is_same<TO, uint16_t>::value) return a.spread >= 60 && a.n_run >= 28000;
+    if (std::is_same<TO, float>::value) return a.spread >= 300 && a.n_run >= 18000 && a.node_rows >= 100;
+    if (std::is_same<TO, f16_t>::value) return a.spread >= 400 && a.n_run >= 28000 && a.node_rows >= 160;
+    if (std::is_same<TO, uint16_t>::value) return a.spread >= 60 && a.n_run >= 28000 && a.node_rows >= 160;
     return false;
 }
 

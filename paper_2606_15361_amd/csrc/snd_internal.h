@@ -382,6 +382,7 @@ struct AnchorArgs {
     int32_t len_cut;  // n_out - n_run: samples dropped from the end of every row
     int32_t tile;     // reference samples per workgroup window (a multiple of kAnchorTile)
     int32_t spread;   // largest delay difference inside a row (see Stage)
+    int32_t node_rows;  // rows of a node, on average
     // graded u8 output: one word per workgroup receives the largest value it computed, and
     // the word after the last the largest of them all (k_bound_reduce); nullptr: not tracked
     uint32_t *bound_slots;

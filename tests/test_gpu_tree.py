@@ -756,7 +756,7 @@ def test_leaf_rows_by_records_and_by_tables(snd, orc, mode, nchan, dmax, around)
     entry tables, ragged and unaligned: whole numbers, whose sums are exact in each type, so the planes equal
     the generic kernels' bit for bit, and the first samples those of the shorter block."""
     f = synth.channel_freqs(nchan)
-    dms = np.linspace(0.0, dmax, 21)
+    dms = np.linspace(0.0, dmax, 210 if nchan < 512 else 600)
     dmaxd = int(orc.delays(f, dms, 0.138e-3).max())
     rng = synth.make_rng(nchan + around)
     n = dmaxd + around + 1
