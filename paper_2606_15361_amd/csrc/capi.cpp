@@ -175,7 +175,8 @@ Prepared prepare_stage(const PlanImpl &P, size_t si, const Run &run, const void 
         g.node_closes = reinterpret_cast<const int32_t *>(tb + S.off_node_closes);
         g.lin_smem = reinterpret_cast<const uint32_t *>(tb + S.off_lin_smem);
         g.lin = reinterpret_cast<const uint32_t *>(tb + S.off_lin);
-        g.lin_kernel = S.group_lin ? (S.lin_short ? 3 : 1) : S.group_pack ? 2 : 0;
+        g.lin_kernel = S.group_lin ? 1 : S.group_pack ? 2 : 0;
+        g.lin_blocks = S.lin_blocks;
         g.xcd_chunk = S.xcd_chunk;
         g.ngroups = (int32_t)S.ngroups;
         g.n_entries = S.n_entries;

@@ -147,6 +147,50 @@ struct LinF32 : LinBase {
     }
 };
 
+// f32 rows, eight per wave: st[q * V + v] is sample lane + 64 v of row q, each read as a dword (stride-64
+// reads of two).
+struct LinDwords : LinBase {
+    using TI = float;
+    static constexpr int R = lin_rows(SND_DT_F32, kLinDwords), kRows = R, kStep = lin_tile(SND_DT_F32, kLinDwords);
+    static constexpr int V = kStep / 64;
+    static constexpr int kState = R * V;
+
+    static __device__ __forceinline__ void add_batch(float (&st)[kState], const unsigned char *buf,
+                                                     const uint32_t (&w)[1], int lane, const Carry &c,
+                                                     const GroupArgs &)
+    {
+        const uint32_t vw = w[0];
+        const int n = c.n;
+        const unsigned char *lane_base = buf + 4 * lane;
+        for (int i = 0; i < n; ++i) {
+#pragma unroll
+            for (int q0 = 0; q0 < R; q0 += 2) {
+                float x[2][V];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)vw, (q0 + u) * n + i);
+                    const float *p = reinterpret_cast<const float *>(lane_base + o);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) x[u][v] = p[64 * v];
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < V; ++v) st[(q0 + u) * V + v] += x[u][v];
+                __builtin_amdgcn_sched_barrier(0);  // two rows' reads at a time: all eight's spill
+            }
+        }
+    }
+    static __device__ __forceinline__ void store(const float (&st)[kState], int q, float *drow, int lane, int vt,
+                                                 const GroupArgs &s)
+    {
+        auto d = as_global(drow);
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (lane + 64 * v < vt) d[lane + 64 * v] = st[q * V + v] * s.scale;
+    }
+};
+
 // bf16 / f16 rows: st[LO + q * V + v] and st[HI + q * V + v] are samples 2 lane + 128 v and
 // 2 lane + 1 + 128 v of row q.  An input whose first sample starts a dword is read as one
 // dword per pair; one whose first sample sits in the upper half of a dword as the upper half of
@@ -155,7 +199,7 @@ struct LinF32 : LinBase {
 template <bool F16>
 struct Lin16 : LinBase {
     using TI = uint16_t;
-    static constexpr int R = lin_rows(SND_DT_BF16), kRows = R, kStep = lin_tile(SND_DT_BF16);
+    static constexpr int R = lin_rows(SND_DT_BF16), kRows = R, kStep = lin_tile(SND_DT_BF16, 0);
     static constexpr int V = kStep / 128;
     static constexpr int LO = 0, HI = R * V, kState = 2 * R * V;
 
@@ -322,10 +366,33 @@ struct Lin16 : LinBase {
 
 }  // namespace
 
+// The last tile of a launch takes as few blocks as hold its samples, one or two (see lin_blocks; 1024
+// channels x 4096 DMs x 16,384 samples, eight tiles twice and half a block: 1430 us with all four, 1376 so).
+template <class Sum>
+struct LastTile {
+    static __device__ __forceinline__ void run(const GroupArgs &s, uint32_t bid, uint32_t nblk, int)
+    {
+        group_tab_run<Sum>(s, bid, nblk);
+    }
+};
+template <int V>
+struct LastTile<LinF32<V>> {
+    static __device__ __forceinline__ void run(const GroupArgs &s, uint32_t bid, uint32_t nblk, int left)
+    {
+        if (left <= kLinBlock) group_tab_run<LinF32<1>, V * kLinBlock>(s, bid, nblk);
+        else if (V > 2 && left <= 2 * kLinBlock) group_tab_run<LinF32<2>, V * kLinBlock>(s, bid, nblk);
+        else group_tab_run<LinF32<V>>(s, bid, nblk);
+    }
+};
+
 template <class Sum>
 __global__ __launch_bounds__(1024) void k_group_lin(GroupArgs s0, Multi m)
 {
-    group_tab_body<Sum>(s0, m);
+    GroupArgs s;
+    uint32_t bid, nblk;
+    select_record(s0, m, s, bid, nblk);
+    const int t0 = (int)(xcd_remap_chunked(bid, nblk, (uint32_t)s.xcd_chunk) / (uint32_t)s.ngroups) * Sum::kStep;
+    LastTile<Sum>::run(s, bid, nblk, s.n_out - t0);
 }
 
 namespace {
@@ -348,8 +415,12 @@ int launch_group_lin(int src_dt, const GroupArgs &a, int64_t n_out, int lds, voi
 {
     switch (src_dt) {
     case SND_DT_F32:
-        if (a.lin_kernel == 3) return launch_lin<LinF32<kLinShortTile / kLinBlock>>(a, n_out, lds, stream, m, nblocks);
-        return launch_lin<LinF32<lin_tile(SND_DT_F32) / kLinBlock>>(a, n_out, lds, stream, m, nblocks);
+        switch (a.lin_blocks) {
+        case 2: return launch_lin<LinF32<2>>(a, n_out, lds, stream, m, nblocks);
+        case 4: return launch_lin<LinF32<4>>(a, n_out, lds, stream, m, nblocks);
+        case kLinDwords: return launch_lin<LinDwords>(a, n_out, lds, stream, m, nblocks);
+        default: return (int)hipErrorInvalidValue;
+        }
     case SND_DT_BF16: return launch_lin<Lin16<false>>(a, n_out, lds, stream, m, nblocks);
     case SND_DT_F16: return launch_lin<Lin16<true>>(a, n_out, lds, stream, m, nblocks);
     default: return (int)hipErrorInvalidValue;

@@ -16,14 +16,15 @@
 
 namespace snd {
 
-// The pipeline for workgroup bid of nblk over the arguments s (its record, already selected).
-template <class Sum>
+// The pipeline for workgroup bid of nblk over the arguments s (its record, already selected).  T: samples of
+// the launch's tiles (a Sum of fewer serves a last tile that it covers).
+template <class Sum, int T = Sum::kStep>
 __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, uint32_t nblk)
 {
     using TI = typename Sum::TI;
     using A = typename Sum::A;
     constexpr int ES = (int)sizeof(TI);
-    constexpr int R = Sum::kRows, T = Sum::kStep, NW = Sum::kWords, NSM = Sum::kSmemWords;
+    constexpr int R = Sum::kRows, NW = Sum::kWords, NSM = Sum::kSmemWords;
     constexpr int WPL = NW / 64;  // offset words per lane
     static_assert(WPL == 1 || WPL == 4, "one load of 4 or 16 bytes per lane");
     extern __shared__ __align__(16) unsigned char smem[];
@@ -129,15 +130,6 @@ __device__ __forceinline__ void group_tab_run(const GroupArgs &s, uint32_t bid, 
         if (row[q] < 0) continue;
         Sum::store(st, q, static_cast<typename Sum::TO *>(s.dst) + (int64_t)row[q] * s.dst_pitch + t0, lane, vt, s);
     }
-}
-
-template <class Sum>
-__device__ __forceinline__ void group_tab_body(const GroupArgs &s0, const Multi &m)
-{
-    GroupArgs s;
-    uint32_t bid, nblk;
-    select_record(s0, m, s, bid, nblk);
-    group_tab_run<Sum>(s, bid, nblk);
 }
 
 }  // namespace snd

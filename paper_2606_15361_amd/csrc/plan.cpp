@@ -110,7 +110,7 @@ bool valid_dtype_pair(int mode, int in_dt, int node_dt, int cap)
 // to 16 inputs and depth <= 4: the linear kernel's staging, levels formed on bytes and pairs of 16-bit
 // counts).
 enum { kGroupGeneric = 0, kGroupFast = 1, kGroupLin = 2, kGroupPack = 3 };
-bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
+bool build_group_lds(const PlanImpl &p, Stage &S, int variant, int blocks = 4)
 {
     const bool allow_fast = variant == kGroupFast || variant == kGroupPack;
     const bool lin = variant == kGroupLin;
@@ -183,16 +183,15 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     if (bits && !f1) return false;  // bit rows: specialised kernel only
     // samples a window holds beyond its span (its tile, plus one unit for the linear kernel on
     // 16-bit rows), and the tile step in time
-    const bool lin_short = lin && S.src_dtype == SND_DT_F32 && rows <= kGroupRows * lin_rows(S.src_dtype) &&
-                           (p.n_out + lin_tile(S.src_dtype) - 1) / lin_tile(S.src_dtype) < kLinMinBlocks;
-    const int tile = lin    ? (lin_short ? kLinShortTile + 4 : lin_cover(S.src_dtype))
+    const int lin_blocks = lin && S.src_dtype == SND_DT_F32 ? blocks : 0;
+    const int tile = lin    ? lin_cover(S.src_dtype, lin_blocks)
                      : pack ? (pack_rows(f1, S.depth) == 2 ? kPackReach : pack_tile(f1, S.depth) + 16)
                      : bits ? kGroupTileBits
                      : f1   ? kGroupTileFast
                             : kGroupTile;
-    const int tile_step = lin ? (lin_short ? kLinShortTile : lin_tile(S.src_dtype)) : pack ? pack_tile(f1, S.depth) : tile;
-    const int rpw = lin ? lin_rows(S.src_dtype) : pack ? pack_rows(f1, S.depth) : f1 ? kFastRows : 1;  // rows per wave
-    const int max_entries = lin ? lin_max_batch_entries(S.src_dtype) : kPackMaxBatchEntries;  // table kernels
+    const int tile_step = lin ? lin_tile(S.src_dtype, lin_blocks) : pack ? pack_tile(f1, S.depth) : tile;
+    const int rpw = lin ? lin_rows(S.src_dtype, lin_blocks) : pack ? pack_rows(f1, S.depth) : f1 ? kFastRows : 1;  // rows per wave
+    const int max_entries = lin ? lin_max_batch_entries(S.src_dtype, lin_blocks) : kPackMaxBatchEntries;  // table kernels
     const int n_words = lin ? kLinWords : kPackWords;
     const int n_smem = lin ? kLinSmemWords : kPackSmemWords;
     const int gr = kGroupRows * rpw;     // rows per group
@@ -289,6 +288,9 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
         int64_t need = 0;
         for (const Src &s : unit_srcs) need += slot_elems(s.lo, s.hi - s.lo);
         if (need > budget || (int32_t)unit_srcs.size() > max_slots) return false;
+        // (only grids that fit tiles of four blocks take other shapes: which kernel a stage gets stays the same)
+        if (lin_blocks == kLinDwords && need + (int64_t)unit_srcs.size() * (lin_cover(S.src_dtype) - tile) > budget)
+            return false;
         idle = idle || (small && need > kPackRoom);
         if (idle && p.desc.chunk <= 0) return false;
         const int32_t nslot_batch = (int32_t)(slots.size() / 4) - s0;
@@ -482,7 +484,7 @@ bool build_group_lds(const PlanImpl &p, Stage &S, int variant)
     S.group_tile = tile_step;
     S.group_rpw = rpw;
     S.group_lin = lin;
-    S.lin_short = lin_short;
+    S.lin_blocks = lin_blocks;
     S.group_pack = pack;
     S.wide_level = wide_level;
     S.wide_inputs = wide_inputs;
@@ -909,7 +911,9 @@ snd_status build_plan(const snd_plan_desc &d, PlanImpl &p, std::string &err)
     for (Stage &S : p.stages) {
         S.kernel = kKernelGeneric;
         if (d.generic_kernels) continue;
-        if (S.final_stage && (build_group_lds(p, S, kGroupLin) || build_group_lds(p, S, kGroupPack) ||
+        const int blocks = lin_blocks(S.rows, p.n_out);
+        if (S.final_stage && (build_group_lds(p, S, kGroupLin, blocks) ||
+                              (blocks != 4 && build_group_lds(p, S, kGroupLin)) || build_group_lds(p, S, kGroupPack) ||
                               build_group_lds(p, S, kGroupFast) || (!bits && build_group_lds(p, S, kGroupGeneric)))) {
             if (S.pack_idle) {
                 Stage A = S;

@@ -76,7 +76,7 @@ struct Stage {
     // row's inputs that start a dword (4 bits per row), and last n.  The packed kernel keeps its
     // tables (kPackWords and kPackSmemWords per batch and wave) in the same two vectors.
     bool group_lin = false;
-    bool lin_short = false;  // tiles of kLinShortTile
+    int32_t lin_blocks = 0;  // f32 rows: blocks of a tile, or kLinDwords (0 on 16-bit rows)
     bool group_pack = false;
     // packed kernel, two-row shapes: the super nodes' level and largest number of inputs, and that of
     // the nodes one level below
@@ -122,22 +122,46 @@ constexpr int kFastBuffers = 2;           // batch b + 1 lands while b is read
 constexpr int kGroupFastLdsBytes = 81920; // per buffer (two fill the 160 KB of LDS)
 constexpr int kGroupTileBits = 2048;  // bit rows: 32 samples (one word) per lane
 // Linear kernel shape per row storage: four rows per wave (64-row groups share the staged windows).  f32
-// rows: tiles of 4 x 252 samples, read by 16-byte units that run up to four samples past the tile.
+// rows: tiles of 4 x 252 samples, read by 16-byte units that run up to four samples past the tile, or other
+// shapes (lin_blocks).
 // 16-bit rows: tiles of 1024 samples, lane i owning the sample pairs 2 i + 128 v (v = 0 .. 7); an input
 // that starts in the upper half of a dword reads one dword past the tile, so those windows stage one
 // 16-byte unit more.
 constexpr int kLinBlock = 4 * 63;
-// f32 rows of one group take tiles of two blocks where four would give fewer workgroups than half the CUs
-// (final stage of 1024 channels, 24 DMs x 30,014 samples: 391 us in tiles of four, 243 of two; 64 x 2514
-// 369 and 268; 300 channels, 16 x 9017: 122 and 81).
-constexpr int kLinShortTile = 2 * kLinBlock;
-constexpr int64_t kLinMinBlocks = 128;
-constexpr int lin_rows(int) { return 4; }
-constexpr int lin_tile(int src_dtype) { return src_dtype == SND_DT_F32 ? 4 * kLinBlock : 1024; }
-inline int lin_cover(int src_dtype) { return src_dtype == SND_DT_F32 ? lin_tile(src_dtype) + 4 : lin_tile(src_dtype) + 8; }
+constexpr int kLinDwords = 8;   // (in place of the blocks of a tile) eight rows per wave, 512 samples by dwords
+constexpr int64_t kLinMinBlocks = 128, kLinRound = 256;
+constexpr int lin_rows(int src_dtype, int blocks = 4) { return src_dtype == SND_DT_F32 && blocks == kLinDwords ? 8 : 4; }
+constexpr int lin_tile(int src_dtype, int blocks = 4)
+{
+    return src_dtype != SND_DT_F32 ? 1024 : blocks == kLinDwords ? 512 : blocks * kLinBlock;
+}
+constexpr int lin_cover(int src_dtype, int blocks = 4)
+{
+    return lin_tile(src_dtype, blocks) + (src_dtype != SND_DT_F32 ? 8 : blocks == kLinDwords ? 0 : 4);
+}
+// Blocks of a tile on f32 rows.  Two where the rows are one group and tiles of four would give fewer
+// workgroups than half the CUs (final stage of 1024 channels, 24 DMs x 30,014 samples: 214 us in tiles of four,
+// 151 of two; 64 x 2514 221 and 158; 300 channels, 16 x 9017: 66 and 48).  Else four, or eight rows by dwords
+// where that takes so many fewer rounds of a workgroup on every CU that they make up for its longer ones (320
+// against 290 us a round at 1024 channels x 4096 DMs): rows of 2^k samples divide into its tiles alone.  1024
+// channels x 4096 DMs x 8192 samples 782 us by four blocks, 639 by dwords; 16,384 1376 and 1265; 256 x 2000 x
+// 8192 159 and 108; but 8064 samples 583 and 690, 16,128 1154 and 1331, 65,536 4906 and 5122.
+inline int lin_blocks(int64_t rows, int64_t n_out)
+{
+    auto wgs = [&](int b) {
+        const int64_t gr = kGroupRows * lin_rows(SND_DT_F32, b), tile = lin_tile(SND_DT_F32, b);
+        return ((rows + gr - 1) / gr) * ((n_out + tile - 1) / tile);
+    };
+    auto rounds = [&](int b) { return (wgs(b) + kLinRound - 1) / kLinRound; };
+    if (rows <= kGroupRows * lin_rows(SND_DT_F32) && wgs(4) < kLinMinBlocks) return 2;
+    return 32 * rounds(kLinDwords) < 29 * rounds(4) ? kLinDwords : 4;
+}
 // inputs per row and batch: the wave's offset words fit 64 lanes, and the 16-bit kernels pack
 // each row's count of inputs of one dword phase in 4 bits
-constexpr int lin_max_batch_entries(int src_dtype) { return 64 / lin_rows(src_dtype) < 15 ? 64 / lin_rows(src_dtype) : 15; }
+constexpr int lin_max_batch_entries(int src_dtype, int blocks = 4)
+{
+    return 64 / lin_rows(src_dtype, blocks) < 15 ? 64 / lin_rows(src_dtype, blocks) : 15;
+}
 constexpr int kLinWords = 64;                  // offset words per (batch, wave), at most
 // Copy chunks of a wave and batch: up to 64 consecutive 16-byte units of the LDS buffer each, from one
 // window or the end of one and the start of the next (windows are laid out one after the other, and a
@@ -341,7 +365,8 @@ struct GroupArgs {
     const int32_t *node_closes;  // specialised kernel only
     const uint32_t *lin_smem;    // linear kernel only
     const uint32_t *lin;
-    int32_t lin_kernel;          // 1: linear kernel, 2: packed kernel, 3: linear kernel, short tiles
+    int32_t lin_kernel;          // 1: linear kernel, 2: packed kernel
+    int32_t lin_blocks;          // linear kernel on f32 rows: blocks of a tile, or kLinDwords
     int32_t xcd_chunk;           // DM groups of one time tile dealt to each XCD in turn
     int32_t ngroups;
     int32_t n_entries;
@@ -416,7 +441,7 @@ int launch_ring_put_bits(const uint32_t *chunk, int64_t chunk_words, uint32_t *r
 // levels above its super nodes).
 inline int stage_shape(const Stage &S)
 {
-    if (S.kernel == kKernelGroupLds && S.group_lin) return S.lin_short ? -2 : -1;
+    if (S.kernel == kKernelGroupLds && S.group_lin) return S.lin_blocks ? -S.lin_blocks : -1;
     if (S.kernel == kKernelGroupLds && S.group_pack)
         return -(S.group_f1 ? 1000 * S.group_f1 + S.depth : 16000 + 10 * (S.depth - S.wide_level) + S.depth);
     if (S.kernel == kKernelGroupLds && S.group_f1 > 0) return 1000 * S.group_f1 + S.depth;

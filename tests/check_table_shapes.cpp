@@ -67,7 +67,7 @@ int main()
         const PlanImpl P = plan_for(s.nchan, s.ndm, s.branching, s.cluster, s.mode, s.dt, s.dm_max, 5000);
         const Stage &S = P.stages.back();
         CHECK(P.stages.size() >= 2 && (s.mode == F ? S.group_lin : S.group_pack) && S.group_rpw == s.rpw);
-        if (!S.lin_short) check_stage(P, S);  // (its cover is that of the long tiles)
+        if (S.lin_blocks % 4 == 0 && S.lin_blocks <= 4) check_stage(P, S);  // (its cover is that of tiles of four blocks)
         check_reach(P, S);
         // offset words in the device image: each wave's inputs one after the other, as the kernel walks them
         const uint32_t *image = reinterpret_cast<const uint32_t *>(&P.table[(size_t)S.off_lin]);

@@ -805,3 +805,32 @@ def test_graded_packed_trees_of_one_level(snd, orc, top, cap):
     y = to_np(p.execute(xt, workspace=ws))
     want, _ = orc.snd_dedup(x, f, d, mode="graded", cluster=4, branching=4, cap=cap)
     assert np.array_equal(y, want.astype(y.dtype))
+
+
+def test_float_final_stage_shapes_agree(snd, orc):
+    """Grids whose f32 final stage takes eight rows by dwords (8065 to 8192 samples of these DMs) or tiles of
+    four blocks, the last of them summed as one, two or four: the same sums in the same order, bit for bit,
+    from unaligned output rows too, and the FP64 oracle's within the tolerance."""
+    f = synth.channel_freqs(64)
+    dms = np.linspace(0.0, 60.0, 2000)
+    d = orc.delays(f, dms, 0.138e-3)
+    top = 9072
+    x = synth.make_rng(8192).standard_normal((64, int(d.max()) + top)).astype(np.float32)
+    xt = torch.from_numpy(x).cuda()
+    planes = {}
+    for n_out in (8064, 8065, 8100, 8192, 8193, 8064 + 253, 8064 + 505, top):
+        p = snd.Plan(f, dms, 0.138e-3, int(d.max()) + n_out, mode="float")
+        assert p.info["stage_kernel"] == ["anchored", "group_lin"] and p.n_out == n_out
+        out = torch.full((p.ndm, n_out + 5), -3.0, device="cuda")
+        p.execute(xt, out=out[:, 3:3 + n_out])
+        y = out.cpu().numpy()
+        assert np.all(y[:, :3] == -3.0) and np.all(y[:, 3 + n_out:] == -3.0)
+        planes[n_out] = (y[:, 3:3 + n_out], p.info["stage_batches"][1])
+    few = planes[8192][1]
+    for n_out, (y, batches) in planes.items():
+        assert (batches == few) == (8064 < n_out <= 8192)  # groups of 128 rows, not of 64
+        assert np.array_equal(y, planes[top][0][:, :n_out]), n_out
+    rng = synth.make_rng(5)
+    ks, ts = rng.integers(0, 2000, 500), rng.integers(0, top, 500)
+    want = orc.snd_points(x, f, d, ks, ts, mode="float", cluster=4, branching=4)
+    assert rel_rms(planes[top][0][ks, ts], want) <= FP32_TOL
