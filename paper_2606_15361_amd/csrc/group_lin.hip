@@ -14,6 +14,8 @@
 //    behind uniform branches.  Sums alone went from 8.5 to 6.7 ms at 1024 channels x 4096 DMs x
 //    102,748 samples, the kernel from 8.9 to 8.2: the copies, 46 GB from a plane of 20 GB, take 6.1 by
 //    themselves, a batch holds 2.4 inputs, and its copies start only when the batch before is done.
+//    Tiles of two blocks, or eight rows of 512 samples by dwords, where those fit the grid to the chip
+//    (lin_blocks).
 //  * bf16 / f16 rows: reads are dwords at o + 4 i + 256 v for an input at LDS byte offset o (v = 0 .. 7),
 //    which pair into stride-64 reads of two.  Lane i owns the sample pairs (2 i + 128 v, 2 i + 1 + 128 v).
 //    An input whose first sample sits in the upper half of a dword takes the upper half of that

@@ -183,8 +183,9 @@ __device__ __forceinline__ void leaf_dwords(const unsigned char *lds, const uint
 // behind, and one row is not enough stores in flight.  A one-level row's table words are one
 // 32-byte record, fetched a row ahead, and 64 VGPRs let two workgroups of 16 waves share a CU.
 // With that and the packed u8 sums the leaf stage went from 1.60 to 1.35 ms (u8, 1024 channels x
-// 4096 DMs x 131,072 samples; its stores alone need 0.9), 476 to 331 us (u8, 64 channels x 3000
-// DMs; row ends by the same dwords: 100 channels, 600 rows of 580 samples 38 us, one by one 40, now 36), and for eight beams of 8192 samples from 0.80 to 0.73 ms (u8) and 1.18 to 1.06 (bf16).
+// 4096 DMs x 131,072 samples; its stores alone need 0.9), 476 to 331 us (u8, 64 channels x 3000 DMs), and for
+// eight beams of 8192 samples from 0.80 to 0.73 ms (u8) and 1.18 to 1.06 (bf16).  Row ends of u8 rows by the
+// same dwords: 100 channels, 600 rows of 580 samples 40 to 36 us.
 // REC: rows by records, in one-level stages.  Without, a row reads its words from the plan's row and entry
 // tables, which holds its stores back: the better form where those alone set the pace (see tables_pay).
 template <int MODE, typename TI, typename TO, int MAXD, bool REC>
